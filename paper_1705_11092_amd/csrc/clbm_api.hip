@@ -129,6 +129,30 @@ int default_vec(int storage)
     }
 }
 
+// Compute units of the current device.
+int compute_units()
+{
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1) {
+        (void)hipGetLastError();
+        return 256;
+    }
+    return n;
+}
+
+// Whether a two-buffer FP32 or FP64 lattice steps four steps per launch.
+// Measured (us per step, sweeps against pairs): FP32 512^2 4.0 / 3.6, 4096 x
+// 64 3.8 / 3.6, 300 x 2000 5.8 / 6.5, 768^2 6.3 / 6.6, 1024^2 8.0 / 9.8,
+// 3000^2 44.8 / 66.1; FP64 512^2 5.0 / 4.8, 300 x 2000 8.5 / 11.3, 1024^2
+// 12.6 / 16.4: below about 550,000 nodes a wave's rows are too few for the
+// rows it collides again.
+constexpr int64_t kSweepMinNodes = 550000;
+bool sweep_by_default(const clbm::LatDesc &d)
+{
+    return d.nx >= 64 && d.ny >= 64 && (int64_t)d.nx * d.ny >= kSweepMinNodes;
+}
+
 // Check that [p, p + bytes) lies inside one HIP device allocation.
 int check_device_range(const void *p, size_t bytes, const char *name)
 {
@@ -259,6 +283,7 @@ struct clbm_handle {
     size_t lds0 = 0;             // the same for in-place phase-0 steps
     int pairs = -1;              // two fused steps per launch: 1 where supported,
                                  // 0 never, -1 the default (pairs_by_default)
+    clbm::SweepPlan sweep{};     // four fused steps per launch by default (vec 0: never)
     int graph_steps = 64;
     hipGraphExec_t graph[2] = {nullptr, nullptr};
 };
@@ -290,19 +315,35 @@ bool use_pairs(const clbm_handle *h)
     return h->pairs < 0 ? pairs_by_default(h->d) : h->pairs != 0;
 }
 
+// Whether steps go four per launch (the sweep kernel): by default, where the
+// lattice has a plan; an explicit clbm_set_step_pairs(1) keeps pairs.
+bool use_sweeps(const clbm_handle *h) { return h->pairs < 0 && h->sweep.vec != 0 && use_pairs(h); }
+
+// The next launch of a run with `left` steps to go, from state `parity`: four
+// steps, two or one, whichever the lattice takes.  Each launch flips the
+// buffer or phase.
+hipError_t launch_next(const clbm_handle *h, int parity, int64_t left, hipStream_t s, int *taken)
+{
+    if (left >= clbm::kSweepSteps && use_sweeps(h)) {
+        *taken = clbm::kSweepSteps;
+        return clbm::launch_sweep(h->d, parity, h->sweep, s);
+    }
+    if (left >= 2 && use_pairs(h)) {
+        *taken = 2;
+        return clbm::launch_step2(h->d, parity, s);
+    }
+    *taken = 1;
+    return clbm::launch_step(h->d, parity, h->vec, step_lds(h, parity), s);
+}
+
 int build_graph(clbm_handle *h, int parity)
 {
     hipGraph_t g = nullptr;
     if (!h->cap) HIPCHK(hipStreamCreateWithFlags(&h->cap, hipStreamNonBlocking));
     HIPCHK(hipStreamBeginCapture(h->cap, hipStreamCaptureModeThreadLocal));
     hipError_t le = hipSuccess;
-    if (use_pairs(h)) {
-        for (int k = 0; k < h->graph_steps / 2 && le == hipSuccess; ++k)
-            le = clbm::launch_step2(h->d, (parity + k) & 1, h->cap);
-    } else {
-        for (int k = 0; k < h->graph_steps && le == hipSuccess; ++k)
-            le = clbm::launch_step(h->d, (parity + k) & 1, h->vec, step_lds(h, (parity + k) & 1), h->cap);
-    }
+    for (int done = 0, p = parity, n = 0; done < h->graph_steps && le == hipSuccess; done += n, p ^= 1)
+        le = launch_next(h, p, h->graph_steps - done, h->cap, &n);
     hipError_t ce = hipStreamEndCapture(h->cap, &g);
     if (le != hipSuccess) {
         if (g) (void)hipGraphDestroy(g);
@@ -386,6 +427,9 @@ int clbm_create(const clbm_config *cfg, clbm_handle **out)
     h->vec = default_vec(cfg->storage);
     h->occ = default_occupancy(cfg->storage, 2 * need, inplace, 1);
     h->lds = lds_for_occupancy(h->occ);
+    if (clbm::step2_supported(d) && (cfg->storage == CLBM_F32 || cfg->storage == CLBM_F64) &&
+        sweep_by_default(d))
+        h->sweep = clbm::sweep_plan(d.nx, d.ny, eb, 4 * compute_units());
     h->lds0 = inplace ? lds_for_occupancy(default_occupancy(cfg->storage, 2 * need, true, 0)) : h->lds;
 
     reap_retired();
@@ -527,23 +571,21 @@ int clbm_step(clbm_handle *h, int64_t nsteps)
         return CLBM_OK;
     }
     const bool pairs = use_pairs(h);
+    const int per = use_sweeps(h) ? clbm::kSweepSteps : (pairs ? 2 : 1);
+    // Launches of one graph: whole groups of `per` steps, then pairs (graph_steps is even).
+    const int launches = h->graph_steps / per + h->graph_steps % per / 2;
     int64_t left = nsteps;
     while (left > 0) {
         if (h->graph_steps > 0 && left >= h->graph_steps) {
             if (!h->graph[h->parity] && (rc = build_graph(h, h->parity))) return rc;
             HIPCHK(hipGraphLaunch(h->graph[h->parity], h->stream));
             left -= h->graph_steps;
-            // graph_steps is even: one-step launches leave the parity as it
-            // was, fused pairs flip it once per launch.
-            if (pairs) h->parity ^= (h->graph_steps / 2) & 1;
-        } else if (pairs && left >= 2) {
-            HIPCHK(clbm::launch_step2(h->d, h->parity, h->stream));
-            h->parity ^= 1;
-            left -= 2;
+            h->parity ^= launches & 1;
         } else {
-            HIPCHK(clbm::launch_step(h->d, h->parity, h->vec, step_lds(h, h->parity), h->stream));
+            int n = 0;
+            HIPCHK(launch_next(h, h->parity, left, h->stream, &n));
             h->parity ^= 1;
-            left -= 1;
+            left -= n;
         }
     }
     h->steps += nsteps;

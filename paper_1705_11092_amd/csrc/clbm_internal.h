@@ -172,6 +172,66 @@ inline int tile_h(int shape, int storage)
     return storage == ST_F64 ? h / 2 : h;
 }
 
+// Four fused steps per launch (clbm_sweep.h): a wave marches down the rows of
+// a strip of 64 lanes x vec columns.
+constexpr int kSweepSteps = 4;
+struct SweepPlan {
+    int32_t vec;     // columns per lane (1 or 2); 0: this lattice takes no sweeps
+    int32_t strips;  // strips across the lattice
+    int32_t rows;    // rows per chunk: chunk c is rows [c rows, (c + 1) rows)
+    int32_t units;   // strips x chunks, one wave each
+    int32_t groups;  // groups of vec columns along a row: ceil(nx / vec)
+    int32_t halo;    // lanes at each end of a wave that are collided, not stored
+};
+
+// Microseconds of one launch under a plan, from what bounds it: the
+// VALU issue of the busiest SIMD (a wave collides rows + K - 1 rows of each
+// of K levels on average, 0.222 us per level and column of a lane in FP32,
+// 0.238 in FP64; one wave per SIMD hides its latencies to 72 % of the issue
+// rate, two to 92 %), or HBM at 5.3 TB/s (3.6 with one wave per SIMD; each
+// chunk reads 2 K rows beyond its own), plus 3 us of launch.  Within 10 % of
+// the times measured for 24 plans of 1024^2, 2048^2 and 4096^2 lattices.
+inline double sweep_us(int64_t nodes, int eb, int simds, int vec, int rows, int64_t units)
+{
+    const int64_t n = (units + simds - 1) / simds;  // waves on the busiest SIMD
+    const double eff = n == 1 ? 0.72 : (n == 2 ? 0.92 : 0.95);
+    const double valu = kSweepSteps * (eb == 8 ? 0.238 : 0.222) * vec * n * (rows + kSweepSteps) / eff;
+    const double state = 9.0 * nodes * eb;
+    const double mem = state * (2.0 + 2.0 * kSweepSteps / rows) / (n == 1 ? 3.6e6 : 5.3e6);
+    return (valu > mem ? valu : mem) + 3.0;
+}
+
+// The plan of a lattice: columns per lane and rows per chunk with the least
+// sweep_us among those that fill the SIMDs 1 .. 8 times.
+inline SweepPlan sweep_plan(int nx, int ny, int eb, int simds)
+{
+    SweepPlan best{};
+    double best_us = 0.0;
+    for (int vec = 1; vec <= 2; ++vec) {
+        SweepPlan p{};
+        p.vec = vec;
+        p.groups = (nx + vec - 1) / vec;
+        // Every level loses one column at each side; the last group of a
+        // ragged row holds fewer than vec of them.
+        p.halo = (kSweepSteps + vec - 1) / vec + (nx % vec ? 1 : 0);
+        p.strips = (p.groups + 63 - 2 * p.halo) / (64 - 2 * p.halo);
+        for (int n = 1; n <= 8; ++n) {
+            int64_t chunks = (int64_t)n * simds / p.strips;
+            if (chunks < 1) continue;
+            if (chunks > ny) chunks = ny;
+            p.rows = (int)((ny + chunks - 1) / chunks);
+            const int64_t units = (int64_t)p.strips * ((ny + p.rows - 1) / p.rows);
+            p.units = (int32_t)units;
+            const double us = sweep_us((int64_t)nx * ny, eb, simds, vec, p.rows, units);
+            if (best.vec == 0 || us < best_us) {
+                best = p;
+                best_us = us;
+            }
+        }
+    }
+    return best;
+}
+
 // Lattice descriptors carried in one upload kernel's arguments.
 constexpr int kUploadMax = 12;
 struct UploadPayload {
@@ -221,6 +281,11 @@ hipError_t launch_resident(const LatDesc &d, int src, int nsteps, hipStream_t s)
 // buffers, any storage type, any force but Shan-Chen (step2_supported).
 bool step2_supported(const LatDesc &d);
 hipError_t launch_step2(const LatDesc &d, int src, hipStream_t s);
+// Four fused steps from buffer src into src ^ 1 under a plan of sweep_plan:
+// FP32 or FP64 storage, otherwise as step2_supported.
+hipError_t launch_sweep(const LatDesc &d, int src, const SweepPlan &p, hipStream_t s);
+template <int ST>
+hipError_t launch_sweep_st(const LatDesc &d, int src, const SweepPlan &p, hipStream_t s);
 // Pair substep `pair` of a batch group whose lattices step in pairs: each
 // lattice with at least 2 pair + 2 steps left takes two fused steps, one
 // with 2 pair + 1 left takes its last single step.  small: every buffer of

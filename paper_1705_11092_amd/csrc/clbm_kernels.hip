@@ -317,6 +317,16 @@ hipError_t launch_step2(const LatDesc &d, int src, hipStream_t s)
     }
 }
 
+hipError_t launch_sweep(const LatDesc &d, int src, const SweepPlan &p, hipStream_t s)
+{
+    if (!step2_supported(d) || p.vec == 0) return hipErrorInvalidValue;
+    switch (d.storage) {
+    case ST_F64: return launch_sweep_st<ST_F64>(d, src, p, s);
+    case ST_F32: return launch_sweep_st<ST_F32>(d, src, p, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
 hipError_t launch_batch2(int storage, const LatDesc *lats, const int32_t *tile_lat, int64_t ntiles, int key,
                          bool small, int pair, int shape, int grid, hipStream_t s)
 {
