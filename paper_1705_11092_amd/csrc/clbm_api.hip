@@ -315,6 +315,17 @@ bool use_pairs(const clbm_handle *h)
     return h->pairs < 0 ? pairs_by_default(h->d) : h->pairs != 0;
 }
 
+// The plan of the fused kernels for the lattice and its force (at creation
+// and when the force changes).
+void plan_fused(clbm_handle *h)
+{
+    const LatDesc &d = h->d;
+    h->sweep = clbm::SweepPlan{};
+    if (clbm::step2_supported(d) && (d.storage == CLBM_F32 || d.storage == CLBM_F64) && sweep_by_default(d))
+        h->sweep = clbm::sweep_plan(d.nx, d.ny, elem_bytes(d.storage), 4 * compute_units(),
+                                    clbm::sweep_max_vec(d.storage, d.force_mode, d.bc_y));
+}
+
 // Whether steps go four per launch (the sweep kernel): by default, where the
 // lattice has a plan; an explicit clbm_set_step_pairs(1) keeps pairs.
 bool use_sweeps(const clbm_handle *h) { return h->pairs < 0 && h->sweep.vec != 0 && use_pairs(h); }
@@ -427,9 +438,7 @@ int clbm_create(const clbm_config *cfg, clbm_handle **out)
     h->vec = default_vec(cfg->storage);
     h->occ = default_occupancy(cfg->storage, 2 * need, inplace, 1);
     h->lds = lds_for_occupancy(h->occ);
-    if (clbm::step2_supported(d) && (cfg->storage == CLBM_F32 || cfg->storage == CLBM_F64) &&
-        sweep_by_default(d))
-        h->sweep = clbm::sweep_plan(d.nx, d.ny, eb, 4 * compute_units());
+    plan_fused(h);
     h->lds0 = inplace ? lds_for_occupancy(default_occupancy(cfg->storage, 2 * need, true, 0)) : h->lds;
 
     reap_retired();
@@ -530,6 +539,7 @@ int clbm_set_force(clbm_handle *h, int32_t kind, const double *params, const dou
     default:
         return fail(CLBM_EINVAL, "unknown force kind");
     }
+    plan_fused(h);
     drop_graphs(h);
     return CLBM_OK;
 }

@@ -184,6 +184,14 @@ struct SweepPlan {
     int32_t halo;    // lanes at each end of a wave that are collided, not stored
 };
 
+// Columns per lane compiled: two need the registers, which an FP64 lattice
+// with walls or a per-node force no longer has (it would spill 78 to 156 of
+// them; 1501 x 703 with both 17.3 us per step, no faster than pairs).
+constexpr int sweep_max_vec(int storage, int force_mode, int bc_y)
+{
+    return storage == ST_F64 && (force_mode == FM_FIELD || bc_y) ? 1 : 2;
+}
+
 // Microseconds of one launch under a plan, from what bounds it: the
 // VALU issue of the busiest SIMD (a wave collides rows + K - 1 rows of each
 // of K levels on average, 0.222 us per level and column of a lane in FP32,
@@ -203,11 +211,11 @@ inline double sweep_us(int64_t nodes, int eb, int simds, int vec, int rows, int6
 
 // The plan of a lattice: columns per lane and rows per chunk with the least
 // sweep_us among those that fill the SIMDs 1 .. 8 times.
-inline SweepPlan sweep_plan(int nx, int ny, int eb, int simds)
+inline SweepPlan sweep_plan(int nx, int ny, int eb, int simds, int max_vec)
 {
     SweepPlan best{};
     double best_us = 0.0;
-    for (int vec = 1; vec <= 2; ++vec) {
+    for (int vec = 1; vec <= max_vec; ++vec) {
         SweepPlan p{};
         p.vec = vec;
         p.groups = (nx + vec - 1) / vec;

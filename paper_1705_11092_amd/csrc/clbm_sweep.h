@@ -175,26 +175,60 @@ __device__ __forceinline__ void sweep_strip(const LatDesc &d, int src, int q, in
         }
     };
     auto wrap = [&](int y) { return y < 0 ? y + d.ny : (y >= d.ny ? y - d.ny : y); };
+    // The body force of row y (any row of the march: beyond a wall the
+    // wall's, not used).  Memory waits are in issue order, so the forces of
+    // levels 2 .. K of an iteration are loaded ahead of the next row's state,
+    // and level 1's with that state; a row's force is the same for the whole
+    // wave and comes by scalar loads.
+    R F[K][2][V];
+    auto load_force = [&](int l, int y) {
+        if constexpr (FM == FM_CONST) {
+#pragma unroll
+            for (int k = 0; k < V; ++k) {
+                F[l][0][k] = R(d.Fx);
+                F[l][1][k] = R(d.Fy);
+            }
+        } else {
+            y = WALL ? (y < 0 ? 0 : (y >= d.ny ? d.ny - 1 : y)) : wrap(y);
+            if constexpr (FM == FM_ROW) {
+                typedef const __attribute__((address_space(4))) R *Table;
+                const R f = reinterpret_cast<Table>(reinterpret_cast<uint64_t>(d.force))[y];
+#pragma unroll
+                for (int k = 0; k < V; ++k) {
+                    F[l][0][k] = f;
+                    F[l][1][k] = R(0);
+                }
+            } else if constexpr (SEAM) {
+#pragma unroll
+                for (int k = 0; k < V; ++k)
+                    force_at<R, FM>(d, base + k < d.nx ? base + k : d.nx - 1, y, F[l][0][k], F[l][1][k]);
+            } else {
+                const R *f = static_cast<const R *>(d.force) + (int64_t)y * d.nx;
+                const Pack<R, V> a = load_pack<R, V, false>(f + (uint32_t)base);
+                const Pack<R, V> b = load_pack<R, V, false>(f + (int64_t)d.nx * d.ny + (uint32_t)base);
+#pragma unroll
+                for (int k = 0; k < V; ++k) {
+                    F[l][0][k] = a.v[k];
+                    F[l][1][k] = b.v[k];
+                }
+            }
+        }
+    };
 
     const int first = ya - (K - 1), iters = (yb - ya) + 2 * K - 2;
+    load_force(0, first);
     if (!WALL || first >= 0) load_row(WALL ? first : wrap(first));
     for (int t = 0; t < iters; ++t) {
         const int y1 = first + t;  // level 1's row
         R p[9][V];                 // the last collided level's row
-        auto update = [&](int y, R (&g)[9][V], bool last) {
-            // The body force, the collision and the rounding of row y.
-            R Fx[V], Fy[V];
-#pragma unroll
-            for (int k = 0; k < V; ++k) {
-                const int x = base + k;
-                force_at<R, FM>(d, SEAM && x >= d.nx ? d.nx - 1 : x, y, Fx[k], Fy[k]);
-            }
+        auto update = [&](int y, R (&g)[9][V], const R (&f)[2][V], bool last) {
+            // The collision and the rounding of row y.
 #pragma unroll
             for (int k = 0; k < V; ++k) {
                 R n[9];
 #pragma unroll
                 for (int i = 0; i < 9; ++i) n[i] = g[i][k];
-                collide<R, SCH>(n, Fx[k], Fy[k], rt);
+                collide<R, SCH>(n, f[0][k], f[1][k], rt);
 #pragma unroll
                 for (int i = 0; i < 9; ++i) g[i][k] = n[i];
             }
@@ -224,6 +258,8 @@ __device__ __forceinline__ void sweep_strip(const LatDesc &d, int src, int q, in
             }
         };
 
+#pragma unroll
+        for (int l = 1; l < K; ++l) load_force(l, y1 - l);
         const bool on1 = !WALL || (y1 >= 0 && y1 < d.ny);
         if (on1) {
             const int y = WALL ? y1 : wrap(y1);
@@ -244,11 +280,12 @@ __device__ __forceinline__ void sweep_strip(const LatDesc &d, int src, int q, in
                     for (int k = 0; k < V; ++k) g[i][k] = v[k];
                 }
             }
-            update(y, g, K == 1);
+            update(y, g, F[0], K == 1);
         }
         // The next row's loads, in flight while the other levels collide.
         if (t + 1 < iters) {
             const int yn = y1 + 1;
+            load_force(0, yn);
             if (!WALL || (yn >= 0 && yn < d.ny)) load_row(WALL ? yn : wrap(yn));
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -310,17 +347,20 @@ __device__ __forceinline__ void sweep_strip(const LatDesc &d, int src, int q, in
                     }
                 }
             }
-            if (go) update(WALL ? yl : wrap(yl), g, l == K - 1);
+            if (go) update(WALL ? yl : wrap(yl), g, F[l], l == K - 1);
         }
     }
 }
 
 // Waves per SIMD the compiler must leave room for: 2 with two columns per
-// lane (FP32 177 VGPRs; FP64 would take 274, one wave), 3 with one.
+// lane (FP32 162-179 VGPRs; FP64 256), 3 with one (FP32 90-107, FP64 162-168),
+// but 2 in FP64 with a per-node force, which would spill.
+template <int ST, int FM, int V>
+constexpr int sweep_waves() { return V == 1 && !(ST == ST_F64 && FM == FM_FIELD) ? 3 : 2; }
+
 template <int ST, int FM, int SCH, int K, int V, bool WALL>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(V == 1 ? 3 : 2))) void k_sweep(LatDesc d,
-                                                                                                     int src,
-                                                                                                     SweepPlan p)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sweep_waves<ST, FM, V>()))) void
+k_sweep(LatDesc d, int src, SweepPlan p)
 {
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int u = (int)xcd_order(blockIdx.x, gridDim.x) * (kBlock / 64) + w;
@@ -351,10 +391,14 @@ hipError_t launch_sweep_st(const LatDesc &d, int src, const SweepPlan &p, hipStr
     switch ((d.force_mode * 2 + d.scheme) * 2 + (d.bc_y ? 1 : 0)) {
 #define CLBM_SW(FM, SCH, WALL)                                                    \
     case (FM * 2 + SCH) * 2 + WALL:                                               \
-        if (p.vec == 2)                                                           \
-            k_sweep<ST, FM, SCH, kSweepSteps, 2, WALL><<<grid, block, 0, s>>>(d, src, p); \
-        else                                                                      \
-            k_sweep<ST, FM, SCH, kSweepSteps, 1, WALL><<<grid, block, 0, s>>>(d, src, p); \
+        if constexpr (sweep_max_vec(ST, FM, WALL) == 2) {                         \
+            if (p.vec == 2) {                                                     \
+                k_sweep<ST, FM, SCH, kSweepSteps, 2, WALL><<<grid, block, 0, s>>>(d, src, p); \
+                break;                                                            \
+            }                                                                     \
+        }                                                                         \
+        if (p.vec != 1) return hipErrorInvalidValue;                              \
+        k_sweep<ST, FM, SCH, kSweepSteps, 1, WALL><<<grid, block, 0, s>>>(d, src, p); \
         break;
 #define CLBM_SW2(FM, SCH) CLBM_SW(FM, SCH, 0) CLBM_SW(FM, SCH, 1)
         CLBM_SW2(FM_CONST, SCH_CONSISTENT)
