@@ -141,18 +141,6 @@ int compute_units()
     return n;
 }
 
-// Whether a two-buffer FP32 or FP64 lattice steps four steps per launch.
-// Measured (us per step, sweeps against pairs): FP32 512^2 4.0 / 3.6, 4096 x
-// 64 3.8 / 3.6, 300 x 2000 5.8 / 6.5, 768^2 6.3 / 6.6, 1024^2 8.0 / 9.8,
-// 3000^2 44.8 / 66.1; FP64 512^2 5.0 / 4.8, 300 x 2000 8.5 / 11.3, 1024^2
-// 12.6 / 16.4: below about 550,000 nodes a wave's rows are too few for the
-// rows it collides again.
-constexpr int64_t kSweepMinNodes = 550000;
-bool sweep_by_default(const clbm::LatDesc &d)
-{
-    return d.nx >= 64 && d.ny >= 64 && (int64_t)d.nx * d.ny >= kSweepMinNodes;
-}
-
 // Check that [p, p + bytes) lies inside one HIP device allocation.
 int check_device_range(const void *p, size_t bytes, const char *name)
 {
@@ -278,13 +266,15 @@ struct clbm_handle {
     double *d_out = nullptr;     // reduced totals on the device
     int vec = 4;
     int occ = 0;                 // blocks per compute unit of the step kernel (0: no cap)
-    int64_t resident_max = clbm::kResidentMaxGroups;  // resident kernel up to this many groups
+    int64_t resident_max = 0;    // resident kernel up to this many groups
     size_t lds = 0;              // dynamic LDS per block that enforces occ
     size_t lds0 = 0;             // the same for in-place phase-0 steps
     int pairs = -1;              // two fused steps per launch: 1 where supported,
                                  // 0 never, -1 the default (pairs_by_default)
     clbm::SweepPlan sweep{};     // four fused steps per launch by default (vec 0: never)
+    clbm::TilePlan tile{};       // up to tile.steps fused steps per launch by default (0: never)
     int graph_steps = 64;
+    int graph_launches = 0;      // launches of one graph: each flips the parity
     hipGraphExec_t graph[2] = {nullptr, nullptr};
 };
 
@@ -316,25 +306,53 @@ bool use_pairs(const clbm_handle *h)
 }
 
 // The plan of the fused kernels for the lattice and its force (at creation
-// and when the force changes).
+// and when the force changes): the tile kernel or the sweep kernel, whichever
+// model gives less time per step.  The two cross near a million nodes.  The
+// 16-bit types have no sweeps (their pair kernel is as fast: FP16-SR 4096^2
+// 202 against 181 GLUPS); their tiles step faster than pairs up to
+// kTileMaxNodes16.
+constexpr int64_t kTileMaxNodes16 = 600000;
 void plan_fused(clbm_handle *h)
 {
     const LatDesc &d = h->d;
     h->sweep = clbm::SweepPlan{};
-    if (clbm::step2_supported(d) && (d.storage == CLBM_F32 || d.storage == CLBM_F64) && sweep_by_default(d))
-        h->sweep = clbm::sweep_plan(d.nx, d.ny, elem_bytes(d.storage), 4 * compute_units(),
-                                    clbm::sweep_max_vec(d.storage, d.force_mode, d.bc_y));
+    h->tile = clbm::TilePlan{};
+    if (!clbm::step2_supported(d)) return;
+    const int64_t nodes = (int64_t)d.nx * d.ny;
+    const int eb = elem_bytes(d.storage), cus = compute_units();
+    double us = 0.0;
+    const clbm::TilePlan t = clbm::tile_plan(d.nx, d.ny, eb, cus, &us);
+    if (eb == 2) {
+        if (nodes <= kTileMaxNodes16) h->tile = t;
+        return;
+    }
+    if (d.nx >= 64 && d.ny >= 64) {
+        const clbm::SweepPlan p =
+            clbm::sweep_plan(d.nx, d.ny, eb, 4 * cus, clbm::sweep_max_vec(d.storage, d.force_mode, d.bc_y));
+        if (clbm::sweep_us(nodes, eb, 4 * cus, p.vec, p.rows, p.units) / clbm::kSweepSteps < us) {
+            h->sweep = p;
+            return;
+        }
+    }
+    // The tile kernel's offsets are 32-bit.
+    if (9 * d.pitch * rows_allocated(d.nx, d.ny, eb) < ((int64_t)1 << 31)) h->tile = t;
 }
 
-// Whether steps go four per launch (the sweep kernel): by default, where the
-// lattice has a plan; an explicit clbm_set_step_pairs(1) keeps pairs.
-bool use_sweeps(const clbm_handle *h) { return h->pairs < 0 && h->sweep.vec != 0 && use_pairs(h); }
+// Whether steps go several per launch (the tile or the sweep kernel): by
+// default, where the lattice has a plan; an explicit clbm_set_step_pairs
+// keeps pairs or single steps.
+bool use_tiles(const clbm_handle *h) { return h->pairs < 0 && h->tile.steps != 0; }
+bool use_sweeps(const clbm_handle *h) { return h->pairs < 0 && h->sweep.vec != 0; }
 
-// The next launch of a run with `left` steps to go, from state `parity`: four
-// steps, two or one, whichever the lattice takes.  Each launch flips the
-// buffer or phase.
+// The next launch of a run with `left` steps to go, from state `parity`: as
+// many fused steps as the lattice takes.  Each launch flips the buffer or
+// phase.
 hipError_t launch_next(const clbm_handle *h, int parity, int64_t left, hipStream_t s, int *taken)
 {
+    if (use_tiles(h)) {
+        *taken = (int)std::min<int64_t>(left, h->tile.steps);
+        return clbm::launch_tile(h->d, parity, *taken, h->tile, s);
+    }
     if (left >= clbm::kSweepSteps && use_sweeps(h)) {
         *taken = clbm::kSweepSteps;
         return clbm::launch_sweep(h->d, parity, h->sweep, s);
@@ -353,8 +371,9 @@ int build_graph(clbm_handle *h, int parity)
     if (!h->cap) HIPCHK(hipStreamCreateWithFlags(&h->cap, hipStreamNonBlocking));
     HIPCHK(hipStreamBeginCapture(h->cap, hipStreamCaptureModeThreadLocal));
     hipError_t le = hipSuccess;
-    for (int done = 0, p = parity, n = 0; done < h->graph_steps && le == hipSuccess; done += n, p ^= 1)
-        le = launch_next(h, p, h->graph_steps - done, h->cap, &n);
+    int launches = 0;
+    for (int done = 0, n = 0; done < h->graph_steps && le == hipSuccess; done += n, ++launches)
+        le = launch_next(h, (parity + launches) & 1, h->graph_steps - done, h->cap, &n);
     hipError_t ce = hipStreamEndCapture(h->cap, &g);
     if (le != hipSuccess) {
         if (g) (void)hipGraphDestroy(g);
@@ -364,6 +383,7 @@ int build_graph(clbm_handle *h, int parity)
     hipError_t ie = hipGraphInstantiate(&h->graph[parity], g, nullptr, nullptr, 0);
     (void)hipGraphDestroy(g);
     if (ie != hipSuccess) return hip_fail(ie, "hipGraphInstantiate");
+    h->graph_launches = launches;
     return CLBM_OK;
 }
 
@@ -439,6 +459,9 @@ int clbm_create(const clbm_config *cfg, clbm_handle **out)
     h->occ = default_occupancy(cfg->storage, 2 * need, inplace, 1);
     h->lds = lds_for_occupancy(h->occ);
     plan_fused(h);
+    // The tile kernel steps small lattices faster than the resident one
+    // (16 x 16 FP32 1.0 against 1.7 us per step); it needs two buffers.
+    h->resident_max = h->tile.steps ? 0 : clbm::kResidentMaxGroups;
     h->lds0 = inplace ? lds_for_occupancy(default_occupancy(cfg->storage, 2 * need, true, 0)) : h->lds;
 
     reap_retired();
@@ -580,17 +603,13 @@ int clbm_step(clbm_handle *h, int64_t nsteps)
         h->steps += nsteps;
         return CLBM_OK;
     }
-    const bool pairs = use_pairs(h);
-    const int per = use_sweeps(h) ? clbm::kSweepSteps : (pairs ? 2 : 1);
-    // Launches of one graph: whole groups of `per` steps, then pairs (graph_steps is even).
-    const int launches = h->graph_steps / per + h->graph_steps % per / 2;
     int64_t left = nsteps;
     while (left > 0) {
         if (h->graph_steps > 0 && left >= h->graph_steps) {
             if (!h->graph[h->parity] && (rc = build_graph(h, h->parity))) return rc;
             HIPCHK(hipGraphLaunch(h->graph[h->parity], h->stream));
             left -= h->graph_steps;
-            h->parity ^= launches & 1;
+            h->parity ^= h->graph_launches & 1;
         } else {
             int n = 0;
             HIPCHK(launch_next(h, h->parity, left, h->stream, &n));

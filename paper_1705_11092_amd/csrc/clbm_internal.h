@@ -240,6 +240,55 @@ inline SweepPlan sweep_plan(int nx, int ny, int eb, int simds, int max_vec)
     return best;
 }
 
+// Several fused steps per launch in LDS (clbm_tile.h).  A block's region is W
+// x H cells, its tile the K - 1 cells less at each side that its K-th step
+// still has.
+enum RegionShape { kRegion32x24 = 0, kRegion32x32 = 1, kRegion64x16 = 2, kRegion32x16 = 3, kRegionShapes = 4 };
+constexpr int region_w(int shape) { return shape == kRegion64x16 ? 64 : 32; }
+constexpr int region_h(int shape) { return shape == kRegion32x24 ? 24 : (shape == kRegion32x32 ? 32 : 16); }
+constexpr int region_steps(int shape) { return shape == kRegion32x24 || shape == kRegion32x32 ? 8 : 4; }
+struct TilePlan {
+    int32_t steps;    // most steps of one launch (K); 0: this lattice takes no tiles
+    int32_t shape;    // RegionShape
+    int32_t tiles_x;  // tiles across the lattice
+    int32_t tiles;
+};
+
+// Microseconds of one launch of K steps: a fixed part (launch, first loads,
+// last stores) and the tiles a compute unit takes one after another or side
+// by side.  Fitted to 64 x 32 ... 1024^2 lattices (FP32, FP64; us per launch
+// at 200^2, 512^2, 1024^2): 32 x 24 8.8, 29.7, 93 and 10.5, 51.5, 177; 32 x
+// 32 10.3, 27, 73 and 12.6, 44.7, 130; 64 x 16 6.6, 10.6, 31 and 7.8, 16, 52;
+// 32 x 16 5.2, 12.3, 32 and 5.7, 19, 54.
+inline double tile_us(int shape, int eb, int64_t tiles, int cus)
+{
+    const double per32[] = {4.05, 5.5, 3.5, 1.8}, per64[] = {7.4, 9.7, 6.2, 3.05};
+    const int64_t n = (tiles + cus - 1) / cus;
+    return eb == 8 ? 2.2 + per64[shape] * n : 3.5 + per32[shape] * n;
+}
+
+// The plan with the least time per step, which goes to *us_per_step.
+inline TilePlan tile_plan(int nx, int ny, int eb, int cus, double *us_per_step)
+{
+    TilePlan best{};
+    for (int shape = 0; shape < kRegionShapes; ++shape) {
+        TilePlan p{};
+        p.shape = shape;
+        p.steps = region_steps(shape);
+        const int tw = region_w(shape) - 2 * (p.steps - 1), th = region_h(shape) - 2 * (p.steps - 1);
+        p.tiles_x = (nx + tw - 1) / tw;
+        const int64_t tiles = (int64_t)p.tiles_x * ((ny + th - 1) / th);
+        if (tiles > INT32_MAX) continue;
+        p.tiles = (int32_t)tiles;
+        const double us = tile_us(shape, eb, tiles, cus) / p.steps;
+        if (best.steps == 0 || us < *us_per_step) {
+            best = p;
+            *us_per_step = us;
+        }
+    }
+    return best;
+}
+
 // Lattice descriptors carried in one upload kernel's arguments.
 constexpr int kUploadMax = 12;
 struct UploadPayload {
@@ -294,6 +343,11 @@ hipError_t launch_step2(const LatDesc &d, int src, hipStream_t s);
 hipError_t launch_sweep(const LatDesc &d, int src, const SweepPlan &p, hipStream_t s);
 template <int ST>
 hipError_t launch_sweep_st(const LatDesc &d, int src, const SweepPlan &p, hipStream_t s);
+// n <= p.steps fused steps from buffer src into src ^ 1 under a plan of
+// tile_plan: as step2_supported, buffers below 4 G elements.
+hipError_t launch_tile(const LatDesc &d, int src, int n, const TilePlan &p, hipStream_t s);
+template <int ST>
+hipError_t launch_tile_st(const LatDesc &d, int src, int n, const TilePlan &p, hipStream_t s);
 // Pair substep `pair` of a batch group whose lattices step in pairs: each
 // lattice with at least 2 pair + 2 steps left takes two fused steps, one
 // with 2 pair + 1 left takes its last single step.  small: every buffer of

@@ -327,6 +327,20 @@ hipError_t launch_sweep(const LatDesc &d, int src, const SweepPlan &p, hipStream
     }
 }
 
+hipError_t launch_tile(const LatDesc &d, int src, int n, const TilePlan &p, hipStream_t s)
+{
+    if (!step2_supported(d) || n < 1 || n > p.steps) return hipErrorInvalidValue;
+    switch (d.storage) {
+    case ST_F64: return launch_tile_st<ST_F64>(d, src, n, p, s);
+    case ST_F32: return launch_tile_st<ST_F32>(d, src, n, p, s);
+    case ST_F16: return launch_tile_st<ST_F16>(d, src, n, p, s);
+    case ST_BF16: return launch_tile_st<ST_BF16>(d, src, n, p, s);
+    case ST_F16_SR: return launch_tile_st<ST_F16_SR>(d, src, n, p, s);
+    case ST_BF16_SR: return launch_tile_st<ST_BF16_SR>(d, src, n, p, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
 hipError_t launch_batch2(int storage, const LatDesc *lats, const int32_t *tile_lat, int64_t ntiles, int key,
                          bool small, int pair, int shape, int grid, hipStream_t s)
 {

@@ -1,0 +1,208 @@
+// clbm_tile.h -- up to K fused steps per launch in LDS (two-buffer, pull
+// form), for lattices whose steps are otherwise bound by launches and
+// latencies.  Included by the translation units of the storage types, after
+// clbm_step.h.
+//
+// A block owns a tile and collides, in its first step, the tile and K - 1
+// nodes around it (its region, RW x RH cells), pulling the state from the
+// caches; each later step pulls from the block's LDS and is needed on one
+// node less at each side, until the last collides the tile alone and writes
+// it to the other buffer.  A thread keeps the cells of one column (every
+// NT / RW-th row of it), so its slot 0 stays in a register, its force is read
+// once, and its LDS addresses are one register and constants.  LDS holds the
+// other 8 slots twice: a step reads one copy and writes the other, one
+// barrier per step.
+//
+// The region is the periodic plane around the tile, so a lattice smaller than
+// the region simply repeats.  Every node update is the one-step kernel's, so
+// the result is bitwise that of n one-step launches.
+#pragma once
+
+#include "clbm_step.h"
+
+namespace clbm {
+namespace {
+
+// v in [-n, ...) brought into [0, n).
+__device__ __forceinline__ int wrap_any(int v, int n)
+{
+    if (v < 0) v += n;
+    if (v < 0 || v >= n) {
+        v %= n;
+        if (v < 0) v += n;
+    }
+    return v;
+}
+
+template <int RW_, int RH_, int K_, int NT_>
+struct Region {
+    static constexpr int RW = RW_, RH = RH_, K = K_, NT = NT_;
+    static constexpr int TW = RW - 2 * (K - 1), TH = RH - 2 * (K - 1);  // the tile
+    static constexpr int RPP = NT / RW;                                 // rows per pass of the block
+    static constexpr int M = RH / RPP;                                  // cells per thread
+    static_assert(NT % RW == 0 && RH % RPP == 0, "whole rows per pass, whole passes");
+};
+
+// n <= K steps of the tile at (x0, y0) from buffer src into src ^ 1.
+template <int ST, int FM, int SCH, typename RG, bool WALL>
+__device__ __forceinline__ void tile_steps(const LatDesc &d, int src, int x0, int y0, int n,
+                                           typename Storage<ST>::T (&lds)[2][8][RG::RH][RG::RW])
+{
+    using S = Storage<ST>;
+    using T = typename S::T;
+    using R = typename S::R;
+    constexpr int RW = RG::RW, RH = RG::RH, M = RG::M, H = RG::K - 1;
+    const T *in = static_cast<const T *>(d.buf[src]);
+    T *out = static_cast<T *>(d.buf[src ^ 1]);
+    const Rates<R> rt = rates_of<R>(d);
+    const int c = threadIdx.x % RW, rt0 = threadIdx.x / RW;
+    const int we = d.nx - x0 < RG::TW ? d.nx - x0 : RG::TW;  // the tile's columns and rows in the lattice
+    const int he = d.ny - y0 < RG::TH ? d.ny - y0 : RG::TH;
+
+    const int x = wrap_any(x0 - H + c, d.nx);
+    const uint32_t cm = (uint32_t)(x == 0 ? d.nx - 1 : x - 1), c0 = (uint32_t)x,
+                   cp = (uint32_t)(x == d.nx - 1 ? 0 : x + 1);
+    auto row_off = [&](int y) {
+        return (uint32_t)(y >> d.rshift) * (uint32_t)d.bstride + (uint32_t)(y & ((1 << d.rshift) - 1)) * (uint32_t)d.pitch;
+    };
+    const uint32_t ds = (uint32_t)d.dstride;
+
+    T keep[M];
+    R Fx[M], Fy[M];
+    uint32_t node[M];
+    bool lo[M], hi[M], dead[M];
+
+    // One cell after its collision: rounded, then to LDS or, after the last
+    // step, to the other buffer.
+    auto finish = [&](int m, int r, const R (&g)[9], int l, T(*to)[RH][RW]) {
+        T rv[9];
+        if constexpr (S::kDither) {
+            const uint32_t h = hash32(__float_as_uint(g[0]) ^ (node[m] * 0x9e3779b9u));
+#pragma unroll
+            for (int i = 0; i < 9; ++i) rv[i] = S::from_r_sr(g[i], sr_operand(h, i));
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; i += 2) round_pair<ST>(g[i], g[i + 1], &rv[i]);
+            rv[8] = S::from_r(g[8]);
+        }
+        if (l < n) {
+            keep[m] = rv[0];
+#pragma unroll
+            for (int i = 1; i < 9; ++i) to[i - 1][r][c] = rv[i];
+        } else {
+            const uint32_t o = row_off(y0 + r - H) + (uint32_t)(x0 + c - H);
+#pragma unroll
+            for (int i = 0; i < 9; ++i) out[o + (uint32_t)i * ds] = rv[i];
+        }
+    };
+    // Whether step l is needed at region row r and this thread's column: the
+    // tile and n - l nodes around it.
+    auto needed = [&](int r, int l) {
+        const int e = n - l;
+        return r >= H - e && r < H + he + e && c >= H - e && c < H + we + e;
+    };
+
+    // Step 1, from the state.
+    R ga[M][9];
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        const int r = rt0 + m * RG::RPP;
+        int y = y0 - H + r;
+        dead[m] = false;
+        if (WALL) {
+            dead[m] = y < 0 || y >= d.ny;
+            y = y < 0 ? 0 : (y >= d.ny ? d.ny - 1 : y);
+        } else {
+            y = wrap_any(y, d.ny);
+        }
+        lo[m] = WALL && y == 0;
+        hi[m] = WALL && y == d.ny - 1;
+        node[m] = (uint32_t)y * (uint32_t)d.nx + (uint32_t)x;
+        if (!needed(r, 1) || dead[m]) continue;
+        force_at<R, FM>(d, x, y, Fx[m], Fy[m]);
+        const uint32_t r0 = row_off(y);
+        const uint32_t rm = row_off(y == 0 ? (WALL ? 0 : d.ny - 1) : y - 1);
+        const uint32_t rp = row_off(y == d.ny - 1 ? (WALL ? y : 0) : y + 1);
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            uint32_t o = (uint32_t)i * ds + (ey_of(i) == 0 ? r0 : (ey_of(i) == 1 ? rm : rp)) +
+                         (ex_of(i) == 0 ? c0 : (ex_of(i) == 1 ? cm : cp));
+            if (WALL && ((ey_of(i) == 1 && lo[m]) || (ey_of(i) == -1 && hi[m]))) o = (uint32_t)opp_of(i) * ds + r0 + c0;
+            ga[m][i] = S::to_r(in[o]);
+        }
+    }
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        const int r = rt0 + m * RG::RPP;
+        if (!needed(r, 1) || dead[m]) continue;
+        collide<R, SCH>(ga[m], Fx[m], Fy[m], rt);
+        finish(m, r, ga[m], 1, lds[0]);
+    }
+    for (int l = 2; l <= n; ++l) {
+        __syncthreads();
+        auto from = lds[l & 1], to = lds[(l & 1) ^ 1];
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            const int r = rt0 + m * RG::RPP;
+            if (!needed(r, l) || dead[m]) continue;
+            R g[9];
+            g[0] = S::to_r(keep[m]);
+            const T *p = &from[0][r][c];
+#pragma unroll
+            for (int i = 1; i < 9; ++i) {
+                int o = (i - 1) * RH * RW - ey_of(i) * RW - ex_of(i);
+                if (WALL && ((ey_of(i) == 1 && lo[m]) || (ey_of(i) == -1 && hi[m]))) o = (opp_of(i) - 1) * RH * RW;
+                g[i] = S::to_r(p[o]);
+            }
+            collide<R, SCH>(g, Fx[m], Fy[m], rt);
+            finish(m, r, g, l, to);
+        }
+    }
+}
+
+template <int ST, int FM, int SCH, typename RG, bool WALL>
+__global__ __launch_bounds__(RG::NT) void k_tile(LatDesc d, int src, int n, int tiles_x)
+{
+    __shared__ typename Storage<ST>::T lds[2][8][RG::RH][RG::RW];
+    const int t = (int)xcd_order(blockIdx.x, gridDim.x);
+    const int ty = t / tiles_x, tx = t - ty * tiles_x;
+    tile_steps<ST, FM, SCH, RG, WALL>(d, src, tx * RG::TW, ty * RG::TH, n, lds);
+}
+
+}  // namespace
+
+// n <= tile_steps_max(p.shape) fused steps of one lattice from buffer src
+// into buffer src ^ 1.
+template <int ST>
+hipError_t launch_tile_st(const LatDesc &d, int src, int n, const TilePlan &p, hipStream_t s)
+{
+    const dim3 grid((unsigned)p.tiles);
+    switch ((d.force_mode * 2 + d.scheme) * 2 + (d.bc_y ? 1 : 0)) {
+#define CLBM_TL(FM, SCH, WALL)                                                                             \
+    case (FM * 2 + SCH) * 2 + WALL:                                                                        \
+        if (p.shape == kRegion32x24)                                                                       \
+            k_tile<ST, FM, SCH, Region<32, 24, 8, 768>, WALL><<<grid, 768, 0, s>>>(d, src, n, p.tiles_x);  \
+        else if (p.shape == kRegion32x32)                                                                  \
+            k_tile<ST, FM, SCH, Region<32, 32, 8, 1024>, WALL><<<grid, 1024, 0, s>>>(d, src, n, p.tiles_x); \
+        else if (p.shape == kRegion32x16)                                                                  \
+            k_tile<ST, FM, SCH, Region<32, 16, 4, 512>, WALL><<<grid, 512, 0, s>>>(d, src, n, p.tiles_x);  \
+        else                                                                                               \
+            k_tile<ST, FM, SCH, Region<64, 16, 4, ST == ST_F64 ? 1024 : 512>, WALL>                        \
+                <<<grid, ST == ST_F64 ? 1024 : 512, 0, s>>>(d, src, n, p.tiles_x);                         \
+        break;
+#define CLBM_TL2(FM, SCH) CLBM_TL(FM, SCH, 0) CLBM_TL(FM, SCH, 1)
+        CLBM_TL2(FM_CONST, SCH_CONSISTENT)
+        CLBM_TL2(FM_CONST, SCH_GUO_LBL)
+        CLBM_TL2(FM_ROW, SCH_CONSISTENT)
+        CLBM_TL2(FM_ROW, SCH_GUO_LBL)
+        CLBM_TL2(FM_FIELD, SCH_CONSISTENT)
+        CLBM_TL2(FM_FIELD, SCH_GUO_LBL)
+#undef CLBM_TL2
+#undef CLBM_TL
+    default:
+        return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+}  // namespace clbm

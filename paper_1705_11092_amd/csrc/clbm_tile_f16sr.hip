@@ -1,0 +1,6 @@
+// clbm_tile_f16sr.hip -- the multi-step LDS tile kernel for F16-SR storage.
+#include "clbm_tile.h"
+
+namespace clbm {
+template hipError_t launch_tile_st<ST_F16_SR>(const LatDesc &, int, int, const TilePlan &, hipStream_t);
+}  // namespace clbm

@@ -1,0 +1,6 @@
+// clbm_tile_f64.hip -- the multi-step LDS tile kernel for F64 storage.
+#include "clbm_tile.h"
+
+namespace clbm {
+template hipError_t launch_tile_st<ST_F64>(const LatDesc &, int, int, const TilePlan &, hipStream_t);
+}  // namespace clbm
