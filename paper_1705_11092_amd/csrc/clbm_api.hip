@@ -305,13 +305,19 @@ bool use_pairs(const clbm_handle *h)
     return h->pairs < 0 ? pairs_by_default(h->d) : h->pairs != 0;
 }
 
+// The tile kernel's offsets within a buffer are 32-bit.
+bool tile_offsets_fit(const LatDesc &d)
+{
+    return 9 * d.pitch * rows_allocated(d.nx, d.ny, elem_bytes(d.storage)) < ((int64_t)1 << 31);
+}
+
 // The plan of the fused kernels for the lattice and its force (at creation
-// and when the force changes): the tile kernel or the sweep kernel, whichever
-// model gives less time per step.  The two cross near a million nodes.  The
-// 16-bit types have no sweeps (their pair kernel is as fast: FP16-SR 4096^2
-// 202 against 181 GLUPS); their tiles step faster than pairs up to
-// kTileMaxNodes16.
-constexpr int64_t kTileMaxNodes16 = 600000;
+// and when the force changes): the tile kernel, the sweep kernel or pairs,
+// whichever model gives the least time per step.  Tiles and sweeps cross near
+// a million nodes.  The 16-bit types have no sweeps (their pair kernel is as
+// fast: FP16-SR 4096^2 202 against 181 GLUPS) and go from tiles to pairs
+// (FP16-SR, us per step in tiles and pairs: 512^2 3.1 / 3.9, 768^2 6.2 / 6.4,
+// 1024^2 8.4 / 8.4).
 void plan_fused(clbm_handle *h)
 {
     const LatDesc &d = h->d;
@@ -321,12 +327,8 @@ void plan_fused(clbm_handle *h)
     const int64_t nodes = (int64_t)d.nx * d.ny;
     const int eb = elem_bytes(d.storage), cus = compute_units();
     double us = 0.0;
-    const clbm::TilePlan t = clbm::tile_plan(d.nx, d.ny, eb, cus, &us);
-    if (eb == 2) {
-        if (nodes <= kTileMaxNodes16) h->tile = t;
-        return;
-    }
-    if (d.nx >= 64 && d.ny >= 64) {
+    const clbm::TilePlan t = clbm::tile_plan(d.nx, d.ny, d.storage, cus, &us);
+    if (eb != 2 && d.nx >= 64 && d.ny >= 64) {
         const clbm::SweepPlan p =
             clbm::sweep_plan(d.nx, d.ny, eb, 4 * cus, clbm::sweep_max_vec(d.storage, d.force_mode, d.bc_y));
         if (clbm::sweep_us(nodes, eb, 4 * cus, p.vec, p.rows, p.units) / clbm::kSweepSteps < us) {
@@ -334,8 +336,9 @@ void plan_fused(clbm_handle *h)
             return;
         }
     }
-    // The tile kernel's offsets are 32-bit.
-    if (9 * d.pitch * rows_allocated(d.nx, d.ny, eb) < ((int64_t)1 << 31)) h->tile = t;
+    const int64_t pair_tiles = (int64_t)((d.nx + 63) / 64) * ((d.ny + clbm::tile_h(0, d.storage) - 1) /
+                                                              clbm::tile_h(0, d.storage));
+    if (tile_offsets_fit(d) && us < clbm::pair_us(d.storage, pair_tiles, cus) / 2) h->tile = t;
 }
 
 // Whether steps go several per launch (the tile or the sweep kernel): by
@@ -803,12 +806,17 @@ constexpr int kNumSingle = sizeof(kVariants) / sizeof(kVariants[0]);
 // (persistent blocks per compute unit walking the tiles, or 0: one block per
 // tile; the two-step kernel's LDS lets 4 blocks share a compute unit).
 constexpr int kShapePerLattice = 2;
+// The first steps lattices of the default clbm_set_step_pairs in LDS tiles,
+// four or eight steps per launch; the others (and lattices set to pairs
+// under any) in pairs.
 struct PairVariant {
     int shape;
     int blocks_per_cu;
+    bool tiles;
 };
-const PairVariant kPairVariants[] = {{clbm::kTile64x16, 0}, {clbm::kTile32x32, 0}, {clbm::kTile64x16, 4},
-                                     {clbm::kTile32x32, 4}, {kShapePerLattice, 0}};
+const PairVariant kPairVariants[] = {{clbm::kTile64x16, 0, true},  {clbm::kTile32x32, 0, false},
+                                     {clbm::kTile64x16, 4, false}, {clbm::kTile32x32, 4, false},
+                                     {kShapePerLattice, 0, false}, {clbm::kTile64x16, 0, false}};
 constexpr int kNumPair = sizeof(kPairVariants) / sizeof(kPairVariants[0]);
 constexpr int kNumVariants = kNumSingle * kNumPair;
 int single_index(int v) { return v / kNumPair; }
@@ -830,6 +838,7 @@ struct clbm_batch {
     std::vector<clbm_handle *> lats;  // caller's order
     std::vector<int> order;           // table position -> caller index (grouped by kind)
     std::vector<int> keys;            // group key of each lattice when ordered
+    std::vector<int> per;             // steps per launch of each lattice (caller's order)
     hipStream_t stream = nullptr;
     hipStream_t cap = nullptr;        // capture-only stream, created on first graph
     // Groups beyond the first run on side streams, forked from and joined
@@ -843,9 +852,11 @@ struct clbm_batch {
         int64_t ntiles;
         int64_t tbase;                // first entry of the group in the tile map
         size_t lds;                   // dynamic LDS per block enforcing the cap
-        bool pairs;                   // two fused steps per launch
-        int shape;                    // pairs: the tile shape (clbm::TileShape)
+        int cls;                      // StepClass
+        int shape;                    // pairs: clbm::TileShape; LDS tiles: clbm::RegionShape
         bool small;                   // pairs: every buffer below 4 GB
+        bool walls;                   // a lattice of the group has walls
+        int per;                      // steps per launch
     };
     std::vector<Group> groups;
     std::vector<LatDesc> tab;         // host copy of the table's geometry
@@ -854,7 +865,8 @@ struct clbm_batch {
     bool map_dirty = true;            // geometry changed since the map was built
     int variant = 0;
     int cus = 256;
-    int chunk = 32;                   // launches per captured graph
+    int region[kStorageKinds] = {};   // LDS-tile region shape per storage type, or -1
+    int chunk = 64;                   // steps per captured graph (a multiple of every group's steps per launch)
     hipGraphExec_t graph = nullptr;
 };
 
@@ -873,14 +885,50 @@ int pair_shape(int variant_shape, const clbm::LatDesc &d)
     return tiles(clbm::kTile32x32) < tiles(clbm::kTile64x16) ? clbm::kTile32x32 : clbm::kTile64x16;
 }
 
-// Launch group of a lattice: whether it steps in pairs and in which tile
-// shape, storage type and kernel (storage scheme, force mode, forcing
-// scheme).
-constexpr int kGroupKeys = 3 * kStorageKinds * clbm::kKernelKeys;
+// How a lattice of a batch steps: singly, in pairs of one of two tile shapes
+// or in LDS tiles (whose region shape the whole group shares).
+enum StepClass { kSingle = 0, kPair0 = 1, kPair1 = 2, kLdsTiles = 3, kStepClasses = 4 };
+int step_class(const clbm_batch *b, const clbm_handle *h)
+{
+    const PairVariant &pv = pair_of(b->variant);
+    if (!use_pairs(h)) return kSingle;
+    if (pv.tiles && h->pairs < 0 && b->region[h->d.storage] >= 0 && tile_offsets_fit(h->d)) return kLdsTiles;
+    return kPair0 + pair_shape(pv.shape, h->d);
+}
+
+// Region shape of the lattices of each storage type that may step in LDS
+// tiles: the one with the least modelled time per step for all their tiles,
+// or -1 where pairs take less.
+void batch_regions(clbm_batch *b)
+{
+    for (int st = 0; st < kStorageKinds; ++st) {
+        int64_t pairs = 0, tiles[clbm::kRegionShapes] = {};
+        for (const auto *h : b->lats) {
+            const LatDesc &d = h->d;
+            if (d.storage != st || h->pairs >= 0 || !use_pairs(h)) continue;
+            auto count = [&](int w, int hh) { return (int64_t)((d.nx + w - 1) / w) * ((d.ny + hh - 1) / hh); };
+            pairs += count(64, clbm::tile_h(clbm::kTile64x16, st));
+            for (int shape = 0; shape < clbm::kRegionShapes; ++shape)
+                tiles[shape] += count(clbm::region_tile_w(shape), clbm::region_tile_h(shape));
+        }
+        b->region[st] = -1;
+        double best = clbm::pair_us(st, pairs, b->cus) / 2;
+        for (int shape = 0; shape < clbm::kRegionShapes; ++shape) {
+            const double us = clbm::tile_us(shape, st, tiles[shape], b->cus) / clbm::region_steps(shape);
+            if (us < best) {
+                best = us;
+                b->region[st] = shape;
+            }
+        }
+    }
+}
+
+// Launch group of a lattice: how it steps, storage type and kernel (storage
+// scheme, force mode, forcing scheme).
+constexpr int kGroupKeys = kStepClasses * kStorageKinds * clbm::kKernelKeys;
 int group_key(const clbm_batch *b, const clbm_handle *h)
 {
-    const int cls = use_pairs(h) ? 1 + pair_shape(pair_of(b->variant).shape, h->d) : 0;
-    return (cls * kStorageKinds + h->d.storage) * clbm::kKernelKeys + clbm::kernel_key(h->d);
+    return (step_class(b, h) * kStorageKinds + h->d.storage) * clbm::kKernelKeys + clbm::kernel_key(h->d);
 }
 
 // Table order: grouped by tile shape, storage and kernel (one launch per
@@ -889,6 +937,7 @@ void batch_order(clbm_batch *b)
 {
     b->order.clear();
     b->keys.clear();
+    batch_regions(b);
     for (auto *h : b->lats) b->keys.push_back(group_key(b, h));
     for (int key = 0; key < kGroupKeys; ++key)
         for (size_t j = 0; j < b->lats.size(); ++j)
@@ -902,42 +951,50 @@ void batch_geometry(clbm_batch *b)
     b->groups.clear();
     int64_t tbase = 0;
     b->tab.assign(b->order.size(), LatDesc());
+    b->per.assign(b->order.size(), 1);
     size_t pos = 0;
     while (pos < b->order.size()) {
         const clbm_handle *h0 = b->lats[b->order[pos]];
         const LatDesc &d0 = h0->d;
         const int key = group_key(b, h0);
-        const bool pairs = use_pairs(h0);
-        const int st = d0.storage;
-        const int vec = pairs ? 4 : vec_for(st, single_of(b->variant).vec_bytes);
-        const int shape = pairs ? pair_shape(pair_of(b->variant).shape, d0) : clbm::kTile64x16;
+        const int cls = step_class(b, h0), st = d0.storage;
+        const int vec = cls == kSingle ? vec_for(st, single_of(b->variant).vec_bytes) : 4;
         const int lo = (int)pos;
+        size_t end = pos;
+        while (end < b->order.size() && group_key(b, b->lats[b->order[end]]) == key) ++end;
+        // Tile size of the fused steps in the group's shape.
+        const int shape = cls == kLdsTiles ? b->region[st] : (cls == kPair1 ? 1 : 0);
+        const int tw = cls == kLdsTiles ? clbm::region_tile_w(shape) : clbm::tile_w(shape);
+        const int th = cls == kLdsTiles ? clbm::region_tile_h(shape) : clbm::tile_h(shape, st);
+        const int per = cls == kLdsTiles ? clbm::region_steps(shape) : (cls == kSingle ? 1 : 2);
         int64_t tiles = 0;
         size_t bytes = 0, largest = 0;
-        while (pos < b->order.size() && group_key(b, b->lats[b->order[pos]]) == key) {
+        bool walls = false;
+        for (; pos < end; ++pos) {
             LatDesc d = b->lats[b->order[pos]]->d;
             clbm::tile_geometry(d.pitch, d.ny, vec, &d.tpr, &d.inv_tpr, &d.ntiles);
-            if (pairs) {  // tiles of the two-step kernel in the group's shape, and their walk
-                const int tx = (d.nx + clbm::tile_w(shape) - 1) / clbm::tile_w(shape);
-                const int ty = (d.ny + clbm::tile_h(shape, st) - 1) / clbm::tile_h(shape, st);
-                const int sw = clbm::kStripNodes / clbm::tile_w(shape);
+            if (cls != kSingle) {  // the fused kernel's tiles, and their walk
+                const int tx = (d.nx + tw - 1) / tw, ty = (d.ny + th - 1) / th;
+                const int sw = std::max(clbm::kStripNodes / tw, 1);
                 d.ntiles = (int64_t)tx * ty;
                 d.walk = clbm::strip_walk(tx, ty, tx < sw ? tx : sw);
             }
             d.vec = vec;
-            d.pairs = pairs ? 1 : 0;
+            d.per = per;
+            b->per[b->order[pos]] = per;
             d.tile0 = tiles;
             tiles += d.ntiles;
             const size_t one = clbm_buffer_bytes(d.nx, d.ny, d.storage);
             bytes += 2 * one;
             largest = std::max(largest, one);
+            walls = walls || d.bc_y;
             b->tab[pos] = d;
-            ++pos;
         }
         const int cap = single_of(b->variant).cap;
         const size_t lds = lds_for_occupancy(cap < 0 ? default_occupancy(st, bytes) : cap);
         const bool small = largest + 4096 < ((size_t)1 << 32);
-        b->groups.push_back({st, clbm::kernel_key(d0), vec, lo, (int)pos, tiles, tbase, lds, pairs, shape, small});
+        b->groups.push_back({st, clbm::kernel_key(d0), vec, lo, (int)pos, tiles, tbase, lds, cls, shape, small, walls,
+                             per});
         tbase += tiles;
     }
     b->map_dirty = true;
@@ -966,7 +1023,7 @@ int batch_upload(clbm_batch *b, const int64_t *nsteps, void *spare = nullptr)
             d.tile0 = g.tile0;
             d.ntiles = g.ntiles;
             d.walk = g.walk;
-            d.pairs = g.pairs;
+            d.per = g.per;
             d.parity = h->parity;
             d.steps = (int32_t)nsteps[b->order[pos]];
             if (spare && d.inplace) d.buf[1] = spare;
@@ -1023,14 +1080,18 @@ int batch_side_streams(clbm_batch *b, size_t n)
     return CLBM_OK;
 }
 
-// Steps k0 .. k0 + n - 1 of the current call for every group (which = 3),
-// or only the groups that step singly (1) or in pairs (2).  The groups
+// Steps 0 .. n - 1 of the current call for every group (which = 3), or only
+// the groups that step singly (1) or in fused steps (2); with `first`, only
+// the first launch of every group, as often as makes kTimedSteps fused steps
+// (the autotuner's timed launches, which must not read what they wrote).  The
+// groups
 // touch disjoint lattices, so with more than one they run concurrently:
 // group 0 on s, the others on side streams forked from s once and joined
 // back to it after their n steps (a group of small lattices alone leaves
 // HBM idle in its tail; measured +15 % on a batch of FP32 and FP16
 // lattices).  Within a group the steps follow each other in stream order.
-int batch_launch_steps(clbm_batch *b, int k0, int n, hipStream_t s, int which = 3)
+constexpr int kTimedSteps = 8;
+int batch_launch_steps(clbm_batch *b, int n, hipStream_t s, int which = 3, bool first = false)
 {
     const Variant &v = single_of(b->variant);
     const PairVariant &pv = pair_of(b->variant);
@@ -1046,19 +1107,21 @@ int batch_launch_steps(clbm_batch *b, int k0, int n, hipStream_t s, int which = 
     for (size_t k = 0; k < ng; ++k) {
         const auto &g = b->groups[k];
         hipStream_t gs = k == 0 ? s : b->side[k - 1];
-        if (!(which & (g.pairs ? 2 : 1))) continue;
-        if (g.pairs) {
-            // Steps k0 .. k0 + n - 1 as pair substeps (k0 is even).
-            const int gg = (int)std::min<int64_t>(pgrid, g.ntiles);
-            for (int p = k0 / 2; p < (k0 + n + 1) / 2; ++p)
-                HIPCHK(clbm::launch_batch2(g.storage, b->d_lats, b->d_tile_lat + g.tbase, g.ntiles, g.key,
-                                           g.small, p, g.shape, gg, gs));
-            continue;
+        if (!(which & (g.cls == kSingle ? 1 : 2))) continue;
+        const int timed = g.cls == kSingle ? 1 : kTimedSteps / g.per;
+        const int launches = first ? timed : (n + g.per - 1) / g.per;
+        const int32_t *map = b->d_tile_lat + g.tbase;
+        for (int k2 = 0; k2 < launches; ++k2) {
+            const int sub = first ? 0 : k2;
+            if (g.cls == kLdsTiles)
+                HIPCHK(clbm::launch_batch_tile(g.storage, b->d_lats, map, g.ntiles, g.key, g.walls, g.shape, sub, gs));
+            else if (g.cls == kSingle)
+                HIPCHK(clbm::launch_batch(b->d_lats, map, g.ntiles, g.storage, g.key, g.vec,
+                                          (int)std::min<int64_t>(grid, g.ntiles), sub, g.lds, gs));
+            else
+                HIPCHK(clbm::launch_batch2(g.storage, b->d_lats, map, g.ntiles, g.key, g.small, sub, g.shape,
+                                           (int)std::min<int64_t>(pgrid, g.ntiles), gs));
         }
-        const int gg = (int)std::min<int64_t>(grid, g.ntiles);
-        for (int sub = k0; sub < k0 + n; ++sub)
-            HIPCHK(clbm::launch_batch(b->d_lats, b->d_tile_lat + g.tbase, g.ntiles, g.storage, g.key,
-                                      g.vec, gg, sub, g.lds, gs));
     }
     for (size_t k = 1; k < ng; ++k) {
         HIPCHK(hipEventRecord(b->join[k - 1], b->side[k - 1]));
@@ -1072,7 +1135,7 @@ int batch_build_graph(clbm_batch *b)
     hipGraph_t g = nullptr;
     if (!b->cap) HIPCHK(hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking));
     HIPCHK(hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal));
-    const int rc = batch_launch_steps(b, 0, b->chunk, b->cap);
+    const int rc = batch_launch_steps(b, b->chunk, b->cap);
     hipError_t le = rc == CLBM_OK
                         ? clbm::launch_batch_advance(b->d_lats, (int)b->order.size(), b->chunk, b->cap)
                         : hipSuccess;
@@ -1112,13 +1175,13 @@ int batch_run(clbm_batch *b, const int64_t *nsteps)
         left -= b->chunk;
     }
     if (left > 0) {
-        if ((rc = batch_launch_steps(b, 0, (int)left, b->stream))) return rc;
+        if ((rc = batch_launch_steps(b, (int)left, b->stream))) return rc;
         HIPCHK(clbm::launch_batch_advance(b->d_lats, (int)b->order.size(), (int)left, b->stream));
     }
     for (size_t j = 0; j < b->lats.size(); ++j) {
-        // Lattices stepping in pairs flip buffers once per launch; every
-        // chunk but a lattice's last holds an even number of its steps.
-        const int64_t launches = use_pairs(b->lats[j]) ? (nsteps[j] + 1) / 2 : nsteps[j];
+        // Buffers flip once per launch; every chunk but a lattice's last
+        // holds whole launches.
+        const int64_t launches = (nsteps[j] + b->per[j] - 1) / b->per[j];
         b->lats[j]->parity = (int)((b->lats[j]->parity + launches) & 1);
         b->lats[j]->steps += nsteps[j];
     }
@@ -1169,11 +1232,8 @@ int clbm_batch_create(clbm_handle *const *lattices, int32_t count, void *stream,
     clbm_batch *b = new clbm_batch();
     b->lats = v;
     b->stream = static_cast<hipStream_t>(stream);
+    b->cus = compute_units();
     batch_order(b);
-    int dev = 0;
-    if (hipGetDevice(&dev) == hipSuccess)
-        (void)hipDeviceGetAttribute(&b->cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (b->cus < 1) b->cus = 256;
     hipError_t e = hipMallocAsync(reinterpret_cast<void **>(&b->d_lats), sizeof(LatDesc) * count,
                                   b->stream);
     if (e != hipSuccess) {
@@ -1249,13 +1309,8 @@ int clbm_batch_autotune(clbm_batch *b, const char *cache_path, int32_t *chosen)
     // its contents are never read).  The single-step part of the variant is
     // chosen first, on the groups that step singly, then the two-step part
     // on the groups that step in pairs.
-    std::vector<int64_t> counts(b->lats.size(), 1);
-    bool any_single = false, any_pairs = false;
-    for (size_t j = 0; j < b->lats.size(); ++j) {
-        const bool p = use_pairs(b->lats[j]);
-        counts[j] = p ? 2 : 1;
-        (p ? any_pairs : any_single) = true;
-    }
+    bool any_single = false, any_fused = false;
+    for (auto *h : b->lats) (use_pairs(h) ? any_fused : any_single) = true;
     size_t spare_bytes = 0;
     for (auto *h : b->lats)
         if (h->d.inplace)
@@ -1266,16 +1321,19 @@ int clbm_batch_autotune(clbm_batch *b, const char *cache_path, int32_t *chosen)
     HIPCHK(hipEventCreate(&t0));
     HIPCHK(hipEventCreate(&t1));
     int rc = CLBM_OK;
-    // Mean time of one launch sequence of variant v over the groups `which`.
+    // Mean time of the groups `which` under variant v: one step of those that
+    // step singly, kTimedSteps of those that step fused.
     auto time_variant = [&](int v, int which, float *ms) -> int {
         int r = clbm_batch_set_variant(b, v);
+        std::vector<int64_t> counts(b->lats.size());
+        for (size_t j = 0; j < counts.size(); ++j) counts[j] = b->per[j];
         if (!r) r = batch_upload(b, counts.data(), spare);
         const int reps = 5;
-        for (int w = 0; w < 2 && r == CLBM_OK; ++w) r = batch_launch_steps(b, 0, 1, b->stream, which);
+        for (int w = 0; w < 2 && r == CLBM_OK; ++w) r = batch_launch_steps(b, 1, b->stream, which, true);
         if (r) return r;
         hipError_t e = hipEventRecord(t0, b->stream);
         for (int k = 0; k < reps && r == CLBM_OK && e == hipSuccess; ++k)
-            r = batch_launch_steps(b, 0, 1, b->stream, which);
+            r = batch_launch_steps(b, 1, b->stream, which, true);
         if (r) return r;
         if (e == hipSuccess) e = hipEventRecord(t1, b->stream);
         if (e == hipSuccess) e = hipEventSynchronize(t1);
@@ -1295,7 +1353,7 @@ int clbm_batch_autotune(clbm_batch *b, const char *cache_path, int32_t *chosen)
             }
         }
     }
-    if (any_pairs && rc == CLBM_OK) {
+    if (any_fused && rc == CLBM_OK) {
         float best_ms = 1e30f;
         for (int vp = 0; vp < kNumPair && rc == CLBM_OK; ++vp) {
             float ms = 0.f;

@@ -123,10 +123,10 @@ struct LatDesc {
     int32_t vec;         // nodes per thread along x
     int32_t inplace;     // 0: two buffers (pull form); 1: one buffer, AA pattern
     int32_t rshift;      // log2 of the rows per row block
-    int32_t pairs;       // batch: steps go two per launch (64 x 16 tiles, parity counts launches)
+    int32_t per;         // batch: steps per launch (1, 2, 4 or 8; parity counts launches)
     int64_t tile0;       // batch: first tile of this lattice in its group
     int64_t ntiles;      // batch: tiles of this lattice
-    StripWalk walk;      // batch, two steps per launch: the strip walk of its tiles in the group's shape
+    StripWalk walk;      // batch, fused steps: the strip walk of its tiles in the group's shape
     double inv_tpr;      // 1 / tpr, for the tile decode
     double Fx, Fy;       // FM_CONST force density
     double sc_g, sc_psi0, sc_rho;  // FM_SC: G, psi0 and rho_ref of psi = psi0 exp(-rho_ref/rho)
@@ -243,10 +243,22 @@ inline SweepPlan sweep_plan(int nx, int ny, int eb, int simds, int max_vec)
 // Several fused steps per launch in LDS (clbm_tile.h).  A block's region is W
 // x H cells, its tile the K - 1 cells less at each side that its K-th step
 // still has.
-enum RegionShape { kRegion32x24 = 0, kRegion32x32 = 1, kRegion64x16 = 2, kRegion32x16 = 3, kRegionShapes = 4 };
-constexpr int region_w(int shape) { return shape == kRegion64x16 ? 64 : 32; }
-constexpr int region_h(int shape) { return shape == kRegion32x24 ? 24 : (shape == kRegion32x32 ? 32 : 16); }
+enum RegionShape {
+    kRegion32x24 = 0,
+    kRegion32x32 = 1,
+    kRegion64x16 = 2,
+    kRegion32x16 = 3,
+    kRegion64x32 = 4,
+    kRegionShapes = 5
+};
+constexpr int region_w(int shape) { return shape == kRegion64x16 || shape == kRegion64x32 ? 64 : 32; }
+constexpr int region_h(int shape)
+{
+    return shape == kRegion32x24 ? 24 : (shape == kRegion32x32 || shape == kRegion64x32 ? 32 : 16);
+}
 constexpr int region_steps(int shape) { return shape == kRegion32x24 || shape == kRegion32x32 ? 8 : 4; }
+constexpr int region_tile_w(int shape) { return region_w(shape) - 2 * (region_steps(shape) - 1); }
+constexpr int region_tile_h(int shape) { return region_h(shape) - 2 * (region_steps(shape) - 1); }
 struct TilePlan {
     int32_t steps;    // most steps of one launch (K); 0: this lattice takes no tiles
     int32_t shape;    // RegionShape
@@ -256,31 +268,46 @@ struct TilePlan {
 
 // Microseconds of one launch of K steps: a fixed part (launch, first loads,
 // last stores) and the tiles a compute unit takes one after another or side
-// by side.  Fitted to 64 x 32 ... 1024^2 lattices (FP32, FP64; us per launch
-// at 200^2, 512^2, 1024^2): 32 x 24 8.8, 29.7, 93 and 10.5, 51.5, 177; 32 x
-// 32 10.3, 27, 73 and 12.6, 44.7, 130; 64 x 16 6.6, 10.6, 31 and 7.8, 16, 52;
-// 32 x 16 5.2, 12.3, 32 and 5.7, 19, 54.
-inline double tile_us(int shape, int eb, int64_t tiles, int cus)
+// by side.  Fitted on MI355X to 64 x 32 ... 2048^2 lattices (us per launch at
+// 200^2, 512^2, 2048^2 in FP32; FP16-SR): 32 x 24 8.8, 29.7, 370; 10.1, 38, 481;
+// 32 x 32 10.3, 27, 292; 11.5, 33, 365; 64 x 16 6.6, 10.6, 106; 8.1, 12, 123; 32 x
+// 16 5.2, 12.3, 118; 5.5, 13.8, 126; 64 x 32 9.5, 11.1, 115; 11.5, 12.4, 126.
+inline double tile_us(int shape, int storage, int64_t tiles, int cus)
 {
-    const double per32[] = {4.05, 5.5, 3.5, 1.8}, per64[] = {7.4, 9.7, 6.2, 3.05};
+    static const double per[4][kRegionShapes] = {
+        {7.4, 9.7, 6.2, 3.05, 16.0},  // FP64
+        {4.05, 5.6, 3.5, 1.8, 9.5},   // FP32
+        {4.4, 5.9, 3.6, 1.7, 9.8},    // 16-bit, to nearest
+        {5.4, 7.2, 4.3, 2.0, 11.2},   // 16-bit, stochastic
+    };
     const int64_t n = (tiles + cus - 1) / cus;
-    return eb == 8 ? 2.2 + per64[shape] * n : 3.5 + per32[shape] * n;
+    const int t = storage == ST_F64 ? 0 : (storage == ST_F32 ? 1 : (storage == ST_F16 || storage == ST_BF16 ? 2 : 3));
+    return (t == 0 ? 2.2 : 3.5) + per[t][shape] * n;
+}
+
+// Microseconds of one launch of a fused pair on `tiles` tiles of 64 x 16
+// nodes (64 x 8 in FP64), four and more of which share a compute unit.
+inline double pair_us(int storage, int64_t tiles, int cus)
+{
+    const double per = storage == ST_F64 ? 3.2 : (storage == ST_F32 ? 3.4 : (storage == ST_F16 || storage == ST_BF16 ? 2.4 : 2.7));
+    const double us = 4.0 + per * tiles / cus;
+    return us < 5.8 ? 5.8 : us;
 }
 
 // The plan with the least time per step, which goes to *us_per_step.
-inline TilePlan tile_plan(int nx, int ny, int eb, int cus, double *us_per_step)
+inline TilePlan tile_plan(int nx, int ny, int storage, int cus, double *us_per_step)
 {
     TilePlan best{};
     for (int shape = 0; shape < kRegionShapes; ++shape) {
         TilePlan p{};
         p.shape = shape;
         p.steps = region_steps(shape);
-        const int tw = region_w(shape) - 2 * (p.steps - 1), th = region_h(shape) - 2 * (p.steps - 1);
+        const int tw = region_tile_w(shape), th = region_tile_h(shape);
         p.tiles_x = (nx + tw - 1) / tw;
         const int64_t tiles = (int64_t)p.tiles_x * ((ny + th - 1) / th);
         if (tiles > INT32_MAX) continue;
         p.tiles = (int32_t)tiles;
-        const double us = tile_us(shape, eb, tiles, cus) / p.steps;
+        const double us = tile_us(shape, storage, tiles, cus) / p.steps;
         if (best.steps == 0 || us < *us_per_step) {
             best = p;
             *us_per_step = us;
@@ -348,6 +375,14 @@ hipError_t launch_sweep_st(const LatDesc &d, int src, const SweepPlan &p, hipStr
 hipError_t launch_tile(const LatDesc &d, int src, int n, const TilePlan &p, hipStream_t s);
 template <int ST>
 hipError_t launch_tile_st(const LatDesc &d, int src, int n, const TilePlan &p, hipStream_t s);
+// Substep `sub` of a batch group whose lattices step in LDS tiles of one
+// region shape: each lattice with more than K sub steps left (K the shape's)
+// takes min(K, what is left) of them.  walls: a lattice of the group has them.
+hipError_t launch_batch_tile(int storage, const LatDesc *lats, const int32_t *tile_lat, int64_t ntiles, int key,
+                             bool walls, int shape, int sub, hipStream_t s);
+template <int ST>
+hipError_t launch_batch_tile_st(const LatDesc *lats, const int32_t *tile_lat, int64_t ntiles, int key, bool walls,
+                                int shape, int sub, hipStream_t s);
 // Pair substep `pair` of a batch group whose lattices step in pairs: each
 // lattice with at least 2 pair + 2 steps left takes two fused steps, one
 // with 2 pair + 1 left takes its last single step.  small: every buffer of

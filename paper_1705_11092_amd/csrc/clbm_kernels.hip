@@ -47,9 +47,8 @@ __global__ void k_batch_advance(LatDesc *lats, int count, int chunk)
     const int j = blockIdx.x * blockDim.x + threadIdx.x;
     if (j < count) {
         const int done = lats[j].steps < chunk ? lats[j].steps : chunk;
-        // Lattices stepping in pairs flip buffers once per launch: done / 2
-        // pairs and, for an odd count, one single step.
-        const int launches = lats[j].pairs ? (done + 1) / 2 : done;
+        // Buffers flip once per launch of up to `per` steps.
+        const int launches = (done + lats[j].per - 1) / lats[j].per;
         lats[j].parity = (lats[j].parity + launches) & 1;
         lats[j].steps -= done;
     }
@@ -339,6 +338,22 @@ hipError_t launch_tile(const LatDesc &d, int src, int n, const TilePlan &p, hipS
     case ST_BF16_SR: return launch_tile_st<ST_BF16_SR>(d, src, n, p, s);
     default: return hipErrorInvalidValue;
     }
+}
+
+hipError_t launch_batch_tile(int storage, const LatDesc *lats, const int32_t *tile_lat, int64_t ntiles, int key,
+                             bool walls, int shape, int sub, hipStream_t s)
+{
+#define CLBM_BT(ST) launch_batch_tile_st<ST>(lats, tile_lat, ntiles, key, walls, shape, sub, s)
+    switch (storage) {
+    case ST_F64: return CLBM_BT(ST_F64);
+    case ST_F32: return CLBM_BT(ST_F32);
+    case ST_F16: return CLBM_BT(ST_F16);
+    case ST_BF16: return CLBM_BT(ST_BF16);
+    case ST_F16_SR: return CLBM_BT(ST_F16_SR);
+    case ST_BF16_SR: return CLBM_BT(ST_BF16_SR);
+    default: return hipErrorInvalidValue;
+    }
+#undef CLBM_BT
 }
 
 hipError_t launch_batch2(int storage, const LatDesc *lats, const int32_t *tile_lat, int64_t ntiles, int key,

@@ -236,5 +236,31 @@ __device__ __forceinline__ bool decode(const LatDesc &d, int64_t t, int tid, int
     return decode_group(d, t * kBlock + tid, y, x0);
 }
 
+// n / d for 0 <= n < 2^31 with d's multiply-and-shift constants (FastDiv);
+// with n and the constants uniform, on the scalar unit.
+__host__ __device__ __forceinline__ int div_by(int n, FastDiv f)
+{
+    return (int)(((uint64_t)(uint32_t)n * f.m) >> f.sh);
+}
+
+// Tile t (tx, ty) of a lattice of tiles_x x tiles_y tiles, walked in
+// vertical strips of sw tile columns (the last strip, of w columns,
+// narrower): within a strip row by row, so the tile above was taken sw
+// tiles earlier and its lines are still in the L2 when this tile reads its
+// halo.  The divisions by sw tiles_y, sw and w come prepared from the host
+// (StripWalk).
+__host__ __device__ __forceinline__ void strip_tile(int t, const StripWalk &p, int &tx, int &ty)
+{
+    if (t < p.in_full) {
+        const int st = div_by(t, p.by_strip), i = t - st * (p.sw * p.tiles_y);
+        ty = div_by(i, p.by_sw);
+        tx = st * p.sw + (i - ty * p.sw);
+    } else {
+        const int i = t - p.in_full;
+        ty = div_by(i, p.by_w);
+        tx = p.full * p.sw + (i - ty * p.w);
+    }
+}
+
 }  // namespace
 }  // namespace clbm

@@ -34,9 +34,9 @@ __device__ __forceinline__ int wrap_any(int v, int n)
     return v;
 }
 
-template <int RW_, int RH_, int K_, int NT_>
+template <int RW_, int RH_, int K_, int NT_, int NB_ = 2>
 struct Region {
-    static constexpr int RW = RW_, RH = RH_, K = K_, NT = NT_;
+    static constexpr int RW = RW_, RH = RH_, K = K_, NT = NT_, NB = NB_;
     static constexpr int TW = RW - 2 * (K - 1), TH = RH - 2 * (K - 1);  // the tile
     static constexpr int RPP = NT / RW;                                 // rows per pass of the block
     static constexpr int M = RH / RPP;                                  // cells per thread
@@ -44,9 +44,10 @@ struct Region {
 };
 
 // n <= K steps of the tile at (x0, y0) from buffer src into src ^ 1.
+// WALL: the lattice may have walls (d.bc_y says).
 template <int ST, int FM, int SCH, typename RG, bool WALL>
 __device__ __forceinline__ void tile_steps(const LatDesc &d, int src, int x0, int y0, int n,
-                                           typename Storage<ST>::T (&lds)[2][8][RG::RH][RG::RW])
+                                           typename Storage<ST>::T (&lds)[RG::NB][8][RG::RH][RG::RW])
 {
     using S = Storage<ST>;
     using T = typename S::T;
@@ -109,20 +110,20 @@ __device__ __forceinline__ void tile_steps(const LatDesc &d, int src, int x0, in
         const int r = rt0 + m * RG::RPP;
         int y = y0 - H + r;
         dead[m] = false;
-        if (WALL) {
+        if (WALL && d.bc_y) {
             dead[m] = y < 0 || y >= d.ny;
             y = y < 0 ? 0 : (y >= d.ny ? d.ny - 1 : y);
         } else {
             y = wrap_any(y, d.ny);
         }
-        lo[m] = WALL && y == 0;
-        hi[m] = WALL && y == d.ny - 1;
+        lo[m] = WALL && d.bc_y && y == 0;
+        hi[m] = WALL && d.bc_y && y == d.ny - 1;
         node[m] = (uint32_t)y * (uint32_t)d.nx + (uint32_t)x;
         if (!needed(r, 1) || dead[m]) continue;
         force_at<R, FM>(d, x, y, Fx[m], Fy[m]);
         const uint32_t r0 = row_off(y);
-        const uint32_t rm = row_off(y == 0 ? (WALL ? 0 : d.ny - 1) : y - 1);
-        const uint32_t rp = row_off(y == d.ny - 1 ? (WALL ? y : 0) : y + 1);
+        const uint32_t rm = row_off(y == 0 ? d.ny - 1 : y - 1);
+        const uint32_t rp = row_off(y == d.ny - 1 ? 0 : y + 1);
 #pragma unroll
         for (int i = 0; i < 9; ++i) {
             uint32_t o = (uint32_t)i * ds + (ey_of(i) == 0 ? r0 : (ey_of(i) == 1 ? rm : rp)) +
@@ -138,57 +139,102 @@ __device__ __forceinline__ void tile_steps(const LatDesc &d, int src, int x0, in
         collide<R, SCH>(ga[m], Fx[m], Fy[m], rt);
         finish(m, r, ga[m], 1, lds[0]);
     }
+    auto pull = [&](int m, int r, const T(*from)[RH][RW], R (&g)[9]) {
+        g[0] = S::to_r(keep[m]);
+        const T *p = &from[0][r][c];
+#pragma unroll
+        for (int i = 1; i < 9; ++i) {
+            int o = (i - 1) * RH * RW - ey_of(i) * RW - ex_of(i);
+            if (WALL && ((ey_of(i) == 1 && lo[m]) || (ey_of(i) == -1 && hi[m]))) o = (opp_of(i) - 1) * RH * RW;
+            g[i] = S::to_r(p[o]);
+        }
+    };
     for (int l = 2; l <= n; ++l) {
         __syncthreads();
-        auto from = lds[l & 1], to = lds[(l & 1) ^ 1];
+        if constexpr (RG::NB == 2) {
+            auto from = lds[l & 1], to = lds[(l & 1) ^ 1];
 #pragma unroll
-        for (int m = 0; m < M; ++m) {
-            const int r = rt0 + m * RG::RPP;
-            if (!needed(r, l) || dead[m]) continue;
-            R g[9];
-            g[0] = S::to_r(keep[m]);
-            const T *p = &from[0][r][c];
-#pragma unroll
-            for (int i = 1; i < 9; ++i) {
-                int o = (i - 1) * RH * RW - ey_of(i) * RW - ex_of(i);
-                if (WALL && ((ey_of(i) == 1 && lo[m]) || (ey_of(i) == -1 && hi[m]))) o = (opp_of(i) - 1) * RH * RW;
-                g[i] = S::to_r(p[o]);
+            for (int m = 0; m < M; ++m) {
+                const int r = rt0 + m * RG::RPP;
+                if (!needed(r, l) || dead[m]) continue;
+                R g[9];
+                pull(m, r, from, g);
+                collide<R, SCH>(g, Fx[m], Fy[m], rt);
+                finish(m, r, g, l, to);
             }
-            collide<R, SCH>(g, Fx[m], Fy[m], rt);
-            finish(m, r, g, l, to);
+        } else {
+#pragma unroll
+            for (int m = 0; m < M; ++m) {
+                const int r = rt0 + m * RG::RPP;
+                if (needed(r, l) && !dead[m]) pull(m, r, lds[0], ga[m]);
+            }
+            if (l < n) __syncthreads();
+#pragma unroll
+            for (int m = 0; m < M; ++m) {
+                const int r = rt0 + m * RG::RPP;
+                if (!needed(r, l) || dead[m]) continue;
+                collide<R, SCH>(ga[m], Fx[m], Fy[m], rt);
+                finish(m, r, ga[m], l, lds[0]);
+            }
         }
     }
 }
 
+template <int ST, typename RG>
+using TileLds = typename Storage<ST>::T[RG::NB][8][RG::RH][RG::RW];
+
 template <int ST, int FM, int SCH, typename RG, bool WALL>
 __global__ __launch_bounds__(RG::NT) void k_tile(LatDesc d, int src, int n, int tiles_x)
 {
-    __shared__ typename Storage<ST>::T lds[2][8][RG::RH][RG::RW];
+    __shared__ TileLds<ST, RG> lds;
     const int t = (int)xcd_order(blockIdx.x, gridDim.x);
     const int ty = t / tiles_x, tx = t - ty * tiles_x;
     tile_steps<ST, FM, SCH, RG, WALL>(d, src, tx * RG::TW, ty * RG::TH, n, lds);
 }
 
+// Substep `sub` of a batch group: one block per tile (tiles numbered lattice
+// by lattice, tile_lat naming each tile's lattice).  The buffer parity of a
+// lattice counts launches.
+template <int ST, int FM, int SCH, typename RG, bool WALL>
+__global__ __launch_bounds__(RG::NT) void k_batch_tile(const LatDesc *__restrict__ lats,
+                                                       const int32_t *__restrict__ tile_lat, int64_t ntiles, int sub)
+{
+    __shared__ TileLds<ST, RG> lds;
+    const int64_t t = xcd_order(blockIdx.x, ntiles);
+    const LatDesc &d = lats[tile_lat[t]];
+    const int left = d.steps - RG::K * sub;
+    if (left <= 0) return;  // the whole block: one lattice per tile
+    int tx, ty;
+    strip_tile((int)(t - d.tile0), d.walk, tx, ty);
+    tile_steps<ST, FM, SCH, RG, WALL>(d, (d.parity + sub) & 1, tx * RG::TW, ty * RG::TH, left < RG::K ? left : RG::K,
+                                      lds);
+}
+
+// The regions by shape.  FP64 takes as many cells per thread as FP32 with
+// twice the threads in the wide low one (118 against 86 VGPRs with two).  The
+// largest region has room for one copy of its slots.
+template <int ST, int SHAPE>
+using RegionOf = std::conditional_t<
+    SHAPE == kRegion32x24, Region<32, 24, 8, 768>,
+    std::conditional_t<
+        SHAPE == kRegion32x32, Region<32, 32, 8, 1024>,
+        std::conditional_t<SHAPE == kRegion64x16, Region<64, 16, 4, ST == ST_F64 ? 1024 : 512>,
+                           std::conditional_t<SHAPE == kRegion32x16, Region<32, 16, 4, 512>, Region<64, 32, 4, 1024, 1>>>>>;
+
 }  // namespace
 
-// n <= tile_steps_max(p.shape) fused steps of one lattice from buffer src
-// into buffer src ^ 1.
-template <int ST>
-hipError_t launch_tile_st(const LatDesc &d, int src, int n, const TilePlan &p, hipStream_t s)
+// n <= p.steps fused steps of one lattice from buffer src into buffer
+// src ^ 1.
+template <int ST, int SHAPE>
+hipError_t tile_shape_launch(const LatDesc &d, int src, int n, const TilePlan &p, hipStream_t s)
 {
+    using RG = RegionOf<ST, SHAPE>;
+    static_assert(RG::RW == region_w(SHAPE) && RG::RH == region_h(SHAPE) && RG::K == region_steps(SHAPE), "shape");
     const dim3 grid((unsigned)p.tiles);
     switch ((d.force_mode * 2 + d.scheme) * 2 + (d.bc_y ? 1 : 0)) {
-#define CLBM_TL(FM, SCH, WALL)                                                                             \
-    case (FM * 2 + SCH) * 2 + WALL:                                                                        \
-        if (p.shape == kRegion32x24)                                                                       \
-            k_tile<ST, FM, SCH, Region<32, 24, 8, 768>, WALL><<<grid, 768, 0, s>>>(d, src, n, p.tiles_x);  \
-        else if (p.shape == kRegion32x32)                                                                  \
-            k_tile<ST, FM, SCH, Region<32, 32, 8, 1024>, WALL><<<grid, 1024, 0, s>>>(d, src, n, p.tiles_x); \
-        else if (p.shape == kRegion32x16)                                                                  \
-            k_tile<ST, FM, SCH, Region<32, 16, 4, 512>, WALL><<<grid, 512, 0, s>>>(d, src, n, p.tiles_x);  \
-        else                                                                                               \
-            k_tile<ST, FM, SCH, Region<64, 16, 4, ST == ST_F64 ? 1024 : 512>, WALL>                        \
-                <<<grid, ST == ST_F64 ? 1024 : 512, 0, s>>>(d, src, n, p.tiles_x);                         \
+#define CLBM_TL(FM, SCH, WALL)                                                            \
+    case (FM * 2 + SCH) * 2 + WALL:                                                       \
+        k_tile<ST, FM, SCH, RG, WALL><<<grid, RG::NT, 0, s>>>(d, src, n, p.tiles_x);      \
         break;
 #define CLBM_TL2(FM, SCH) CLBM_TL(FM, SCH, 0) CLBM_TL(FM, SCH, 1)
         CLBM_TL2(FM_CONST, SCH_CONSISTENT)
@@ -203,6 +249,59 @@ hipError_t launch_tile_st(const LatDesc &d, int src, int n, const TilePlan &p, h
         return hipErrorInvalidValue;
     }
     return hipGetLastError();
+}
+
+template <int ST>
+hipError_t launch_tile_st(const LatDesc &d, int src, int n, const TilePlan &p, hipStream_t s)
+{
+    switch (p.shape) {
+    case kRegion32x24: return tile_shape_launch<ST, kRegion32x24>(d, src, n, p, s);
+    case kRegion32x32: return tile_shape_launch<ST, kRegion32x32>(d, src, n, p, s);
+    case kRegion64x16: return tile_shape_launch<ST, kRegion64x16>(d, src, n, p, s);
+    case kRegion32x16: return tile_shape_launch<ST, kRegion32x16>(d, src, n, p, s);
+    case kRegion64x32: return tile_shape_launch<ST, kRegion64x32>(d, src, n, p, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+template <int ST, int SHAPE>
+hipError_t batch_tile_shape_launch(const LatDesc *lats, const int32_t *tile_lat, int64_t ntiles, int key, bool walls,
+                                   int sub, hipStream_t s)
+{
+    using RG = RegionOf<ST, SHAPE>;
+    const dim3 grid((unsigned)ntiles);
+    switch (key * 2 + (walls ? 1 : 0)) {
+#define CLBM_TL(FM, SCH, WALL)                                                                             \
+    case (FM * 2 + SCH) * 2 + WALL:                                                                        \
+        k_batch_tile<ST, FM, SCH, RG, WALL><<<grid, RG::NT, 0, s>>>(lats, tile_lat, ntiles, sub);          \
+        break;
+#define CLBM_TL2(FM, SCH) CLBM_TL(FM, SCH, 0) CLBM_TL(FM, SCH, 1)
+        CLBM_TL2(FM_CONST, SCH_CONSISTENT)
+        CLBM_TL2(FM_CONST, SCH_GUO_LBL)
+        CLBM_TL2(FM_ROW, SCH_CONSISTENT)
+        CLBM_TL2(FM_ROW, SCH_GUO_LBL)
+        CLBM_TL2(FM_FIELD, SCH_CONSISTENT)
+        CLBM_TL2(FM_FIELD, SCH_GUO_LBL)
+#undef CLBM_TL2
+#undef CLBM_TL
+    default:
+        return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+template <int ST>
+hipError_t launch_batch_tile_st(const LatDesc *lats, const int32_t *tile_lat, int64_t ntiles, int key, bool walls,
+                                int shape, int sub, hipStream_t s)
+{
+    switch (shape) {
+    case kRegion32x24: return batch_tile_shape_launch<ST, kRegion32x24>(lats, tile_lat, ntiles, key, walls, sub, s);
+    case kRegion32x32: return batch_tile_shape_launch<ST, kRegion32x32>(lats, tile_lat, ntiles, key, walls, sub, s);
+    case kRegion64x16: return batch_tile_shape_launch<ST, kRegion64x16>(lats, tile_lat, ntiles, key, walls, sub, s);
+    case kRegion32x16: return batch_tile_shape_launch<ST, kRegion32x16>(lats, tile_lat, ntiles, key, walls, sub, s);
+    case kRegion64x32: return batch_tile_shape_launch<ST, kRegion64x32>(lats, tile_lat, ntiles, key, walls, sub, s);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace clbm

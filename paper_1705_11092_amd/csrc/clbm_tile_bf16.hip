@@ -1,6 +1,8 @@
-// clbm_tile_bf16.hip -- the multi-step LDS tile kernel for BF16 storage.
+// clbm_tile_bf16.hip -- the multi-step LDS tile kernels for BF16 storage.
 #include "clbm_tile.h"
 
 namespace clbm {
 template hipError_t launch_tile_st<ST_BF16>(const LatDesc &, int, int, const TilePlan &, hipStream_t);
+template hipError_t launch_batch_tile_st<ST_BF16>(const LatDesc *, const int32_t *, int64_t, int, bool, int, int,
+                                              hipStream_t);
 }  // namespace clbm
