@@ -323,9 +323,11 @@ void plan_fused(clbm_handle *h)
     const LatDesc &d = h->d;
     h->sweep = clbm::SweepPlan{};
     h->tile = clbm::TilePlan{};
-    if (!clbm::step2_supported(d)) return;
     const int64_t nodes = (int64_t)d.nx * d.ny;
     const int eb = elem_bytes(d.storage), cus = compute_units();
+    if (d.force_mode == clbm::FM_SC && !d.inplace && tile_offsets_fit(d))
+        h->tile = clbm::sc_tile_plan(d.nx, d.ny, d.storage, cus);
+    if (!clbm::step2_supported(d)) return;
     double us = 0.0;
     const clbm::TilePlan t = clbm::tile_plan(d.nx, d.ny, d.storage, cus, &us);
     if (eb != 2 && d.nx >= 64 && d.ny >= 64) {

@@ -249,7 +249,10 @@ enum RegionShape {
     kRegion64x16 = 2,
     kRegion32x16 = 3,
     kRegion64x32 = 4,
-    kRegionShapes = 5
+    kRegionShapes = 5,
+    // With the Shan-Chen force, whose steps need two nodes less at each side.
+    kRegionSc32x24 = 5,
+    kRegionSc64x32 = 6
 };
 constexpr int region_w(int shape) { return shape == kRegion64x16 || shape == kRegion64x32 ? 64 : 32; }
 constexpr int region_h(int shape)
@@ -314,6 +317,26 @@ inline TilePlan tile_plan(int nx, int ny, int storage, int cus, double *us_per_s
         }
     }
     return best;
+}
+
+// The plan of a Shan-Chen lattice: regions of 32 x 24 cells and four steps
+// (tiles of 18 x 10) or of 64 x 32 and two (58 x 26), whichever takes less
+// time per step.
+inline TilePlan sc_tile_plan(int nx, int ny, int storage, int cus)
+{
+    TilePlan p[2];
+    double us[2];
+    for (int k = 0; k < 2; ++k) {
+        const int steps = k == 0 ? 4 : 2, h = 2 * steps - 1;
+        const int tw = (k == 0 ? 32 : 64) - 2 * h, th = (k == 0 ? 24 : 32) - 2 * h;
+        p[k].steps = steps;
+        p[k].shape = k == 0 ? kRegionSc32x24 : kRegionSc64x32;
+        p[k].tiles_x = (nx + tw - 1) / tw;
+        p[k].tiles = p[k].tiles_x * ((ny + th - 1) / th);
+        const int n = (p[k].tiles + cus - 1) / cus;
+        us[k] = (3.5 + (k == 0 ? 4.0 : 8.0) * (storage == ST_F64 ? 1.5 : 1.0) * n) / steps;
+    }
+    return us[1] < us[0] ? p[1] : p[0];
 }
 
 // Lattice descriptors carried in one upload kernel's arguments.

@@ -116,7 +116,7 @@ __global__ __launch_bounds__(kBlock) void k_psi(LatDesc d, int src, const double
             for (int i = 0; i < 9; ++i) dr += get_pre<ST>(d, src, i, x, y);
             rho = d.rho0 + dr;
         }
-        psi[p] = R(d.sc_psi0 * exp(-d.sc_rho / rho) - d.sc_psic);
+        psi[p] = R(shan_chen_psi(d, rho));
     }
 }
 
@@ -328,7 +328,8 @@ hipError_t launch_sweep(const LatDesc &d, int src, const SweepPlan &p, hipStream
 
 hipError_t launch_tile(const LatDesc &d, int src, int n, const TilePlan &p, hipStream_t s)
 {
-    if (!step2_supported(d) || n < 1 || n > p.steps) return hipErrorInvalidValue;
+    if (d.inplace || n < 1 || n > p.steps) return hipErrorInvalidValue;
+    if ((d.force_mode == FM_SC) != (p.shape >= kRegionSc32x24)) return hipErrorInvalidValue;
     switch (d.storage) {
     case ST_F64: return launch_tile_st<ST_F64>(d, src, n, p, s);
     case ST_F32: return launch_tile_st<ST_F32>(d, src, n, p, s);

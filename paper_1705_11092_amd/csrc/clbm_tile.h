@@ -180,6 +180,130 @@ __device__ __forceinline__ void tile_steps(const LatDesc &d, int src, int x0, in
     }
 }
 
+// The same with the Shan-Chen force (periodic lattices).  A step's force
+// needs psi of the neighbours' densities of that step, which are pulled from
+// their neighbours in turn: a step is needed on two nodes less at each side
+// than the one before.  A step pulls its cells and writes their psi to LDS,
+// and after a barrier takes the force from there, collides and writes the
+// slots, one copy of which is enough.
+template <int RW_, int RH_, int K_, int NT_>
+struct ScRegion {
+    static constexpr int RW = RW_, RH = RH_, K = K_, NT = NT_, H = 2 * K - 1;
+    static constexpr int TW = RW - 2 * H, TH = RH - 2 * H;
+    static constexpr int RPP = NT / RW, M = RH / RPP;
+    static_assert(NT % RW == 0 && RH % RPP == 0, "whole rows per pass, whole passes");
+};
+template <int ST, typename RG>
+struct ScLds {
+    typename Storage<ST>::T v[8][RG::RH][RG::RW];
+    typename Storage<ST>::R psi[RG::RH][RG::RW];
+};
+
+template <int ST, int SCH, typename RG>
+__device__ __forceinline__ void sc_tile_steps(const LatDesc &d, int src, int x0, int y0, int n, ScLds<ST, RG> &lds)
+{
+    using S = Storage<ST>;
+    using T = typename S::T;
+    using R = typename S::R;
+    constexpr int RW = RG::RW, RH = RG::RH, M = RG::M, H = RG::H;
+    const T *in = static_cast<const T *>(d.buf[src]);
+    T *out = static_cast<T *>(d.buf[src ^ 1]);
+    const Rates<R> rt = rates_of<R>(d);
+    const int c = threadIdx.x % RW, rt0 = threadIdx.x / RW;
+    const int we = d.nx - x0 < RG::TW ? d.nx - x0 : RG::TW;
+    const int he = d.ny - y0 < RG::TH ? d.ny - y0 : RG::TH;
+    const int x = wrap_any(x0 - H + c, d.nx);
+    const uint32_t cm = (uint32_t)(x == 0 ? d.nx - 1 : x - 1), c0 = (uint32_t)x,
+                   cp = (uint32_t)(x == d.nx - 1 ? 0 : x + 1);
+    auto row_off = [&](int y) {
+        return (uint32_t)(y >> d.rshift) * (uint32_t)d.bstride + (uint32_t)(y & ((1 << d.rshift) - 1)) * (uint32_t)d.pitch;
+    };
+    const uint32_t ds = (uint32_t)d.dstride;
+    // Cells within e nodes of the tile.
+    auto near = [&](int r, int e) { return r >= H - e && r < H + he + e && c >= H - e && c < H + we + e; };
+
+    T keep[M];
+    uint32_t node[M];
+    R g[M][9];
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        const int r = rt0 + m * RG::RPP;
+        const int y = wrap_any(y0 - H + r, d.ny);
+        node[m] = (uint32_t)y * (uint32_t)d.nx + (uint32_t)x;
+        if (!near(r, 2 * n - 1)) continue;
+        const uint32_t r0 = row_off(y), rm = row_off(y == 0 ? d.ny - 1 : y - 1),
+                       rp = row_off(y == d.ny - 1 ? 0 : y + 1);
+#pragma unroll
+        for (int i = 0; i < 9; ++i)
+            g[m][i] = S::to_r(in[(uint32_t)i * ds + (ey_of(i) == 0 ? r0 : (ey_of(i) == 1 ? rm : rp)) +
+                                 (ex_of(i) == 0 ? c0 : (ex_of(i) == 1 ? cm : cp))]);
+    }
+    for (int l = 1; l <= n; ++l) {
+        const int e = 2 * (n - l);  // this step's collisions reach e nodes beyond the tile
+        if (l > 1) {
+            __syncthreads();
+#pragma unroll
+            for (int m = 0; m < M; ++m) {
+                const int r = rt0 + m * RG::RPP;
+                if (!near(r, e + 1)) continue;
+                g[m][0] = S::to_r(keep[m]);
+                const T *p = &lds.v[0][r][c];
+#pragma unroll
+                for (int i = 1; i < 9; ++i) g[m][i] = S::to_r(p[(i - 1) * RH * RW - ey_of(i) * RW - ex_of(i)]);
+            }
+        }
+        // psi of the density, as the psi pass forms it.
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            const int r = rt0 + m * RG::RPP;
+            if (!near(r, e + 1)) continue;
+            double dr = 0.0;
+#pragma unroll
+            for (int i = 0; i < 9; ++i) dr += (double)g[m][i];
+            lds.psi[r][c] = R(shan_chen_psi(d, d.rho0 + dr));
+        }
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            const int r = rt0 + m * RG::RPP;
+            if (!near(r, e)) continue;
+            R Fx, Fy;
+            const R *q = &lds.psi[r][c];
+            shan_chen_force<R>(d, q, q - 1, q + 1, q - RW, q - RW - 1, q - RW + 1, q + RW, q + RW - 1, q + RW + 1, Fx,
+                               Fy);
+            collide<R, SCH>(g[m], Fx, Fy, rt);
+            T rv[9];
+            if constexpr (S::kDither) {
+                const uint32_t h = hash32(__float_as_uint(g[m][0]) ^ (node[m] * 0x9e3779b9u));
+#pragma unroll
+                for (int i = 0; i < 9; ++i) rv[i] = S::from_r_sr(g[m][i], sr_operand(h, i));
+            } else {
+#pragma unroll
+                for (int i = 0; i < 8; i += 2) round_pair<ST>(g[m][i], g[m][i + 1], &rv[i]);
+                rv[8] = S::from_r(g[m][8]);
+            }
+            if (l < n) {
+                keep[m] = rv[0];
+#pragma unroll
+                for (int i = 1; i < 9; ++i) lds.v[i - 1][r][c] = rv[i];
+            } else {
+                const uint32_t o = row_off(y0 + r - H) + (uint32_t)(x0 + c - H);
+#pragma unroll
+                for (int i = 0; i < 9; ++i) out[o + (uint32_t)i * ds] = rv[i];
+            }
+        }
+    }
+}
+
+template <int ST, int SCH, typename RG>
+__global__ __launch_bounds__(RG::NT) void k_sc_tile(LatDesc d, int src, int n, int tiles_x)
+{
+    __shared__ ScLds<ST, RG> lds;
+    const int t = (int)xcd_order(blockIdx.x, gridDim.x);
+    const int ty = t / tiles_x, tx = t - ty * tiles_x;
+    sc_tile_steps<ST, SCH, RG>(d, src, tx * RG::TW, ty * RG::TH, n, lds);
+}
+
 template <int ST, typename RG>
 using TileLds = typename Storage<ST>::T[RG::NB][8][RG::RH][RG::RW];
 
@@ -251,10 +375,23 @@ hipError_t tile_shape_launch(const LatDesc &d, int src, int n, const TilePlan &p
     return hipGetLastError();
 }
 
+template <int ST, typename RG>
+hipError_t sc_tile_launch(const LatDesc &d, int src, int n, const TilePlan &p, hipStream_t s)
+{
+    const dim3 grid((unsigned)p.tiles);
+    if (d.scheme == SCH_CONSISTENT)
+        k_sc_tile<ST, SCH_CONSISTENT, RG><<<grid, RG::NT, 0, s>>>(d, src, n, p.tiles_x);
+    else
+        k_sc_tile<ST, SCH_GUO_LBL, RG><<<grid, RG::NT, 0, s>>>(d, src, n, p.tiles_x);
+    return hipGetLastError();
+}
+
 template <int ST>
 hipError_t launch_tile_st(const LatDesc &d, int src, int n, const TilePlan &p, hipStream_t s)
 {
     switch (p.shape) {
+    case kRegionSc32x24: return sc_tile_launch<ST, ScRegion<32, 24, 4, 768>>(d, src, n, p, s);
+    case kRegionSc64x32: return sc_tile_launch<ST, ScRegion<64, 32, 2, 1024>>(d, src, n, p, s);
     case kRegion32x24: return tile_shape_launch<ST, kRegion32x24>(d, src, n, p, s);
     case kRegion32x32: return tile_shape_launch<ST, kRegion32x32>(d, src, n, p, s);
     case kRegion64x16: return tile_shape_launch<ST, kRegion64x16>(d, src, n, p, s);
