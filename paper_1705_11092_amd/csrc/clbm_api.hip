@@ -305,10 +305,10 @@ bool use_pairs(const clbm_handle *h)
     return h->pairs < 0 ? pairs_by_default(h->d) : h->pairs != 0;
 }
 
-// The tile kernel's offsets within a buffer are 32-bit.
+// The tile kernel's byte offsets within a buffer are 32-bit.
 bool tile_offsets_fit(const LatDesc &d)
 {
-    return 9 * d.pitch * rows_allocated(d.nx, d.ny, elem_bytes(d.storage)) < ((int64_t)1 << 31);
+    return clbm_buffer_bytes(d.nx, d.ny, d.storage) < (size_t)1 << 32;
 }
 
 // The plan of the fused kernels for the lattice and its force (at creation

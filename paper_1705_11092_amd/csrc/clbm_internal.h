@@ -192,20 +192,20 @@ constexpr int sweep_max_vec(int storage, int force_mode, int bc_y)
     return storage == ST_F64 && (force_mode == FM_FIELD || bc_y) ? 1 : 2;
 }
 
-// Microseconds of one launch under a plan, from what bounds it: the
-// VALU issue of the busiest SIMD (a wave collides rows + K - 1 rows of each
-// of K levels on average, 0.222 us per level and column of a lane in FP32,
-// 0.238 in FP64; one wave per SIMD hides its latencies to 72 % of the issue
-// rate, two to 92 %), or HBM at 5.3 TB/s (3.6 with one wave per SIMD; each
-// chunk reads 2 K rows beyond its own), plus 3 us of launch.  Within 10 % of
-// the times measured for 24 plans of 1024^2, 2048^2 and 4096^2 lattices.
+// Microseconds of one launch under a plan, from what bounds it: the VALU issue
+// of the busiest SIMD (a wave collides rows + K - 1 rows of each of K levels on
+// average, 0.245 us per level and column of a lane in FP32, 0.262 in FP64; one
+// wave per SIMD hides its latencies to 72 % of the issue rate, two to 92 %), or
+// memory at 4.8 TB/s (3.3 with one wave per SIMD; each chunk reads 2 K rows
+// beyond its own), plus 3 us of launch.  Within 10 % of what 1024^2, 2048^2 and
+// 4096^2 lattices take (FP64 48, 158, 546 us; FP32 32, 99, 315).
 inline double sweep_us(int64_t nodes, int eb, int simds, int vec, int rows, int64_t units)
 {
     const int64_t n = (units + simds - 1) / simds;  // waves on the busiest SIMD
     const double eff = n == 1 ? 0.72 : (n == 2 ? 0.92 : 0.95);
-    const double valu = kSweepSteps * (eb == 8 ? 0.238 : 0.222) * vec * n * (rows + kSweepSteps) / eff;
+    const double valu = kSweepSteps * (eb == 8 ? 0.262 : 0.245) * vec * n * (rows + kSweepSteps) / eff;
     const double state = 9.0 * nodes * eb;
-    const double mem = state * (2.0 + 2.0 * kSweepSteps / rows) / (n == 1 ? 3.6e6 : 5.3e6);
+    const double mem = state * (2.0 + 2.0 * kSweepSteps / rows) / (n == 1 ? 3.3e6 : 4.8e6);
     return (valu > mem ? valu : mem) + 3.0;
 }
 
@@ -248,16 +248,16 @@ enum RegionShape {
     kRegion32x32 = 1,
     kRegion64x16 = 2,
     kRegion32x16 = 3,
-    kRegion64x32 = 4,
+    kRegion64x24 = 4,
     kRegionShapes = 5,
     // With the Shan-Chen force, whose steps need two nodes less at each side.
     kRegionSc32x24 = 5,
     kRegionSc64x32 = 6
 };
-constexpr int region_w(int shape) { return shape == kRegion64x16 || shape == kRegion64x32 ? 64 : 32; }
+constexpr int region_w(int shape) { return shape == kRegion64x16 || shape == kRegion64x24 ? 64 : 32; }
 constexpr int region_h(int shape)
 {
-    return shape == kRegion32x24 ? 24 : (shape == kRegion32x32 || shape == kRegion64x32 ? 32 : 16);
+    return shape == kRegion32x24 || shape == kRegion64x24 ? 24 : (shape == kRegion32x32 ? 32 : 16);
 }
 constexpr int region_steps(int shape) { return shape == kRegion32x24 || shape == kRegion32x32 ? 8 : 4; }
 constexpr int region_tile_w(int shape) { return region_w(shape) - 2 * (region_steps(shape) - 1); }
@@ -271,17 +271,18 @@ struct TilePlan {
 
 // Microseconds of one launch of K steps: a fixed part (launch, first loads,
 // last stores) and the tiles a compute unit takes one after another or side
-// by side.  Fitted on MI355X to 64 x 32 ... 2048^2 lattices (us per launch at
-// 200^2, 512^2, 2048^2 in FP32; FP16-SR): 32 x 24 8.8, 29.7, 370; 10.1, 38, 481;
-// 32 x 32 10.3, 27, 292; 11.5, 33, 365; 64 x 16 6.6, 10.6, 106; 8.1, 12, 123; 32 x
-// 16 5.2, 12.3, 118; 5.5, 13.8, 126; 64 x 32 9.5, 11.1, 115; 11.5, 12.4, 126.
+// by side.  Fitted on MI355X to 200^2 ... 2048^2 lattices (us per launch at
+// 200^2, 512^2, 2048^2 in FP32; FP64; FP16-SR): 32 x 24 8.7, 29, 345; 10.6, 49, 710;
+// 9.4, 35, 473.  32 x 32 9.9, 25, 262; 11.9, 42, 529; 11.4, 33, 353.  64 x 16 6.5, 9.7,
+// 98; 8.1, 14.9, 156; 8.2, 12.5, 120.  32 x 16 5.0, 11.4, 110; 5.9, 18, 188; 5.6, 13.5,
+// 124.  64 x 24 8.3, 12.5, 94; 11.3, 24, 199.
 inline double tile_us(int shape, int storage, int64_t tiles, int cus)
 {
     static const double per[4][kRegionShapes] = {
-        {7.4, 9.7, 6.2, 3.05, 16.0},  // FP64
-        {4.05, 5.6, 3.5, 1.8, 9.5},   // FP32
-        {4.4, 5.9, 3.6, 1.7, 9.8},    // 16-bit, to nearest
-        {5.4, 7.2, 4.3, 2.0, 11.2},   // 16-bit, stochastic
+        {7.8, 10.0, 5.3, 3.0, 11.0},  // FP64
+        {4.2, 5.3, 3.2, 1.65, 5.0},   // FP32
+        {4.4, 5.8, 3.5, 1.65, 5.4},   // 16-bit, to nearest
+        {5.3, 7.0, 4.2, 1.95, 6.5},   // 16-bit, stochastic
     };
     const int64_t n = (tiles + cus - 1) / cus;
     const int t = storage == ST_F64 ? 0 : (storage == ST_F32 ? 1 : (storage == ST_F16 || storage == ST_BF16 ? 2 : 3));

@@ -10,13 +10,14 @@
 // it to the other buffer.  A thread keeps the cells of one column (every
 // NT / RW-th row of it), so its slot 0 stays in a register, its force is read
 // once, and its LDS addresses are one register and constants.  LDS holds the
-// other 8 slots twice: a step reads one copy and writes the other, one
-// barrier per step.
+// other 8 slots once, streamed in place, one barrier per step.
 //
 // The region is the periodic plane around the tile, so a lattice smaller than
 // the region simply repeats.  Every node update is the one-step kernel's, so
 // the result is bitwise that of n one-step launches.
 #pragma once
+
+#include <type_traits>
 
 #include "clbm_step.h"
 
@@ -34,9 +35,22 @@ __device__ __forceinline__ int wrap_any(int v, int n)
     return v;
 }
 
-template <int RW_, int RH_, int K_, int NT_, int NB_ = 2>
+// Element at byte offset off of a buffer below 4 GB: the loads and stores take
+// the uniform base and the 32-bit offset as they are.
+template <typename T>
+__device__ __forceinline__ T load_at(const T *base, uint32_t off)
+{
+    return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + (uint64_t)off);
+}
+template <typename T>
+__device__ __forceinline__ void store_at(T *base, uint32_t off, T v)
+{
+    *reinterpret_cast<T *>(reinterpret_cast<char *>(base) + (uint64_t)off) = v;
+}
+
+template <int RW_, int RH_, int K_, int NT_>
 struct Region {
-    static constexpr int RW = RW_, RH = RH_, K = K_, NT = NT_, NB = NB_;
+    static constexpr int RW = RW_, RH = RH_, K = K_, NT = NT_;
     static constexpr int TW = RW - 2 * (K - 1), TH = RH - 2 * (K - 1);  // the tile
     static constexpr int RPP = NT / RW;                                 // rows per pass of the block
     static constexpr int M = RH / RPP;                                  // cells per thread
@@ -47,12 +61,15 @@ struct Region {
 // WALL: the lattice may have walls (d.bc_y says).
 template <int ST, int FM, int SCH, typename RG, bool WALL>
 __device__ __forceinline__ void tile_steps(const LatDesc &d, int src, int x0, int y0, int n,
-                                           typename Storage<ST>::T (&lds)[RG::NB][8][RG::RH][RG::RW])
+                                           typename Storage<ST>::T (&lds)[8][RG::RH][RG::RW])
 {
     using S = Storage<ST>;
     using T = typename S::T;
     using R = typename S::R;
     constexpr int RW = RG::RW, RH = RG::RH, M = RG::M, H = RG::K - 1;
+    // Cells loaded and collided together: more at once cost registers, and
+    // with them the second block on the compute unit (64 x 24, FP32: 110 VGPRs).
+    constexpr int kStage = 2;
     const T *in = static_cast<const T *>(d.buf[src]);
     T *out = static_cast<T *>(d.buf[src ^ 1]);
     const Rates<R> rt = rates_of<R>(d);
@@ -61,21 +78,27 @@ __device__ __forceinline__ void tile_steps(const LatDesc &d, int src, int x0, in
     const int he = d.ny - y0 < RG::TH ? d.ny - y0 : RG::TH;
 
     const int x = wrap_any(x0 - H + c, d.nx);
-    const uint32_t cm = (uint32_t)(x == 0 ? d.nx - 1 : x - 1), c0 = (uint32_t)x,
-                   cp = (uint32_t)(x == d.nx - 1 ? 0 : x + 1);
-    auto row_off = [&](int y) {
-        return (uint32_t)(y >> d.rshift) * (uint32_t)d.bstride + (uint32_t)(y & ((1 << d.rshift) - 1)) * (uint32_t)d.pitch;
+    constexpr uint32_t kB = sizeof(T);
+    const uint32_t cm = (uint32_t)(x == 0 ? d.nx - 1 : x - 1) * kB, c0 = (uint32_t)x * kB,
+                   cp = (uint32_t)(x == d.nx - 1 ? 0 : x + 1) * kB;
+    const uint32_t bs = (uint32_t)d.bstride * kB, pb = (uint32_t)d.pitch * kB, ds = (uint32_t)d.dstride * kB;
+    auto row_off = [&](int y) {  // bytes
+        return (uint32_t)(y >> d.rshift) * bs + (uint32_t)(y & ((1 << d.rshift) - 1)) * pb;
     };
-    const uint32_t ds = (uint32_t)d.dstride;
 
     T keep[M];
     R Fx[M], Fy[M];
     uint32_t node[M];
     bool lo[M], hi[M], dead[M];
 
-    // One cell after its collision: rounded, then to LDS or, after the last
-    // step, to the other buffer.
-    auto finish = [&](int m, int r, const R (&g)[9], int l, T(*to)[RH][RW]) {
+    // One cell after its collision, rounded: after the last step to the other
+    // buffer, before that to LDS.  The region streams in place (the AA
+    // pattern): odd steps read a cell's own slots and write its value of slot
+    // i into its slot opp(i); even steps read slot opp(i) of cell x - e_i and
+    // write slot i of cell x + e_i.  A location is read and written by one cell
+    // in a step, so a step needs no second copy, and cells follow one another
+    // in any order.
+    auto finish = [&](int m, int r, const R (&g)[9], int l, bool odd) {
         T rv[9];
         if constexpr (S::kDither) {
             const uint32_t h = hash32(__float_as_uint(g[0]) ^ (node[m] * 0x9e3779b9u));
@@ -88,12 +111,19 @@ __device__ __forceinline__ void tile_steps(const LatDesc &d, int src, int x0, in
         }
         if (l < n) {
             keep[m] = rv[0];
+            T *p = &lds[0][r][c];
 #pragma unroll
-            for (int i = 1; i < 9; ++i) to[i - 1][r][c] = rv[i];
+            for (int i = 1; i < 9; ++i) {
+                const int own = (opp_of(i) - 1) * RH * RW;
+                int o = odd ? own : (i - 1) * RH * RW + ey_of(i) * RW + ex_of(i);
+                // Beyond a wall: reflected into the cell's own reversed slot.
+                if (WALL && !odd && ((ey_of(i) == -1 && lo[m]) || (ey_of(i) == 1 && hi[m]))) o = own;
+                p[o] = rv[i];
+            }
         } else {
-            const uint32_t o = row_off(y0 + r - H) + (uint32_t)(x0 + c - H);
+            const uint32_t o = row_off(y0 + r - H) + (uint32_t)(x0 + c - H) * kB;
 #pragma unroll
-            for (int i = 0; i < 9; ++i) out[o + (uint32_t)i * ds] = rv[i];
+            for (int i = 0; i < 9; ++i) store_at(out, o + (uint32_t)i * ds, rv[i]);
         }
     };
     // Whether step l is needed at region row r and this thread's column: the
@@ -104,79 +134,70 @@ __device__ __forceinline__ void tile_steps(const LatDesc &d, int src, int x0, in
     };
 
     // Step 1, from the state.
-    R ga[M][9];
 #pragma unroll
-    for (int m = 0; m < M; ++m) {
-        const int r = rt0 + m * RG::RPP;
-        int y = y0 - H + r;
-        dead[m] = false;
-        if (WALL && d.bc_y) {
-            dead[m] = y < 0 || y >= d.ny;
-            y = y < 0 ? 0 : (y >= d.ny ? d.ny - 1 : y);
-        } else {
-            y = wrap_any(y, d.ny);
+    for (int m0 = 0; m0 < M; m0 += kStage) {
+        R ga[kStage][9];
+#pragma unroll
+        for (int m = m0; m < m0 + kStage && m < M; ++m) {
+            const int r = rt0 + m * RG::RPP;
+            int y = y0 - H + r;
+            dead[m] = false;
+            if (WALL && d.bc_y) {
+                dead[m] = y < 0 || y >= d.ny;
+                y = y < 0 ? 0 : (y >= d.ny ? d.ny - 1 : y);
+            } else {
+                y = wrap_any(y, d.ny);
+            }
+            lo[m] = WALL && d.bc_y && y == 0;
+            hi[m] = WALL && d.bc_y && y == d.ny - 1;
+            node[m] = (uint32_t)y * (uint32_t)d.nx + (uint32_t)x;
+            if (!needed(r, 1) || dead[m]) continue;
+            force_at<R, FM>(d, x, y, Fx[m], Fy[m]);
+            const uint32_t r0 = row_off(y);
+            const uint32_t rm = row_off(y == 0 ? d.ny - 1 : y - 1);
+            const uint32_t rp = row_off(y == d.ny - 1 ? 0 : y + 1);
+#pragma unroll
+            for (int i = 0; i < 9; ++i) {
+                uint32_t o = (uint32_t)i * ds + (ey_of(i) == 0 ? r0 : (ey_of(i) == 1 ? rm : rp)) +
+                             (ex_of(i) == 0 ? c0 : (ex_of(i) == 1 ? cm : cp));
+                if (WALL && ((ey_of(i) == 1 && lo[m]) || (ey_of(i) == -1 && hi[m]))) o = (uint32_t)opp_of(i) * ds + r0 + c0;
+                ga[m - m0][i] = S::to_r(load_at(in, o));
+            }
         }
-        lo[m] = WALL && d.bc_y && y == 0;
-        hi[m] = WALL && d.bc_y && y == d.ny - 1;
-        node[m] = (uint32_t)y * (uint32_t)d.nx + (uint32_t)x;
-        if (!needed(r, 1) || dead[m]) continue;
-        force_at<R, FM>(d, x, y, Fx[m], Fy[m]);
-        const uint32_t r0 = row_off(y);
-        const uint32_t rm = row_off(y == 0 ? d.ny - 1 : y - 1);
-        const uint32_t rp = row_off(y == d.ny - 1 ? 0 : y + 1);
 #pragma unroll
-        for (int i = 0; i < 9; ++i) {
-            uint32_t o = (uint32_t)i * ds + (ey_of(i) == 0 ? r0 : (ey_of(i) == 1 ? rm : rp)) +
-                         (ex_of(i) == 0 ? c0 : (ex_of(i) == 1 ? cm : cp));
-            if (WALL && ((ey_of(i) == 1 && lo[m]) || (ey_of(i) == -1 && hi[m]))) o = (uint32_t)opp_of(i) * ds + r0 + c0;
-            ga[m][i] = S::to_r(in[o]);
+        for (int m = m0; m < m0 + kStage && m < M; ++m) {
+            const int r = rt0 + m * RG::RPP;
+            if (!needed(r, 1) || dead[m]) continue;
+            collide<R, SCH>(ga[m - m0], Fx[m], Fy[m], rt);
+            finish(m, r, ga[m - m0], 1, true);
         }
+        if (m0 + kStage < M) __builtin_amdgcn_sched_barrier(0);
     }
+    auto step = [&](int l, auto odd_) {
+        constexpr bool odd = decltype(odd_)::value;
+        __syncthreads();
 #pragma unroll
-    for (int m = 0; m < M; ++m) {
-        const int r = rt0 + m * RG::RPP;
-        if (!needed(r, 1) || dead[m]) continue;
-        collide<R, SCH>(ga[m], Fx[m], Fy[m], rt);
-        finish(m, r, ga[m], 1, lds[0]);
-    }
-    auto pull = [&](int m, int r, const T(*from)[RH][RW], R (&g)[9]) {
-        g[0] = S::to_r(keep[m]);
-        const T *p = &from[0][r][c];
+        for (int m = 0; m < M; ++m) {
+            const int r = rt0 + m * RG::RPP;
+            if (!needed(r, l) || dead[m]) continue;
+            R g[9];
+            g[0] = S::to_r(keep[m]);
+            const T *p = &lds[0][r][c];
 #pragma unroll
-        for (int i = 1; i < 9; ++i) {
-            int o = (i - 1) * RH * RW - ey_of(i) * RW - ex_of(i);
-            if (WALL && ((ey_of(i) == 1 && lo[m]) || (ey_of(i) == -1 && hi[m]))) o = (opp_of(i) - 1) * RH * RW;
-            g[i] = S::to_r(p[o]);
+            for (int i = 1; i < 9; ++i) {
+                const int own = (i - 1) * RH * RW;
+                int o = odd ? own : (opp_of(i) - 1) * RH * RW - ey_of(i) * RW - ex_of(i);
+                if (WALL && !odd && ((ey_of(i) == 1 && lo[m]) || (ey_of(i) == -1 && hi[m]))) o = own;
+                g[i] = S::to_r(p[o]);
+            }
+            collide<R, SCH>(g, Fx[m], Fy[m], rt);
+            finish(m, r, g, l, odd);
+            if (m % kStage == kStage - 1 && m + 1 < M) __builtin_amdgcn_sched_barrier(0);
         }
     };
-    for (int l = 2; l <= n; ++l) {
-        __syncthreads();
-        if constexpr (RG::NB == 2) {
-            auto from = lds[l & 1], to = lds[(l & 1) ^ 1];
-#pragma unroll
-            for (int m = 0; m < M; ++m) {
-                const int r = rt0 + m * RG::RPP;
-                if (!needed(r, l) || dead[m]) continue;
-                R g[9];
-                pull(m, r, from, g);
-                collide<R, SCH>(g, Fx[m], Fy[m], rt);
-                finish(m, r, g, l, to);
-            }
-        } else {
-#pragma unroll
-            for (int m = 0; m < M; ++m) {
-                const int r = rt0 + m * RG::RPP;
-                if (needed(r, l) && !dead[m]) pull(m, r, lds[0], ga[m]);
-            }
-            if (l < n) __syncthreads();
-#pragma unroll
-            for (int m = 0; m < M; ++m) {
-                const int r = rt0 + m * RG::RPP;
-                if (!needed(r, l) || dead[m]) continue;
-                collide<R, SCH>(ga[m], Fx[m], Fy[m], rt);
-                finish(m, r, ga[m], l, lds[0]);
-            }
-        }
+    for (int l = 2; l <= n; l += 2) {
+        step(l, std::false_type{});
+        if (l + 1 <= n) step(l + 1, std::true_type{});
     }
 }
 
@@ -213,12 +234,13 @@ __device__ __forceinline__ void sc_tile_steps(const LatDesc &d, int src, int x0,
     const int we = d.nx - x0 < RG::TW ? d.nx - x0 : RG::TW;
     const int he = d.ny - y0 < RG::TH ? d.ny - y0 : RG::TH;
     const int x = wrap_any(x0 - H + c, d.nx);
-    const uint32_t cm = (uint32_t)(x == 0 ? d.nx - 1 : x - 1), c0 = (uint32_t)x,
-                   cp = (uint32_t)(x == d.nx - 1 ? 0 : x + 1);
-    auto row_off = [&](int y) {
-        return (uint32_t)(y >> d.rshift) * (uint32_t)d.bstride + (uint32_t)(y & ((1 << d.rshift) - 1)) * (uint32_t)d.pitch;
+    constexpr uint32_t kB = sizeof(T);
+    const uint32_t cm = (uint32_t)(x == 0 ? d.nx - 1 : x - 1) * kB, c0 = (uint32_t)x * kB,
+                   cp = (uint32_t)(x == d.nx - 1 ? 0 : x + 1) * kB;
+    const uint32_t bs = (uint32_t)d.bstride * kB, pb = (uint32_t)d.pitch * kB, ds = (uint32_t)d.dstride * kB;
+    auto row_off = [&](int y) {  // bytes
+        return (uint32_t)(y >> d.rshift) * bs + (uint32_t)(y & ((1 << d.rshift) - 1)) * pb;
     };
-    const uint32_t ds = (uint32_t)d.dstride;
     // Cells within e nodes of the tile.
     auto near = [&](int r, int e) { return r >= H - e && r < H + he + e && c >= H - e && c < H + we + e; };
 
@@ -235,8 +257,8 @@ __device__ __forceinline__ void sc_tile_steps(const LatDesc &d, int src, int x0,
                        rp = row_off(y == d.ny - 1 ? 0 : y + 1);
 #pragma unroll
         for (int i = 0; i < 9; ++i)
-            g[m][i] = S::to_r(in[(uint32_t)i * ds + (ey_of(i) == 0 ? r0 : (ey_of(i) == 1 ? rm : rp)) +
-                                 (ex_of(i) == 0 ? c0 : (ex_of(i) == 1 ? cm : cp))]);
+            g[m][i] = S::to_r(load_at(in, (uint32_t)i * ds + (ey_of(i) == 0 ? r0 : (ey_of(i) == 1 ? rm : rp)) +
+                                              (ex_of(i) == 0 ? c0 : (ex_of(i) == 1 ? cm : cp))));
     }
     for (int l = 1; l <= n; ++l) {
         const int e = 2 * (n - l);  // this step's collisions reach e nodes beyond the tile
@@ -287,9 +309,9 @@ __device__ __forceinline__ void sc_tile_steps(const LatDesc &d, int src, int x0,
 #pragma unroll
                 for (int i = 1; i < 9; ++i) lds.v[i - 1][r][c] = rv[i];
             } else {
-                const uint32_t o = row_off(y0 + r - H) + (uint32_t)(x0 + c - H);
+                const uint32_t o = row_off(y0 + r - H) + (uint32_t)(x0 + c - H) * kB;
 #pragma unroll
-                for (int i = 0; i < 9; ++i) out[o + (uint32_t)i * ds] = rv[i];
+                for (int i = 0; i < 9; ++i) store_at(out, o + (uint32_t)i * ds, rv[i]);
             }
         }
     }
@@ -305,7 +327,7 @@ __global__ __launch_bounds__(RG::NT) void k_sc_tile(LatDesc d, int src, int n, i
 }
 
 template <int ST, typename RG>
-using TileLds = typename Storage<ST>::T[RG::NB][8][RG::RH][RG::RW];
+using TileLds = typename Storage<ST>::T[8][RG::RH][RG::RW];
 
 template <int ST, int FM, int SCH, typename RG, bool WALL>
 __global__ __launch_bounds__(RG::NT) void k_tile(LatDesc d, int src, int n, int tiles_x)
@@ -334,16 +356,14 @@ __global__ __launch_bounds__(RG::NT) void k_batch_tile(const LatDesc *__restrict
                                       lds);
 }
 
-// The regions by shape.  FP64 takes as many cells per thread as FP32 with
-// twice the threads in the wide low one (118 against 86 VGPRs with two).  The
-// largest region has room for one copy of its slots.
+// The regions by shape.
 template <int ST, int SHAPE>
 using RegionOf = std::conditional_t<
     SHAPE == kRegion32x24, Region<32, 24, 8, 768>,
     std::conditional_t<
         SHAPE == kRegion32x32, Region<32, 32, 8, 1024>,
-        std::conditional_t<SHAPE == kRegion64x16, Region<64, 16, 4, ST == ST_F64 ? 1024 : 512>,
-                           std::conditional_t<SHAPE == kRegion32x16, Region<32, 16, 4, 512>, Region<64, 32, 4, 1024, 1>>>>>;
+        std::conditional_t<SHAPE == kRegion64x16, Region<64, 16, 4, 512>,
+                           std::conditional_t<SHAPE == kRegion32x16, Region<32, 16, 4, 512>, Region<64, 24, 4, 512>>>>>;
 
 }  // namespace
 
@@ -396,7 +416,7 @@ hipError_t launch_tile_st(const LatDesc &d, int src, int n, const TilePlan &p, h
     case kRegion32x32: return tile_shape_launch<ST, kRegion32x32>(d, src, n, p, s);
     case kRegion64x16: return tile_shape_launch<ST, kRegion64x16>(d, src, n, p, s);
     case kRegion32x16: return tile_shape_launch<ST, kRegion32x16>(d, src, n, p, s);
-    case kRegion64x32: return tile_shape_launch<ST, kRegion64x32>(d, src, n, p, s);
+    case kRegion64x24: return tile_shape_launch<ST, kRegion64x24>(d, src, n, p, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -436,7 +456,7 @@ hipError_t launch_batch_tile_st(const LatDesc *lats, const int32_t *tile_lat, in
     case kRegion32x32: return batch_tile_shape_launch<ST, kRegion32x32>(lats, tile_lat, ntiles, key, walls, sub, s);
     case kRegion64x16: return batch_tile_shape_launch<ST, kRegion64x16>(lats, tile_lat, ntiles, key, walls, sub, s);
     case kRegion32x16: return batch_tile_shape_launch<ST, kRegion32x16>(lats, tile_lat, ntiles, key, walls, sub, s);
-    case kRegion64x32: return batch_tile_shape_launch<ST, kRegion64x32>(lats, tile_lat, ntiles, key, walls, sub, s);
+    case kRegion64x24: return batch_tile_shape_launch<ST, kRegion64x24>(lats, tile_lat, ntiles, key, walls, sub, s);
     default: return hipErrorInvalidValue;
     }
 }
