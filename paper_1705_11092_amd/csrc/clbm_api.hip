@@ -241,7 +241,9 @@ int noalloc_scratch(double **out)
 }
 
 // Pinned host words for the FP64 totals, one set per host thread for the
-// life of the process (the calls that use them wait for their stream).
+// life of the process (the calls that use them wait for their stream).  The
+// reduction writes them itself (they are mapped): a copy behind it cost 2 us
+// of device time and its launch.
 double *pinned_words()
 {
     static thread_local double *p = nullptr;
@@ -263,7 +265,6 @@ struct clbm_handle {
     bool ready = false;
     void *force_buf = nullptr;   // stream-ordered allocation
     double *partials = nullptr;  // per-block FP64 partial sums (stream-ordered)
-    double *d_out = nullptr;     // reduced totals on the device
     int vec = 4;
     int occ = 0;                 // blocks per compute unit of the step kernel (0: no cap)
     int64_t resident_max = 0;    // resident kernel up to this many groups
@@ -271,6 +272,7 @@ struct clbm_handle {
     size_t lds0 = 0;             // the same for in-place phase-0 steps
     int pairs = -1;              // two fused steps per launch: 1 where supported,
                                  // 0 never, -1 the default (pairs_by_default)
+    int cus = 256;               // compute units of the device
     clbm::SweepPlan sweep{};     // four fused steps per launch by default (vec 0: never)
     clbm::TilePlan tile{};       // up to tile.steps fused steps per launch by default (0: never)
     int graph_steps = 64;
@@ -324,12 +326,12 @@ void plan_fused(clbm_handle *h)
     h->sweep = clbm::SweepPlan{};
     h->tile = clbm::TilePlan{};
     const int64_t nodes = (int64_t)d.nx * d.ny;
-    const int eb = elem_bytes(d.storage), cus = compute_units();
+    const int eb = elem_bytes(d.storage), cus = h->cus;
     if (d.force_mode == clbm::FM_SC && !d.inplace && tile_offsets_fit(d))
         h->tile = clbm::sc_tile_plan(d.nx, d.ny, d.storage, cus);
     if (!clbm::step2_supported(d)) return;
     double us = 0.0;
-    const clbm::TilePlan t = clbm::tile_plan(d.nx, d.ny, d.storage, cus, &us);
+    const clbm::TilePlan t = clbm::tile_plan(d.nx, d.ny, d.storage, (int64_t)clbm_buffer_bytes(d.nx, d.ny, d.storage), cus, &us);
     if (eb != 2 && d.nx >= 64 && d.ny >= 64) {
         const clbm::SweepPlan p =
             clbm::sweep_plan(d.nx, d.ny, eb, 4 * cus, clbm::sweep_max_vec(d.storage, d.force_mode, d.bc_y));
@@ -463,6 +465,7 @@ int clbm_create(const clbm_config *cfg, clbm_handle **out)
     h->vec = default_vec(cfg->storage);
     h->occ = default_occupancy(cfg->storage, 2 * need, inplace, 1);
     h->lds = lds_for_occupancy(h->occ);
+    h->cus = compute_units();
     plan_fused(h);
     // The tile kernel steps small lattices faster than the resident one
     // (16 x 16 FP32 1.0 against 1.7 us per step); it needs two buffers.
@@ -472,8 +475,7 @@ int clbm_create(const clbm_config *cfg, clbm_handle **out)
     reap_retired();
     const int nb = clbm::moments_blocks((int64_t)cfg->nx * cfg->ny);
     hipError_t e = hipMallocAsync(reinterpret_cast<void **>(&h->partials),
-                                  sizeof(double) * (3 * (size_t)nb + 3), h->stream);
-    if (e == hipSuccess) h->d_out = h->partials + 3 * (size_t)nb;
+                                  sizeof(double) * 3 * (size_t)nb, h->stream);
     if (e != hipSuccess) {
         clbm_destroy(h);
         return hip_fail(e, "clbm_create allocations");
@@ -644,8 +646,7 @@ int clbm_moments(clbm_handle *h, double *rho, double *ux, double *uy, double *to
     if (!totals) return CLBM_OK;
     double *w = pinned_words();
     if (!w) return fail(CLBM_EHIP, "pinned host memory for the totals");
-    HIPCHK(clbm::launch_reduce(h->partials, nb, 3, h->d_out, h->stream));
-    HIPCHK(hipMemcpyAsync(w, h->d_out, 3 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
+    HIPCHK(clbm::launch_reduce(h->partials, nb, 3, w, h->stream));
     HIPCHK(hipStreamSynchronize(h->stream));
     totals[0] = (double)h->d.nx * h->d.ny * h->d.rho0 + w[0];
     totals[1] = w[1];
@@ -696,8 +697,7 @@ int clbm_error_norms(clbm_handle *h, const double *ux_ref, const double *uy_ref,
                                 h->partials, &nb, h->stream));
     double *w = pinned_words();
     if (!w) return fail(CLBM_EHIP, "pinned host memory for the norms");
-    HIPCHK(clbm::launch_reduce(h->partials, nb, 2, h->d_out, h->stream));
-    HIPCHK(hipMemcpyAsync(w, h->d_out, 2 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
+    HIPCHK(clbm::launch_reduce(h->partials, nb, 2, w, h->stream));
     HIPCHK(hipStreamSynchronize(h->stream));
     out[0] = w[0];
     out[1] = w[1];
@@ -904,19 +904,20 @@ int step_class(const clbm_batch *b, const clbm_handle *h)
 void batch_regions(clbm_batch *b)
 {
     for (int st = 0; st < kStorageKinds; ++st) {
-        int64_t pairs = 0, tiles[clbm::kRegionShapes] = {};
+        int64_t pairs = 0, bytes = 0, tiles[clbm::kRegionShapes] = {};
         for (const auto *h : b->lats) {
             const LatDesc &d = h->d;
             if (d.storage != st || h->pairs >= 0 || !use_pairs(h)) continue;
             auto count = [&](int w, int hh) { return (int64_t)((d.nx + w - 1) / w) * ((d.ny + hh - 1) / hh); };
             pairs += count(64, clbm::tile_h(clbm::kTile64x16, st));
+            bytes += (int64_t)clbm_buffer_bytes(d.nx, d.ny, st);
             for (int shape = 0; shape < clbm::kRegionShapes; ++shape)
                 tiles[shape] += count(clbm::region_tile_w(shape), clbm::region_tile_h(shape));
         }
         b->region[st] = -1;
         double best = clbm::pair_us(st, pairs, b->cus) / 2;
         for (int shape = 0; shape < clbm::kRegionShapes; ++shape) {
-            const double us = clbm::tile_us(shape, st, tiles[shape], b->cus) / clbm::region_steps(shape);
+            const double us = clbm::tile_us(shape, st, tiles[shape], bytes, b->cus) / clbm::region_steps(shape);
             if (us < best) {
                 best = us;
                 b->region[st] = shape;

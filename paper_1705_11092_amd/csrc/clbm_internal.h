@@ -271,12 +271,12 @@ struct TilePlan {
 
 // Microseconds of one launch of K steps: a fixed part (launch, first loads,
 // last stores) and the tiles a compute unit takes one after another or side
-// by side.  Fitted on MI355X to 200^2 ... 2048^2 lattices (us per launch at
+// by side (bytes: one buffer of all the lattices).  Fitted on MI355X to 200^2 ... 2048^2 lattices (us per launch at
 // 200^2, 512^2, 2048^2 in FP32; FP64; FP16-SR): 32 x 24 8.7, 29, 345; 10.6, 49, 710;
 // 9.4, 35, 473.  32 x 32 9.9, 25, 262; 11.9, 42, 529; 11.4, 33, 353.  64 x 16 6.5, 9.7,
 // 98; 8.1, 14.9, 156; 8.2, 12.5, 120.  32 x 16 5.0, 11.4, 110; 5.9, 18, 188; 5.6, 13.5,
 // 124.  64 x 24 8.3, 12.5, 94; 11.3, 24, 199.
-inline double tile_us(int shape, int storage, int64_t tiles, int cus)
+inline double tile_us(int shape, int storage, int64_t tiles, int64_t bytes, int cus)
 {
     static const double per[4][kRegionShapes] = {
         {7.8, 10.0, 5.3, 3.0, 11.0},  // FP64
@@ -286,7 +286,10 @@ inline double tile_us(int shape, int storage, int64_t tiles, int cus)
     };
     const int64_t n = (tiles + cus - 1) / cus;
     const int t = storage == ST_F64 ? 0 : (storage == ST_F32 ? 1 : (storage == ST_F16 || storage == ST_BF16 ? 2 : 3));
-    return (t == 0 ? 2.2 : 3.5) + per[t][shape] * n;
+    // 64 x 24 on 3000^2 and 4096^2: 5.7 and 5.1 per tile where the two buffers
+    // no longer fit the 256 MB Infinity Cache.
+    const double per_tile = per[t][shape] * (2 * bytes > (int64_t)256 << 20 ? 1.08 : 1.0);
+    return (t == 0 ? 2.2 : 3.5) + per_tile * n;
 }
 
 // Microseconds of one launch of a fused pair on `tiles` tiles of 64 x 16
@@ -299,7 +302,7 @@ inline double pair_us(int storage, int64_t tiles, int cus)
 }
 
 // The plan with the least time per step, which goes to *us_per_step.
-inline TilePlan tile_plan(int nx, int ny, int storage, int cus, double *us_per_step)
+inline TilePlan tile_plan(int nx, int ny, int storage, int64_t bytes, int cus, double *us_per_step)
 {
     TilePlan best{};
     for (int shape = 0; shape < kRegionShapes; ++shape) {
@@ -311,7 +314,7 @@ inline TilePlan tile_plan(int nx, int ny, int storage, int cus, double *us_per_s
         const int64_t tiles = (int64_t)p.tiles_x * ((ny + th - 1) / th);
         if (tiles > INT32_MAX) continue;
         p.tiles = (int32_t)tiles;
-        const double us = tile_us(shape, storage, tiles, cus) / p.steps;
+        const double us = tile_us(shape, storage, tiles, bytes, cus) / p.steps;
         if (best.steps == 0 || us < *us_per_step) {
             best = p;
             *us_per_step = us;

@@ -199,14 +199,32 @@ __device__ __forceinline__ int wrap_x(int x, int nx)
     return x < 0 ? x + nx : (x >= nx ? x - nx : x);
 }
 
-// Where the pre-collision population i of node (x, y) sits when the state
-// is in buffer (two buffers) or phase (in place) `src`.
-template <typename T>
-__device__ __forceinline__ T *pre_slot(const LatDesc &d, int src, int i, int x, int y)
+// Where the pre-collision populations of node (x, y) sit when the state is in
+// buffer (two buffers) or phase (in place) src: element offsets from that
+// buffer's start, from three row and three column offsets formed once.
+__device__ __forceinline__ void pre_slots(const LatDesc &d, int src, int x, int y, int64_t (&o)[9])
 {
-    const Loc s = d.inplace ? aa_source(d, i, y, src) : source_of(d, i, y);
-    T *base = static_cast<T *>(d.buf[d.inplace ? 0 : src]);
-    return base + (int64_t)s.dir * d.dstride + row_base(d, s.row) + wrap_x(x - s.dx, d.nx);
+    const int64_t r0 = row_base(d, y);
+    if (d.inplace && src == 0) {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) o[i] = (int64_t)i * d.dstride + r0 + x;
+        return;
+    }
+    const bool lo = y == 0, hi = y == d.ny - 1;
+    const int64_t rm = row_base(d, lo ? d.ny - 1 : y - 1), rp = row_base(d, hi ? 0 : y + 1);
+    const int xm = x == 0 ? d.nx - 1 : x - 1, xp = x == d.nx - 1 ? 0 : x + 1;
+    const bool in_m = !d.bc_y || !lo, in_p = !d.bc_y || !hi;
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+        // Slot i, or reversed in place (phase 1); beyond a wall the node's
+        // own, the other way round.
+        const int64_t si = (int64_t)(d.inplace ? opp_of(i) : i) * d.dstride;
+        const int64_t so = (int64_t)(d.inplace ? i : opp_of(i)) * d.dstride;
+        const bool in = ey_of(i) == 0 || (ey_of(i) == 1 ? in_m : in_p);
+        const int64_t row = ey_of(i) == 0 ? r0 : (ey_of(i) == 1 ? rm : rp);
+        const int col = ex_of(i) == 0 ? x : (ex_of(i) == 1 ? xm : xp);
+        o[i] = in ? si + row + col : so + r0 + x;
+    }
 }
 
 // Decode group g64 of a lattice: row y = g / tpr, first node

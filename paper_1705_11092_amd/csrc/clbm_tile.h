@@ -54,6 +54,9 @@ struct Region {
     static constexpr int TW = RW - 2 * (K - 1), TH = RH - 2 * (K - 1);  // the tile
     static constexpr int RPP = NT / RW;                                 // rows per pass of the block
     static constexpr int M = RH / RPP;                                  // cells per thread
+    // Waves per SIMD to leave room for: two blocks of 512 threads on a
+    // compute unit (FP64 between walls would take 134 VGPRs, one block).
+    static constexpr int WV = NT == 512 ? 4 : 1;
     static_assert(NT % RW == 0 && RH % RPP == 0, "whole rows per pass, whole passes");
 };
 
@@ -330,7 +333,8 @@ template <int ST, typename RG>
 using TileLds = typename Storage<ST>::T[8][RG::RH][RG::RW];
 
 template <int ST, int FM, int SCH, typename RG, bool WALL>
-__global__ __launch_bounds__(RG::NT) void k_tile(LatDesc d, int src, int n, int tiles_x)
+__global__ __launch_bounds__(RG::NT) __attribute__((amdgpu_waves_per_eu(RG::WV))) void
+k_tile(LatDesc d, int src, int n, int tiles_x)
 {
     __shared__ TileLds<ST, RG> lds;
     const int t = (int)xcd_order(blockIdx.x, gridDim.x);
@@ -342,8 +346,8 @@ __global__ __launch_bounds__(RG::NT) void k_tile(LatDesc d, int src, int n, int 
 // by lattice, tile_lat naming each tile's lattice).  The buffer parity of a
 // lattice counts launches.
 template <int ST, int FM, int SCH, typename RG, bool WALL>
-__global__ __launch_bounds__(RG::NT) void k_batch_tile(const LatDesc *__restrict__ lats,
-                                                       const int32_t *__restrict__ tile_lat, int64_t ntiles, int sub)
+__global__ __launch_bounds__(RG::NT) __attribute__((amdgpu_waves_per_eu(RG::WV))) void
+k_batch_tile(const LatDesc *__restrict__ lats, const int32_t *__restrict__ tile_lat, int64_t ntiles, int sub)
 {
     __shared__ TileLds<ST, RG> lds;
     const int64_t t = xcd_order(blockIdx.x, ntiles);
