@@ -22,6 +22,8 @@
 // result is bitwise that of K one-step launches.
 #pragma once
 
+#include <type_traits>
+
 #include "clbm_step.h"
 
 namespace clbm {
@@ -218,7 +220,12 @@ __device__ __forceinline__ void sweep_strip(const LatDesc &d, int src, int q, in
     const int first = ya - (K - 1), iters = (yb - ya) + 2 * K - 2;
     load_force(0, first);
     if (!WALL || first >= 0) load_row(WALL ? first : wrap(first));
-    for (int t = 0; t < iters; ++t) {
+    // Iteration t of the march.  STEADY: every level has its rows, none of
+    // them next to a wall, and there is a next row to load; without the
+    // conditions the levels schedule into one another and their values stay in
+    // place.
+    auto iterate = [&](int t, auto steady_) {
+        constexpr bool STEADY = decltype(steady_)::value, EDGE = WALL && !STEADY;
         const int y1 = first + t;  // level 1's row
         R p[9][V];                 // the last collided level's row
         auto update = [&](int y, R (&g)[9][V], const R (&f)[2][V], bool last) {
@@ -260,7 +267,7 @@ __device__ __forceinline__ void sweep_strip(const LatDesc &d, int src, int q, in
 
 #pragma unroll
         for (int l = 1; l < K; ++l) load_force(l, y1 - l);
-        const bool on1 = !WALL || (y1 >= 0 && y1 < d.ny);
+        const bool on1 = !EDGE || (y1 >= 0 && y1 < d.ny);
         if (on1) {
             const int y = WALL ? y1 : wrap(y1);
             R g[9][V];
@@ -275,7 +282,7 @@ __device__ __forceinline__ void sweep_strip(const LatDesc &d, int src, int q, in
                     shift_x<SEAM, -1, V, R>(v, g[i], seam);
                 else
                     shift_x<SEAM, 0, V, R>(v, g[i], seam);
-                if (WALL && ((ey_of(i) == 1 && y == 0) || (ey_of(i) == -1 && y == d.ny - 1))) {
+                if (EDGE && ((ey_of(i) == 1 && y == 0) || (ey_of(i) == -1 && y == d.ny - 1))) {
 #pragma unroll
                     for (int k = 0; k < V; ++k) g[i][k] = v[k];
                 }
@@ -283,7 +290,7 @@ __device__ __forceinline__ void sweep_strip(const LatDesc &d, int src, int q, in
             update(y, g, F[0], K == 1);
         }
         // The next row's loads, in flight while the other levels collide.
-        if (t + 1 < iters) {
+        if (STEADY || t + 1 < iters) {
             const int yn = y1 + 1;
             load_force(0, yn);
             if (!WALL || (yn >= 0 && yn < d.ny)) load_row(WALL ? yn : wrap(yn));
@@ -293,8 +300,8 @@ __device__ __forceinline__ void sweep_strip(const LatDesc &d, int src, int q, in
         for (int l = 1; l < K; ++l) {
             // Level l + 1 at row yl from level l, whose row yl + 1 is in p.
             const int yl = y1 - l;
-            const bool have = t >= 2 * (l - 1) && (!WALL || (yl + 1 >= 0 && yl + 1 < d.ny));
-            const bool go = t >= 2 * l && (!WALL || (yl >= 0 && yl < d.ny));
+            const bool have = STEADY || (t >= 2 * (l - 1) && (!WALL || (yl + 1 >= 0 && yl + 1 < d.ny)));
+            const bool go = STEADY || (t >= 2 * l && (!WALL || (yl >= 0 && yl < d.ny)));
             Held<R, V> &c = h[l];
             R g[9][V];
 #pragma unroll
@@ -305,7 +312,7 @@ __device__ __forceinline__ void sweep_strip(const LatDesc &d, int src, int q, in
                 g[0][k] = c.mid[0][k];
                 g[1][k] = c.mid[1][k];
                 g[3][k] = c.mid[2][k];
-                if (WALL) {
+                if (EDGE) {
                     // The row beyond the upper wall: the node's own reversed
                     // slots, kept unshifted in up1.
                     g[4][k] = c.up1[0][k];
@@ -330,7 +337,7 @@ __device__ __forceinline__ void sweep_strip(const LatDesc &d, int src, int q, in
                 for (int k = 0; k < V; ++k) c.up1[0][k] = p[2][k];
                 shift_x<SEAM, 1, V, R>(p[5], c.up1[1], seam);
                 shift_x<SEAM, -1, V, R>(p[6], c.up1[2], seam);
-                if (WALL && yl + 1 == 0) {
+                if (EDGE && yl + 1 == 0) {
 #pragma unroll
                     for (int k = 0; k < V; ++k) {
                         c.up0[0][k] = p[4][k];
@@ -338,7 +345,7 @@ __device__ __forceinline__ void sweep_strip(const LatDesc &d, int src, int q, in
                         c.up0[2][k] = p[8][k];
                     }
                 }
-                if (WALL && yl + 1 == d.ny - 1) {
+                if (EDGE && yl + 1 == d.ny - 1) {
 #pragma unroll
                     for (int k = 0; k < V; ++k) {
                         c.up1[0][k] = p[2][k];
@@ -349,7 +356,23 @@ __device__ __forceinline__ void sweep_strip(const LatDesc &d, int src, int q, in
             }
             if (go) update(WALL ? yl : wrap(yl), g, F[l], l == K - 1);
         }
+    };
+    int t = 0;
+    if constexpr (sizeof(R) == 4) {
+        // The steady part: after every level has started, and with walls
+        // while level 1 stays below the upper one and level K above the lower
+        // one.  116 VALU instructions per update against 135 (66 of them
+        // moves) with the conditions, 201 VGPRs against 171.  In FP64 it would
+        // spill 450 registers.
+        int t1 = 2 * (K - 1), t2 = iters - 1;
+        if (WALL) {
+            t1 = t1 > K - first ? t1 : K - first;
+            t2 = t2 < d.ny - 2 - first ? t2 : d.ny - 2 - first;
+        }
+        for (; t < t1 && t < iters; ++t) iterate(t, std::false_type{});
+        for (; t < t2; ++t) iterate(t, std::true_type{});
     }
+    for (; t < iters; ++t) iterate(t, std::false_type{});
 }
 
 // Waves per SIMD the compiler must leave room for: 2 with two columns per
