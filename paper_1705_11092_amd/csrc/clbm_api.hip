@@ -275,7 +275,7 @@ struct clbm_handle {
     int cus = 256;               // compute units of the device
     clbm::SweepPlan sweep{};     // four fused steps per launch by default (vec 0: never)
     clbm::TilePlan tile{};       // up to tile.steps fused steps per launch by default (0: never)
-    int graph_steps = 64;
+    int graph_steps = -1;        // steps per graph, 0 none, -1 the default (graph_steps_of)
     int graph_launches = 0;      // launches of one graph: each flips the parity
     hipGraphExec_t graph[2] = {nullptr, nullptr};
 };
@@ -351,6 +351,19 @@ void plan_fused(clbm_handle *h)
 bool use_tiles(const clbm_handle *h) { return h->pairs < 0 && h->tile.steps != 0; }
 bool use_sweeps(const clbm_handle *h) { return h->pairs < 0 && h->sweep.vec != 0; }
 
+// Steps per graph replay.  By default graphs only serve launches shorter than
+// what the host needs to queue them, about 6 us (in place 256^2: 4.7 us per step
+// through graphs, 5.7 without): the tile and sweep kernels and large lattices
+// take longer, run as fast launch by launch, and a first run saves the
+// capture (64 x 32 FP64, 200 steps: 320 -> 248 us, 246 on a repeat).
+constexpr int kGraphSteps = 64;
+constexpr int64_t kGraphMaxNodes = 600000;
+int graph_steps_of(const clbm_handle *h)
+{
+    if (h->graph_steps >= 0) return h->graph_steps;
+    return use_tiles(h) || use_sweeps(h) || (int64_t)h->d.nx * h->d.ny > kGraphMaxNodes ? 0 : kGraphSteps;
+}
+
 // The next launch of a run with `left` steps to go, from state `parity`: as
 // many fused steps as the lattice takes.  Each launch flips the buffer or
 // phase.
@@ -379,8 +392,9 @@ int build_graph(clbm_handle *h, int parity)
     HIPCHK(hipStreamBeginCapture(h->cap, hipStreamCaptureModeThreadLocal));
     hipError_t le = hipSuccess;
     int launches = 0;
-    for (int done = 0, n = 0; done < h->graph_steps && le == hipSuccess; done += n, ++launches)
-        le = launch_next(h, (parity + launches) & 1, h->graph_steps - done, h->cap, &n);
+    const int steps = graph_steps_of(h);
+    for (int done = 0, n = 0; done < steps && le == hipSuccess; done += n, ++launches)
+        le = launch_next(h, (parity + launches) & 1, steps - done, h->cap, &n);
     hipError_t ce = hipStreamEndCapture(h->cap, &g);
     if (le != hipSuccess) {
         if (g) (void)hipGraphDestroy(g);
@@ -610,12 +624,13 @@ int clbm_step(clbm_handle *h, int64_t nsteps)
         h->steps += nsteps;
         return CLBM_OK;
     }
+    const int graph = graph_steps_of(h);
     int64_t left = nsteps;
     while (left > 0) {
-        if (h->graph_steps > 0 && left >= h->graph_steps) {
+        if (graph > 0 && left >= graph) {
             if (!h->graph[h->parity] && (rc = build_graph(h, h->parity))) return rc;
             HIPCHK(hipGraphLaunch(h->graph[h->parity], h->stream));
-            left -= h->graph_steps;
+            left -= graph;
             h->parity ^= h->graph_launches & 1;
         } else {
             int n = 0;
@@ -641,7 +656,7 @@ int clbm_moments(clbm_handle *h, double *rho, double *ux, double *uy, double *to
     if (uy && (rc = check_device_range(uy, fb, "uy"))) return rc;
     int nb = 0;
     if (h->d.force_mode == clbm::FM_SC) HIPCHK(clbm::launch_psi(h->d, h->parity, nullptr, h->stream));
-    HIPCHK(clbm::launch_moments(h->d, h->parity, rho, ux, uy, nullptr, nullptr, h->partials, &nb,
+    HIPCHK(clbm::launch_moments(h->d, h->parity, rho, ux, uy, nullptr, nullptr, totals ? h->partials : nullptr, &nb,
                                 h->stream));
     if (!totals) return CLBM_OK;
     double *w = pinned_words();
@@ -674,7 +689,7 @@ int clbm_moments_noalloc(clbm_handle *h, double *rho, double *ux, double *uy, do
     // Every partial is written before it is read: nothing to clear.
     int used = 0;
     if (h->d.force_mode == clbm::FM_SC) HIPCHK(clbm::launch_psi(h->d, h->parity, nullptr, h->stream));
-    HIPCHK(clbm::launch_moments(h->d, h->parity, rho, ux, uy, nullptr, nullptr, partials, &used,
+    HIPCHK(clbm::launch_moments(h->d, h->parity, rho, ux, uy, nullptr, nullptr, totals ? partials : nullptr, &used,
                                 h->stream));
     if (!totals) return CLBM_OK;
     HIPCHK(clbm::launch_reduce(partials, used, 3, totals, h->stream,
@@ -1171,8 +1186,12 @@ int batch_run(clbm_batch *b, const int64_t *nsteps)
     batch_refresh(b);
     int rc = batch_upload(b, nsteps);
     if (rc) return rc;
+    // One group of long launches runs as fast launch by launch: no graph to
+    // capture on the first call (12 lattices of 10^2 .. 80^2 FP64, 100 steps:
+    // 371 -> 190 us).
+    const bool direct = b->groups.size() == 1 && (b->groups[0].cls == kLdsTiles || b->groups[0].ntiles >= 4096);
     int64_t left = maxn;
-    while (left >= b->chunk) {
+    while (!direct && left >= b->chunk) {
         if (!b->graph && (rc = batch_build_graph(b))) return rc;
         HIPCHK(hipGraphLaunch(b->graph, b->stream));
         left -= b->chunk;

@@ -439,7 +439,8 @@ hipError_t launch_init(const LatDesc &d, int dst, const double *rho, const doubl
                        const double *uy, hipStream_t s);
 hipError_t launch_set_populations(const LatDesc &d, int dst, const double *f, hipStream_t s);
 hipError_t launch_get_populations(const LatDesc &d, int src, double *f, hipStream_t s);
-// Moments and FP64 partial sums; returns the number of partial blocks.
+// Moments and, with partials, FP64 partial sums; returns the number of partial
+// blocks.
 hipError_t launch_moments(const LatDesc &d, int src, double *rho, double *ux, double *uy,
                           const double *ux_ref, const double *uy_ref, double *partials,
                           int *nblocks, hipStream_t s);

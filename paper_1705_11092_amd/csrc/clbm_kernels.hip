@@ -255,6 +255,7 @@ __global__ __launch_bounds__(kBlock) void k_moments(LatDesc d, int src, double *
             acc[2] += r * v;
         }
     }
+    if (!partials) return;
     block_sum<3>(acc);
     if (threadIdx.x == 0) {
         partials[3 * blockIdx.x + 0] = acc[0];
