@@ -248,16 +248,16 @@ enum RegionShape {
     kRegion32x32 = 1,
     kRegion64x16 = 2,
     kRegion32x16 = 3,
-    kRegion64x24 = 4,
+    kRegion64x32 = 4,
     kRegionShapes = 5,
     // With the Shan-Chen force, whose steps need two nodes less at each side.
     kRegionSc32x24 = 5,
     kRegionSc64x32 = 6
 };
-constexpr int region_w(int shape) { return shape == kRegion64x16 || shape == kRegion64x24 ? 64 : 32; }
+constexpr int region_w(int shape) { return shape == kRegion64x16 || shape == kRegion64x32 ? 64 : 32; }
 constexpr int region_h(int shape)
 {
-    return shape == kRegion32x24 || shape == kRegion64x24 ? 24 : (shape == kRegion32x32 ? 32 : 16);
+    return shape == kRegion32x24 ? 24 : (shape == kRegion32x32 || shape == kRegion64x32 ? 32 : 16);
 }
 constexpr int region_steps(int shape) { return shape == kRegion32x24 || shape == kRegion32x32 ? 8 : 4; }
 constexpr int region_tile_w(int shape) { return region_w(shape) - 2 * (region_steps(shape) - 1); }
@@ -275,19 +275,19 @@ struct TilePlan {
 // 200^2, 512^2, 2048^2 in FP32; FP64; FP16-SR): 32 x 24 8.7, 29, 345; 10.6, 49, 710;
 // 9.4, 35, 473.  32 x 32 9.9, 25, 262; 11.9, 42, 529; 11.4, 33, 353.  64 x 16 6.5, 9.7,
 // 98; 8.1, 14.9, 156; 8.2, 12.5, 120.  32 x 16 5.0, 11.4, 110; 5.9, 18, 188; 5.6, 13.5,
-// 124.  64 x 24 8.3, 12.5, 94; 11.3, 24, 199.
+// 124.  64 x 32 9.6, 11.2, 90 (FP32).
 inline double tile_us(int shape, int storage, int64_t tiles, int64_t bytes, int cus)
 {
     static const double per[4][kRegionShapes] = {
-        {7.8, 10.0, 5.3, 3.0, 11.0},  // FP64
-        {4.2, 5.3, 3.2, 1.65, 5.0},   // FP32
-        {4.4, 5.8, 3.5, 1.65, 5.4},   // 16-bit, to nearest
-        {5.3, 7.0, 4.2, 1.95, 6.5},   // 16-bit, stochastic
+        {7.8, 10.0, 5.2, 3.0, 16.0},  // FP64
+        {4.2, 5.3, 3.2, 1.65, 7.3},   // FP32
+        {4.4, 5.8, 3.5, 1.65, 7.7},   // 16-bit, to nearest
+        {5.3, 7.0, 4.2, 1.95, 8.8},   // 16-bit, stochastic
     };
     const int64_t n = (tiles + cus - 1) / cus;
     const int t = storage == ST_F64 ? 0 : (storage == ST_F32 ? 1 : (storage == ST_F16 || storage == ST_BF16 ? 2 : 3));
-    // 64 x 24 on 3000^2 and 4096^2: 5.7 and 5.1 per tile where the two buffers
-    // no longer fit the 256 MB Infinity Cache.
+    // Tiles take longer where the two buffers no longer fit the 256 MB Infinity
+    // Cache.
     const double per_tile = per[t][shape] * (2 * bytes > (int64_t)256 << 20 ? 1.08 : 1.0);
     return (t == 0 ? 2.2 : 3.5) + per_tile * n;
 }

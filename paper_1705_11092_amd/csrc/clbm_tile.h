@@ -47,6 +47,19 @@ __device__ __forceinline__ void store_at(T *base, uint32_t off, T v)
 {
     *reinterpret_cast<T *>(reinterpret_cast<char *>(base) + (uint64_t)off) = v;
 }
+// base advanced by a row's (and slot's) byte offset.  In regions 64 cells wide
+// a wave's cells share their row, the offset is uniform, and the scalar unit
+// adds it; in narrower ones it joins the lane's offset.
+template <bool UNIFORM, typename T>
+__device__ __forceinline__ T *row_base_at(T *base, uint32_t row, uint32_t &off)
+{
+    if constexpr (UNIFORM) {
+        using C = std::conditional_t<std::is_const_v<T>, const char, char>;
+        return reinterpret_cast<T *>(reinterpret_cast<C *>(base) + (uint64_t)row);
+    }
+    off += row;
+    return base;
+}
 
 template <int RW_, int RH_, int K_, int NT_>
 struct Region {
@@ -71,12 +84,14 @@ __device__ __forceinline__ void tile_steps(const LatDesc &d, int src, int x0, in
     using R = typename S::R;
     constexpr int RW = RG::RW, RH = RG::RH, M = RG::M, H = RG::K - 1;
     // Cells loaded and collided together: more at once cost registers, and
-    // with them the second block on the compute unit (64 x 24, FP32: 110 VGPRs).
+    // with them the second block on the compute unit.
     constexpr int kStage = 2;
     const T *in = static_cast<const T *>(d.buf[src]);
     T *out = static_cast<T *>(d.buf[src ^ 1]);
     const Rates<R> rt = rates_of<R>(d);
-    const int c = threadIdx.x % RW, rt0 = threadIdx.x / RW;
+    constexpr bool kU = RW == 64;  // a wave's cells lie in one row
+    const int c = threadIdx.x % RW;
+    const int rt0 = kU ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / RW) : (int)threadIdx.x / RW;
     const int we = d.nx - x0 < RG::TW ? d.nx - x0 : RG::TW;  // the tile's columns and rows in the lattice
     const int he = d.ny - y0 < RG::TH ? d.ny - y0 : RG::TH;
 
@@ -124,9 +139,13 @@ __device__ __forceinline__ void tile_steps(const LatDesc &d, int src, int x0, in
                 p[o] = rv[i];
             }
         } else {
-            const uint32_t o = row_off(y0 + r - H) + (uint32_t)(x0 + c - H) * kB;
+            const uint32_t ro = row_off(y0 + r - H);
 #pragma unroll
-            for (int i = 0; i < 9; ++i) store_at(out, o + (uint32_t)i * ds, rv[i]);
+            for (int i = 0; i < 9; ++i) {
+                uint32_t o = (uint32_t)(x0 + c - H) * kB;
+                T *p = row_base_at<kU>(out, (uint32_t)i * ds + ro, o);
+                store_at(p, o, rv[i]);
+            }
         }
     };
     // Whether step l is needed at region row r and this thread's column: the
@@ -161,10 +180,14 @@ __device__ __forceinline__ void tile_steps(const LatDesc &d, int src, int x0, in
             const uint32_t rp = row_off(y == d.ny - 1 ? 0 : y + 1);
 #pragma unroll
             for (int i = 0; i < 9; ++i) {
-                uint32_t o = (uint32_t)i * ds + (ey_of(i) == 0 ? r0 : (ey_of(i) == 1 ? rm : rp)) +
-                             (ex_of(i) == 0 ? c0 : (ex_of(i) == 1 ? cm : cp));
-                if (WALL && ((ey_of(i) == 1 && lo[m]) || (ey_of(i) == -1 && hi[m]))) o = (uint32_t)opp_of(i) * ds + r0 + c0;
-                ga[m - m0][i] = S::to_r(load_at(in, o));
+                uint32_t ro = (uint32_t)i * ds + (ey_of(i) == 0 ? r0 : (ey_of(i) == 1 ? rm : rp));
+                uint32_t o = ex_of(i) == 0 ? c0 : (ex_of(i) == 1 ? cm : cp);
+                if (WALL && ((ey_of(i) == 1 && lo[m]) || (ey_of(i) == -1 && hi[m]))) {
+                    ro = (uint32_t)opp_of(i) * ds + r0;
+                    o = c0;
+                }
+                const T *p = row_base_at<kU>(in, ro, o);
+                ga[m - m0][i] = S::to_r(load_at(p, o));
             }
         }
 #pragma unroll
@@ -233,7 +256,9 @@ __device__ __forceinline__ void sc_tile_steps(const LatDesc &d, int src, int x0,
     const T *in = static_cast<const T *>(d.buf[src]);
     T *out = static_cast<T *>(d.buf[src ^ 1]);
     const Rates<R> rt = rates_of<R>(d);
-    const int c = threadIdx.x % RW, rt0 = threadIdx.x / RW;
+    constexpr bool kU = RW == 64;  // a wave's cells lie in one row
+    const int c = threadIdx.x % RW;
+    const int rt0 = kU ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / RW) : (int)threadIdx.x / RW;
     const int we = d.nx - x0 < RG::TW ? d.nx - x0 : RG::TW;
     const int he = d.ny - y0 < RG::TH ? d.ny - y0 : RG::TH;
     const int x = wrap_any(x0 - H + c, d.nx);
@@ -259,9 +284,11 @@ __device__ __forceinline__ void sc_tile_steps(const LatDesc &d, int src, int x0,
         const uint32_t r0 = row_off(y), rm = row_off(y == 0 ? d.ny - 1 : y - 1),
                        rp = row_off(y == d.ny - 1 ? 0 : y + 1);
 #pragma unroll
-        for (int i = 0; i < 9; ++i)
-            g[m][i] = S::to_r(load_at(in, (uint32_t)i * ds + (ey_of(i) == 0 ? r0 : (ey_of(i) == 1 ? rm : rp)) +
-                                              (ex_of(i) == 0 ? c0 : (ex_of(i) == 1 ? cm : cp))));
+        for (int i = 0; i < 9; ++i) {
+            uint32_t o = ex_of(i) == 0 ? c0 : (ex_of(i) == 1 ? cm : cp);
+            const T *p = row_base_at<kU>(in, (uint32_t)i * ds + (ey_of(i) == 0 ? r0 : (ey_of(i) == 1 ? rm : rp)), o);
+            g[m][i] = S::to_r(load_at(p, o));
+        }
     }
     for (int l = 1; l <= n; ++l) {
         const int e = 2 * (n - l);  // this step's collisions reach e nodes beyond the tile
@@ -312,9 +339,13 @@ __device__ __forceinline__ void sc_tile_steps(const LatDesc &d, int src, int x0,
 #pragma unroll
                 for (int i = 1; i < 9; ++i) lds.v[i - 1][r][c] = rv[i];
             } else {
-                const uint32_t o = row_off(y0 + r - H) + (uint32_t)(x0 + c - H) * kB;
+                const uint32_t ro = row_off(y0 + r - H);
 #pragma unroll
-                for (int i = 0; i < 9; ++i) store_at(out, o + (uint32_t)i * ds, rv[i]);
+                for (int i = 0; i < 9; ++i) {
+                    uint32_t o = (uint32_t)(x0 + c - H) * kB;
+                    T *p = row_base_at<kU>(out, (uint32_t)i * ds + ro, o);
+                    store_at(p, o, rv[i]);
+                }
             }
         }
     }
@@ -367,7 +398,7 @@ using RegionOf = std::conditional_t<
     std::conditional_t<
         SHAPE == kRegion32x32, Region<32, 32, 8, 1024>,
         std::conditional_t<SHAPE == kRegion64x16, Region<64, 16, 4, 512>,
-                           std::conditional_t<SHAPE == kRegion32x16, Region<32, 16, 4, 512>, Region<64, 24, 4, 512>>>>>;
+                           std::conditional_t<SHAPE == kRegion32x16, Region<32, 16, 4, 512>, Region<64, 32, 4, 512>>>>>;
 
 }  // namespace
 
@@ -420,7 +451,7 @@ hipError_t launch_tile_st(const LatDesc &d, int src, int n, const TilePlan &p, h
     case kRegion32x32: return tile_shape_launch<ST, kRegion32x32>(d, src, n, p, s);
     case kRegion64x16: return tile_shape_launch<ST, kRegion64x16>(d, src, n, p, s);
     case kRegion32x16: return tile_shape_launch<ST, kRegion32x16>(d, src, n, p, s);
-    case kRegion64x24: return tile_shape_launch<ST, kRegion64x24>(d, src, n, p, s);
+    case kRegion64x32: return tile_shape_launch<ST, kRegion64x32>(d, src, n, p, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -460,7 +491,7 @@ hipError_t launch_batch_tile_st(const LatDesc *lats, const int32_t *tile_lat, in
     case kRegion32x32: return batch_tile_shape_launch<ST, kRegion32x32>(lats, tile_lat, ntiles, key, walls, sub, s);
     case kRegion64x16: return batch_tile_shape_launch<ST, kRegion64x16>(lats, tile_lat, ntiles, key, walls, sub, s);
     case kRegion32x16: return batch_tile_shape_launch<ST, kRegion32x16>(lats, tile_lat, ntiles, key, walls, sub, s);
-    case kRegion64x24: return batch_tile_shape_launch<ST, kRegion64x24>(lats, tile_lat, ntiles, key, walls, sub, s);
+    case kRegion64x32: return batch_tile_shape_launch<ST, kRegion64x32>(lats, tile_lat, ntiles, key, walls, sub, s);
     default: return hipErrorInvalidValue;
     }
 }
