@@ -4,13 +4,13 @@ Workload: the decaying Taylor-Green vortex plus a uniform body force
 (Fx, Fy) = (1e-6, 5e-7) on a periodic 4096 x 4096 lattice, u0 = 0.01,
 nu = 0.01, populations stored as FP32 deviations f_i - w_i rho0, FP32
 arithmetic.  A step is one collide-and-stream update of the whole lattice
-(Eqs. 9-15); the library advances this lattice two fused steps per launch
-(step n + 1 on a tile and its halo kept in LDS, step n + 2 from there).
+(Eqs. 9-15); the library advances this lattice four fused steps per launch
+(waves march down the rows with four time levels in registers).
 Inputs are resident in HBM before timing starts.
 
-Prints one JSON line: MLUPS, the HBM roofline of the two-step kernel (per
-launch the state is read and written once: 72 algorithmic bytes per node
-for two node updates) and the oracle's throughput on the host cores for a
+Prints one JSON line: MLUPS, the HBM roofline of that kernel (per launch the
+state is read and written once: 72 algorithmic bytes per node for four node
+updates) and the oracle's throughput on the host cores for a
 bounded sample of the same workload.  Beside it, in the same line: the same
 lattice one step per launch (72 bytes per node update), the same lattice streamed in place
 (one buffer), the same lattice with FP64 and 16-bit storage, the 64 x 32
@@ -46,8 +46,8 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, published
 BYTES_PER_LUP = {"f64": 144, "f32": 72, "f16": 36, "bf16": 36, "f16sr": 36, "bf16sr": 36}
-KERNEL_SOURCES = ["paper_1705_11092_amd/csrc/clbm_step_f32.hip",
-                  "paper_1705_11092_amd/csrc/clbm_step2.h",
+KERNEL_SOURCES = ["paper_1705_11092_amd/csrc/clbm_sweep_f32.hip",
+                  "paper_1705_11092_amd/csrc/clbm_sweep.h",
                   "paper_1705_11092_amd/csrc/clbm_step.h",
                   "paper_1705_11092_amd/csrc/clbm_layout.h",
                   "paper_1705_11092_amd/csrc/clbm_force.h",
@@ -89,7 +89,7 @@ def measured_traffic(storage: str, n_nodes: int):
 
 
 def measured_valu(storage: str, n_nodes: int):
-    """VALU wave-instructions per launch of the two-step kernel from the
+    """VALU wave-instructions per launch of the four-step kernel from the
     committed rocprofv3 counter summary, or None when the kernel sources
     changed since it was taken."""
     try:
@@ -116,8 +116,9 @@ def run_gpu(n: int, storage: str, steps: int, warmup: int, inplace: bool = False
 
     wl = inputs.taylor_green(n, u0=0.01, nu=0.01, F=(1e-6, 5e-7), steps=steps)
     lat = clbm.lattice_from_workload(wl, storage=storage, inplace=inplace)
-    lat.step_pairs = pairs
+    lat.step_pairs = None if pairs else False  # the default fused steps, or singly
     run_gpu.pairs = lat.step_pairs
+    run_gpu.per_launch = lat.steps_per_launch
     stream = lat.stream
     lat.step(warmup)
     torch.cuda.synchronize()
@@ -166,7 +167,7 @@ def run_small():
     for st in ("f64", "f32"):
         wl = inputs.taylor_green(1024, u0=0.01, nu=0.01, F=(1e-6, 5e-7), steps=2000)
         lat = clbm.lattice_from_workload(wl, storage=st)
-        per_launch = 2 if lat.step_pairs else 1
+        per_launch = lat.steps_per_launch
         us = timed(lat, 2000)
         lat.close()
         out[f"taylor_green_1024_{st}"] = {
@@ -179,8 +180,8 @@ def run_small():
 
 def run_batch(steps: int, warmup: int, count: int = 256, variant: int = -1, reps: int = 3):
     """The batch of uneven Kolmogorov lattices (sides log-uniform in
-    [32, 512], seed 0), FP32 storage, two fused steps per launch over all
-    lattices (hbm_frac: 72 B per node per launch, i.e. per two updates).
+    [32, 512], seed 0), FP32 storage, several fused steps per launch over all
+    lattices (hbm_frac_one_step_model: 72 B per node update).
     The kernel variant is the autotuner's, or `variant` when >= 0 (a
     profiler's counters would distort the autotuner's timings)."""
     import torch
@@ -189,7 +190,6 @@ def run_batch(steps: int, warmup: int, count: int = 256, variant: int = -1, reps
     wls = inputs.kolmogorov_batch(count=count, seed=0, steps=steps)
     lats = [clbm.lattice_from_workload(wl, storage="f32") for wl in wls]
     b = clbm.Batch(lats)
-    per_launch = 2 if lats[0].step_pairs else 1
     if variant >= 0:
         b.variant = variant
     else:
@@ -216,8 +216,7 @@ def run_batch(steps: int, warmup: int, count: int = 256, variant: int = -1, reps
     return {"workload": f"{count} Kolmogorov lattices, sides log-uniform 32..512 (seed 0), f32",
             "nodes": nodes, "steps": steps, "ms_per_step": round(ms / steps, 5),
             "mlups": round(mlups, 1), "repetitions": reps, "statistic": "median",
-            "steps_per_launch": per_launch,
-            "hbm_frac": round(mlups * 1e6 * 72 / per_launch / 8e12, 4),
+            "hbm_frac_one_step_model": round(mlups * 1e6 * 72 / 8e12, 4),
             "variant": variant}
 
 
@@ -299,7 +298,7 @@ def traffic_summary(dirs, copy_bytes: int = 603979776, n: int = 4096):
     the summary bench.py reports as roofline.traffic."""
     import statistics
     csvs = [os.path.join(d, "run_counter_collection.csv") for d in dirs]
-    step = "k_step2<1, 0, 0, unsigned int"
+    step = "k_sweep<1, 0, 0, 4, 2, false>"
     fetch = _counter_values(csvs[0], step, "FETCH_SIZE")
     write = _counter_values(csvs[1], step, "WRITE_SIZE")
     cf = statistics.median(_counter_values(csvs[2], "copyBuffer", "FETCH_SIZE"))
@@ -310,11 +309,11 @@ def traffic_summary(dirs, copy_bytes: int = 603979776, n: int = 4096):
     wr = statistics.median(write) * 1024.0 * ws
     alg = BYTES_PER_LUP["f32"] * n * n
     base = "rocprofv3 --pmc {c} --output-format csv -d {d} -o run -- python3 bench.py {a}"
-    step_args = "--steps 6 --warmup 0 --reps 1 --no-cpu-baseline --no-extra"
+    step_args = "--steps 24 --warmup 0 --reps 1 --no-cpu-baseline --no-extra"
     copy_args = f"--calibrate-copy {copy_bytes}"
     out = {
-        "kernel": "clbm::k_step2<1, 0, 0, unsigned int, Tile<64, 16, 4>> (two fused steps per launch; FP32 "
-                  "deviations, constant force, consistent scheme, 64 x 16 tiles)",
+        "kernel": "clbm::k_sweep<1, 0, 0, 4, 2, false> (four fused steps per launch; FP32 deviations, constant "
+                  "force, consistent scheme, two columns per lane, periodic)",
         "workload": f"taylor_green_{n}x{n}_uniform_force", "storage": "f32", "nodes": n * n,
         "kernel_hash": kernel_hash(),
         "commands": [base.format(c="FETCH_SIZE", d=dirs[0], a=step_args),
@@ -335,13 +334,13 @@ def traffic_summary(dirs, copy_bytes: int = 603979776, n: int = 4096):
 
 
 def valu_summary(d: str, n: int = 4096):
-    """VALU wave-instructions, waves and clock per launch of the two-step
+    """VALU wave-instructions, waves and clock per launch of the four-step
     kernel from one rocprofv3 --pmc SQ_INSTS_VALU SQ_WAVES GRBM_GUI_ACTIVE run
     (its run_counter_collection.csv), written to profiles/valu_step_f32_tg4096.json
     with the hash of the kernel sources it was taken on."""
     import csv
     import statistics
-    step = "k_step2<1, 0, 0, unsigned int"
+    step = "k_sweep<1, 0, 0, 4, 2, false>"
     per = {}
     with open(os.path.join(d, "run_counter_collection.csv"), newline="") as fh:
         for row in csv.DictReader(fh):
@@ -357,15 +356,15 @@ def valu_summary(d: str, n: int = 4096):
     waves = statistics.median(e["SQ_WAVES"] for e in per.values())
     clocks = [e["GRBM_GUI_ACTIVE"] / 8.0 / e["ns"] for e in per.values() if e.get("ns")]
     out = {
-        "kernel": "clbm::k_step2<1, 0, 0, unsigned int, Tile<64, 16, 4>> (two fused steps per launch; FP32 "
-                  "deviations, constant force, consistent scheme, 64 x 16 tiles)",
+        "kernel": "clbm::k_sweep<1, 0, 0, 4, 2, false> (four fused steps per launch; FP32 deviations, constant "
+                  "force, consistent scheme, two columns per lane, periodic)",
         "workload": f"taylor_green_{n}x{n}_uniform_force", "storage": "f32", "nodes": n * n,
         "kernel_hash": kernel_hash(),
         "command": f"rocprofv3 --pmc SQ_INSTS_VALU SQ_WAVES GRBM_GUI_ACTIVE --output-format csv -d {d} -o run "
-                   "-- python3 bench.py --steps 6 --warmup 0 --reps 1 --no-cpu-baseline --no-extra",
+                   "-- python3 bench.py --steps 24 --warmup 0 --reps 1 --no-cpu-baseline --no-extra",
         "dispatches": len(per), "valu_wave_insts_per_launch": valu, "waves_per_launch": waves,
         "valu_insts_per_wave": round(valu / waves, 1),
-        "valu_insts_per_node_update": round(valu * 64 / (2 * n * n), 1),
+        "valu_insts_per_node_update": round(valu * 64 / (4 * n * n), 1),
         "issue_us_at_2p4_ghz": round(valu / (256 * 2.4e9) * 1e6, 2),
         "clock_ghz": round(statistics.median(clocks), 3) if clocks else None,
     }
@@ -406,7 +405,7 @@ def main():
     ap.add_argument("--no-extra", action="store_true",
                     help="only the main lattice (16-bit, batch and served legs skipped)")
     ap.add_argument("--single-steps", action="store_true",
-                    help="step the main lattice one step per launch (no fused pairs)")
+                    help="step the main lattice one step per launch (no fused steps)")
     ap.add_argument("--serve-requests", type=int, default=200)
     ap.add_argument("--calibrate-copy", type=int, default=0, metavar="BYTES")
     ap.add_argument("--traffic-summary", nargs=4, default=None,
@@ -453,9 +452,9 @@ def main():
     ms_step = ms / args.steps
     mlups = nodes / (ms_step / 1e3) / 1e6
     bpl = BYTES_PER_LUP[args.storage]
-    # The dominant kernel's launch: two steps (reading and writing the state
-    # once) with pairs, one step otherwise; bytes per launch bpl * nodes.
-    steps_per_launch = 2 if pairs else 1
+    # The dominant kernel's launch reads and writes the state once for all the
+    # steps it takes; bytes per launch bpl * nodes.
+    steps_per_launch = run_gpu.per_launch
     ms_launch = ms_step * steps_per_launch
     achieved = bpl * nodes / (ms_launch / 1e3) / 1e9
     traffic = measured_traffic(args.storage, nodes) if pairs else None
@@ -478,12 +477,13 @@ def main():
                          "clock_ghz_under_counters": valu.get("clock_ghz")}
     bound = max(limits, key=lambda k: limits[k]["frac"])
     roof = {"bound": bound, **{k: v for k, v in limits[bound].items()},
-            "kernel": "k_step2 (two fused steps per launch)" if pairs else "k_step",
+            "kernel": {4: "k_sweep (four fused steps per launch)", 2: "k_step2 (two fused steps per launch)",
+                       1: "k_step"}.get(steps_per_launch, f"{steps_per_launch} fused steps per launch"),
             "ms_per_launch": round(ms_launch, 5), "limits": limits}
     if pairs:
         # The per-update byte model (every node update reads and writes the
-        # state once) does not hold for fused pairs: the state crosses HBM
-        # once per two updates.
+        # state once) does not hold for fused steps: the state crosses HBM
+        # once per launch.
         per_update = bpl * nodes * steps_per_launch / (ms_launch / 1e3) / 1e9
         roof["per_update_model"] = {"bytes_per_update": bpl, "equivalent_gb_s": round(per_update, 1),
                                     "frac_of_hbm_peak": round(per_update / HBM_PEAK_GBS, 4),
@@ -528,12 +528,12 @@ def main():
             "footprint_bytes": nodes * bpl // 2}
         for st in ("f64", "f16", "bf16", "f16sr", "bf16sr"):
             ms16, _, _ = run_gpu(args.n, st, args.steps, args.warmup)
-            spl = 2 if run_gpu.pairs else 1
+            spl = run_gpu.per_launch
             m = nodes / (ms16 / args.steps / 1e3) / 1e6
             extra[st] = {"mlups": round(m, 1), "ms_per_step": round(ms16 / args.steps, 5),
                          "steps_per_launch": spl,
                          "hbm_frac": round(m * 1e6 * BYTES_PER_LUP[st] / spl / 8e12, 4)}
-            if spl == 2:
+            if spl > 1:
                 ms1, _, _ = run_gpu(args.n, st, args.steps, args.warmup, pairs=False)
                 m1 = nodes / (ms1 / args.steps / 1e3) / 1e6
                 extra[f"{st}_one_step_per_launch"] = {

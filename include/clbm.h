@@ -157,10 +157,10 @@ int clbm_destroy(clbm_handle *h);
  * [ny][nx]) into a library-owned device buffer in the arithmetic type, so
  * the caller may free them once the stream has passed this call.
  * SHAN_CHEN reads params[3] = {G, psi0, rho_ref} (host) and makes the force
- * depend on the state (Sec. IV C): at every step, before any node collides,
- * a pass writes psi = psi0 exp(-rho_ref / rho) of each node's pre-collision
- * density (Eq. 11) into a library-owned [ny][nx] plane in the arithmetic
- * type; the step then takes F(x) = -G psi(x) sum_i w_i psi(x + e_i) e_i
+ * depend on the state (Sec. IV C): at every step psi = psi0 exp(-rho_ref / rho)
+ * of each node's pre-collision density (Eq. 11) is formed in the arithmetic
+ * type, in the fused steps' LDS or, where the lattice steps singly, by a pass
+ * into a library-owned [ny][nx] plane; the step then takes F(x) = -G psi(x) sum_i w_i psi(x + e_i) e_i
  * with w = 1/3 on the axes and 1/12 on the diagonals.  G < 0 attracts
  * (the phase-separating sign).  Needs a periodic lattice (bc_y periodic);
  * such a handle cannot join a batch.  clbm_init, clbm_moments and
@@ -184,11 +184,12 @@ int clbm_init(clbm_handle *h, const double *rho, const double *ux, const double 
 
 /* Advance nsteps >= 0 time steps: per node the collision of Eq. (12) and
  * the back-transform of Eq. (9), then streaming (Eq. 10), fused in one
- * kernel launch per step (two buffers: each node gathers its pre-collision
- * populations from its neighbours' post-collision ones; in place: the AA
- * pattern of clbm_streaming).  Two-buffer lattices (any force but
- * Shan-Chen) advance two steps per launch by default (clbm_set_step_pairs),
- * with bitwise the same result.  Long runs replay a captured hipGraph.
+ * kernel (two buffers: each node gathers its pre-collision populations from
+ * its neighbours' post-collision ones; in place: the AA pattern of
+ * clbm_streaming).  Two-buffer lattices advance several steps per launch by
+ * default (clbm_set_step_pairs, clbm_steps_per_launch), with bitwise the same
+ * result.  Long runs of short launches replay a captured hipGraph
+ * (clbm_set_graph_steps).
  * Errors: CLBM_ESTATE before clbm_init or clbm_set_populations, CLBM_EINVAL
  * (nsteps < 0), CLBM_EHIP. */
 int clbm_step(clbm_handle *h, int64_t nsteps);
@@ -243,7 +244,8 @@ int clbm_get_populations(clbm_handle *h, double *f);
 int clbm_set_populations(clbm_handle *h, const double *f);
 
 /* Steps per captured hipGraph replay in clbm_step; 0 launches every step
- * directly.  Default 64. */
+ * directly.  By default 64 where launches are short (lattices of up to 600,000
+ * nodes that step singly or in pairs) and 0 elsewhere. */
 int clbm_set_graph_steps(clbm_handle *h, int32_t steps);
 
 /* Cap on the step kernel's resident blocks per compute unit (0 = none, or
@@ -258,20 +260,25 @@ int clbm_set_graph_steps(clbm_handle *h, int32_t steps);
  * Errors: CLBM_EINVAL. */
 int clbm_set_occupancy(clbm_handle *h, int32_t blocks_per_cu);
 
-/* Two fused steps per launch (enable = 1) or one (0), or the default (-1).  A block
- * computes step n + 1 on a tile (64 x 16 nodes, 64 x 8 for FP64) and a
- * one-node halo from HBM, keeps it in LDS, and computes step n + 2 from
- * there, so the state crosses HBM
- * once per two steps; every node update is the one-step kernel's, so results
- * are bitwise equal either way (stochastic rounding included: a node's
- * operand depends on its index and values only).  Applies to two-buffer
- * lattices of every storage type without the Shan-Chen force; in-place
- * lattices always step singly.  The default, from measurements on MI355X:
- * pairs for every storage type at every size.  clbm_get_step_pairs
- * returns 1 when this lattice steps in pairs, 0 when not, -1 for NULL.
+/* Fused steps: two per launch (enable = 1), one (0), or the default (-1), as
+ * many as measured fastest on MI355X for the lattice.  With 1 a block computes
+ * step n + 1 on a tile (64 x 16 nodes, 64 x 8 for FP64) and a one-node halo
+ * from HBM, keeps it in LDS, and computes step n + 2 from there, so the state
+ * crosses HBM once per two steps.  The default takes up to four or eight steps
+ * per launch in LDS tiles (lattices of up to about a million nodes, and any
+ * Shan-Chen lattice), four in a kernel that marches down the rows with four
+ * time levels in registers (larger FP32 and FP64 lattices), and otherwise
+ * pairs.  Every node update is the one-step kernel's, so results are bitwise
+ * equal (stochastic rounding included: a node's operand depends on its index
+ * and values only).  In-place lattices always step singly, and Shan-Chen ones
+ * under 0 or 1.  clbm_get_step_pairs returns 1 when this lattice takes two or
+ * more fused steps per launch (0 for Shan-Chen lattices), 0 when not, -1 for
+ * NULL; clbm_steps_per_launch the most steps of one launch (1, 2, 4 or 8; the
+ * resident kernel aside), -1 for NULL.
  * Errors: CLBM_EINVAL (NULL handle, enable not -1, 0 or 1). */
 int clbm_set_step_pairs(clbm_handle *h, int32_t enable);
 int32_t clbm_get_step_pairs(const clbm_handle *h);
+int32_t clbm_steps_per_launch(const clbm_handle *h);
 int32_t clbm_get_occupancy(const clbm_handle *h); /* -1 for NULL */
 
 /* Small lattices step in a resident kernel: one block of 1024 threads that
@@ -279,10 +286,11 @@ int32_t clbm_get_occupancy(const clbm_handle *h); /* -1 for NULL */
  * barrier between steps, instead of one launch per step (tiny lattices are
  * otherwise bound by launch overhead).  It applies when the lattice has at
  * most max_groups groups of nodes (ny x padded nx / nodes per thread, 2
- * nodes per thread for FP64 and 4 otherwise; default 512, the measured
- * break-even on MI355X: one compute unit does all the work, so larger
- * lattices step faster as graphed launches), nsteps >= 2 and the force is
- * not Shan-Chen.  0 disables it; the limit is at most 2^20.  Results are
+ * nodes per thread for FP64 and 4 otherwise), nsteps >= 2 and the force is
+ * not Shan-Chen.  The default is 512 for in-place lattices, the measured
+ * break-even on MI355X (one compute unit does all the work, so larger
+ * lattices step faster as graphed launches), and 0 for two-buffer ones, which
+ * step faster in LDS tiles.  0 disables it; the limit is at most 2^20.  Results are
  * bitwise the same either way.  Errors: CLBM_EINVAL. */
 int clbm_set_resident_limit(clbm_handle *h, int64_t max_groups);
 
@@ -300,7 +308,8 @@ double clbm_s_from_nu(double nu);
 
 /* A batch advances many independent lattices (any sizes, storages, forces,
  * rates, y boundaries and streaming forms; not Shan-Chen) with one
- * kernel launch per time step (or per fused pair of steps) and kernel kind.
+ * kernel launch per time step (or per two, four or eight fused steps) and
+ * kernel kind.
  * Each node is updated by exactly the arithmetic of clbm_step, so a
  * lattice's result is bitwise the same alone and in any batch. */
 typedef struct clbm_batch clbm_batch;
@@ -324,12 +333,15 @@ int clbm_batch_step_each(clbm_batch *b, const int64_t *nsteps);
 /* Time the kernel variants of the batch on its own lattices and keep the
  * fastest (results do not depend on the variant).  A variant has two parts:
  * one for the lattices that step one step per launch (bytes per thread per
- * direction, occupancy cap, persistent grid) and one for those that step
- * in fused pairs (tile shape 64 x 16 or 32 x 32 nodes -- half as many rows
- * for FP64 -- or per lattice whichever of the two covers it with fewer
- * tiles; one block per tile or persistent blocks walking the tiles).  The first part is chosen on the
- * lattices that step singly, timing one step of each, then the second on
- * those that step in pairs, timing one fused pair of each.  With cache_path
+ * direction, occupancy cap, persistent grid) and one for those that take
+ * fused steps: variant 0 the default stepping of clbm_set_step_pairs in LDS
+ * tiles of one region shape per storage type, or pairs where those are
+ * modelled faster; the others pairs (tile shape 64 x 16 or 32 x 32 nodes --
+ * half as many rows for FP64 -- or per lattice whichever of the two covers it
+ * with fewer tiles; one block per tile or persistent blocks walking the
+ * tiles), which lattices set to pairs take under any variant.  The first part
+ * is chosen on the lattices that step singly, timing one step of each, then
+ * the second on those that take fused steps, timing eight.  With cache_path
  * set, look the choice up first and record it after, keyed by architecture,
  * variant set and batch shape.  *chosen (optional) receives the variant
  * index.  The timed launches leave every lattice's state untouched: with

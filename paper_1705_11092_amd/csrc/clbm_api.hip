@@ -335,7 +335,7 @@ void plan_fused(clbm_handle *h)
     if (eb != 2 && d.nx >= 64 && d.ny >= 64) {
         const clbm::SweepPlan p =
             clbm::sweep_plan(d.nx, d.ny, eb, 4 * cus, clbm::sweep_max_vec(d.storage, d.force_mode, d.bc_y));
-        if (clbm::sweep_us(nodes, eb, 4 * cus, p.vec, p.rows, p.units) / clbm::kSweepSteps < us) {
+        if (clbm::sweep_us(nodes, eb, 4 * cus, p.vec, p.halo, p.rows, p.units) / clbm::kSweepSteps < us) {
             h->sweep = p;
             return;
         }
@@ -763,6 +763,14 @@ int clbm_set_step_pairs(clbm_handle *h, int32_t enable)
 }
 
 int32_t clbm_get_step_pairs(const clbm_handle *h) { return h ? (use_pairs(h) ? 1 : 0) : -1; }
+
+int32_t clbm_steps_per_launch(const clbm_handle *h)
+{
+    if (!h) return -1;
+    if (use_tiles(h)) return h->tile.steps;
+    if (use_sweeps(h)) return clbm::kSweepSteps;
+    return use_pairs(h) ? 2 : 1;
+}
 
 int clbm_set_occupancy(clbm_handle *h, int32_t blocks_per_cu)
 {

@@ -196,16 +196,17 @@ constexpr int sweep_max_vec(int storage, int force_mode, int bc_y)
 // of the busiest SIMD (a wave collides rows + K - 1 rows of each of K levels on
 // average, 0.230 us per level and column of a lane in FP32, 0.262 in FP64; one
 // wave per SIMD hides its latencies to 72 % of the issue rate, two to 92 %), or
-// memory at 4.8 TB/s (3.3 with one wave per SIMD; each chunk reads 2 K rows
-// beyond its own), plus 3 us of launch.  Within 10 % of what 1024^2, 2048^2 and
+// memory at 4.8 TB/s (3.3 with one wave per SIMD; each chunk reads 2 K rows and
+// each strip 2 halo lanes beyond its own), plus 3 us of launch.  Within 10 % of what 1024^2, 2048^2 and
 // 4096^2 lattices take (FP64 48, 154, 532 us; FP32 31, 95, 300).
-inline double sweep_us(int64_t nodes, int eb, int simds, int vec, int rows, int64_t units)
+inline double sweep_us(int64_t nodes, int eb, int simds, int vec, int halo, int rows, int64_t units)
 {
     const int64_t n = (units + simds - 1) / simds;  // waves on the busiest SIMD
     const double eff = n == 1 ? 0.72 : (n == 2 ? 0.92 : 0.95);
     const double valu = kSweepSteps * (eb == 8 ? 0.262 : 0.230) * vec * n * (rows + kSweepSteps) / eff;
     const double state = 9.0 * nodes * eb;
-    const double mem = state * (2.0 + 2.0 * kSweepSteps / rows) / (n == 1 ? 3.3e6 : 4.8e6);
+    const double reads = 64.0 / (64 - 2 * halo) * (1.0 + 2.0 * kSweepSteps / rows);
+    const double mem = state * (1.0 + reads) / (n == 1 ? 3.3e6 : 4.8e6);
     return (valu > mem ? valu : mem) + 3.0;
 }
 
@@ -230,7 +231,7 @@ inline SweepPlan sweep_plan(int nx, int ny, int eb, int simds, int max_vec)
             p.rows = (int)((ny + chunks - 1) / chunks);
             const int64_t units = (int64_t)p.strips * ((ny + p.rows - 1) / p.rows);
             p.units = (int32_t)units;
-            const double us = sweep_us((int64_t)nx * ny, eb, simds, vec, p.rows, units);
+            const double us = sweep_us((int64_t)nx * ny, eb, simds, vec, p.halo, p.rows, units);
             if (best.vec == 0 || us < best_us) {
                 best = p;
                 best_us = us;
