@@ -272,34 +272,35 @@ struct TilePlan {
 
 // Microseconds of one launch of K steps: a fixed part (launch, first loads,
 // last stores) and the tiles a compute unit takes one after another or side
-// by side (bytes: one buffer of all the lattices).  Fitted on MI355X to 200^2 ... 2048^2 lattices (us per launch at
-// 200^2, 512^2, 2048^2 in FP32; FP64; FP16-SR): 32 x 24 8.7, 29, 345; 10.6, 49, 710;
-// 9.4, 35, 473.  32 x 32 9.9, 25, 262; 11.9, 42, 529; 11.4, 33, 353.  64 x 16 6.5, 9.7,
-// 98; 8.1, 14.9, 156; 8.2, 12.5, 120.  32 x 16 5.0, 11.4, 110; 5.9, 18, 188; 5.6, 13.5,
-// 124.  64 x 32 9.6, 11.2, 90 (FP32).
+// by side (bytes: one buffer of all the lattices).  Fitted on MI355X to flows
+// on 64 x 32 ... 4096^2 lattices, within 12 % (us per launch at 200^2, 512^2,
+// 2048^2): FP32 32 x 24 8.7, 28; 32 x 32 9.8, 25; 64 x 16 6.8, 9.8, 94;
+// 32 x 16 5.6, 11.3, 111; 64 x 32 9.8, 10.8, 91.  FP64 10.4, 41; 12.0, 40;
+// 8.2, 13.7, 168; 6.0, 15.8, 184; 13.9, 15.8, 194.  FP16-SR 10.0, 36; 11.5, 31;
+// 8.1, 11.5, 106; 6.0, 12.7, 125; 13.2, 14.0, 94.
 inline double tile_us(int shape, int storage, int64_t tiles, int64_t bytes, int cus)
 {
-    static const double per[4][kRegionShapes] = {
-        {7.8, 10.0, 5.2, 3.0, 16.0},  // FP64
-        {4.2, 5.3, 3.2, 1.65, 7.3},   // FP32
-        {4.4, 5.8, 3.5, 1.65, 7.7},   // 16-bit, to nearest
-        {5.3, 7.0, 4.2, 1.95, 8.8},   // 16-bit, stochastic
+    struct Fit { double fixed, per; };
+    static const Fit fit[4][kRegionShapes] = {
+        {{5.0, 5.8}, {3.7, 9.0}, {4.2, 4.6}, {3.4, 2.5}, {1.5, 15.0}},     // FP64
+        {{4.8, 3.8}, {4.7, 5.07}, {4.2, 2.7}, {3.9, 1.45}, {3.5, 6.7}},    // FP32
+        {{4.5, 4.2}, {4.7, 5.45}, {5.0, 2.8}, {3.9, 1.52}, {7.0, 6.05}},   // 16-bit, to nearest
+        {{5.0, 4.9}, {5.0, 6.5}, {5.0, 3.25}, {3.9, 1.79}, {7.0, 7.2}},    // 16-bit, stochastic
     };
     const int64_t n = (tiles + cus - 1) / cus;
     const int t = storage == ST_F64 ? 0 : (storage == ST_F32 ? 1 : (storage == ST_F16 || storage == ST_BF16 ? 2 : 3));
-    // Tiles take longer where the two buffers no longer fit the 256 MB Infinity
-    // Cache.
-    const double per_tile = per[t][shape] * (2 * bytes > (int64_t)256 << 20 ? 1.08 : 1.0);
-    return (t == 0 ? 2.2 : 3.5) + per_tile * n;
+    // Tiles of FP32 and FP64 take longer where the two buffers no longer fit the
+    // 256 MB Infinity Cache.
+    const double miss = 2 * bytes > (int64_t)256 << 20 ? (t == 0 ? 1.17 : (t == 1 ? 1.08 : 1.0)) : 1.0;
+    return fit[t][shape].fixed + fit[t][shape].per * miss * n;
 }
 
 // Microseconds of one launch of a fused pair on `tiles` tiles of 64 x 16
 // nodes (64 x 8 in FP64), four and more of which share a compute unit.
 inline double pair_us(int storage, int64_t tiles, int cus)
 {
-    const double per = storage == ST_F64 ? 3.2 : (storage == ST_F32 ? 3.4 : (storage == ST_F16 || storage == ST_BF16 ? 2.4 : 2.7));
-    const double us = 4.0 + per * tiles / cus;
-    return us < 5.8 ? 5.8 : us;
+    const double per = storage == ST_F64 ? 3.2 : (storage == ST_F32 ? 3.35 : (storage == ST_F16 || storage == ST_BF16 ? 2.27 : 2.5));
+    return 6.0 + per * tiles / cus;
 }
 
 // The plan with the least time per step, which goes to *us_per_step.

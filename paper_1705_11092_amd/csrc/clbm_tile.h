@@ -61,6 +61,18 @@ __device__ __forceinline__ T *row_base_at(T *base, uint32_t row, uint32_t &off)
     return base;
 }
 
+// Keeps a loop-invariant value, and all that follows from it, from being formed
+// ahead of the loop: the last step's store addresses, 9 per cell, would
+// otherwise sit in registers through every step.
+template <bool UNIFORM>
+__device__ __forceinline__ void form_here(uint32_t &v)
+{
+    if constexpr (UNIFORM)
+        asm volatile("" : "+s"(v));
+    else
+        asm volatile("" : "+v"(v));
+}
+
 template <int RW_, int RH_, int K_, int NT_>
 struct Region {
     static constexpr int RW = RW_, RH = RH_, K = K_, NT = NT_;
@@ -89,7 +101,7 @@ __device__ __forceinline__ void tile_steps(const LatDesc &d, int src, int x0, in
     const T *in = static_cast<const T *>(d.buf[src]);
     T *out = static_cast<T *>(d.buf[src ^ 1]);
     const Rates<R> rt = rates_of<R>(d);
-    constexpr bool kU = RW == 64;  // a wave's cells lie in one row
+    constexpr bool kU = RW % 64 == 0;  // a wave's cells lie in one row
     const int c = threadIdx.x % RW;
     const int rt0 = kU ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / RW) : (int)threadIdx.x / RW;
     const int we = d.nx - x0 < RG::TW ? d.nx - x0 : RG::TW;  // the tile's columns and rows in the lattice
@@ -139,10 +151,13 @@ __device__ __forceinline__ void tile_steps(const LatDesc &d, int src, int x0, in
                 p[o] = rv[i];
             }
         } else {
-            const uint32_t ro = row_off(y0 + r - H);
+            uint32_t ro = row_off(y0 + r - H);
+            uint32_t co = (uint32_t)(x0 + c - H) * kB;
+            form_here<kU>(ro);
+            form_here<false>(co);
 #pragma unroll
             for (int i = 0; i < 9; ++i) {
-                uint32_t o = (uint32_t)(x0 + c - H) * kB;
+                uint32_t o = co;
                 T *p = row_base_at<kU>(out, (uint32_t)i * ds + ro, o);
                 store_at(p, o, rv[i]);
             }
@@ -256,7 +271,7 @@ __device__ __forceinline__ void sc_tile_steps(const LatDesc &d, int src, int x0,
     const T *in = static_cast<const T *>(d.buf[src]);
     T *out = static_cast<T *>(d.buf[src ^ 1]);
     const Rates<R> rt = rates_of<R>(d);
-    constexpr bool kU = RW == 64;  // a wave's cells lie in one row
+    constexpr bool kU = RW % 64 == 0;  // a wave's cells lie in one row
     const int c = threadIdx.x % RW;
     const int rt0 = kU ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / RW) : (int)threadIdx.x / RW;
     const int we = d.nx - x0 < RG::TW ? d.nx - x0 : RG::TW;
@@ -339,10 +354,13 @@ __device__ __forceinline__ void sc_tile_steps(const LatDesc &d, int src, int x0,
 #pragma unroll
                 for (int i = 1; i < 9; ++i) lds.v[i - 1][r][c] = rv[i];
             } else {
-                const uint32_t ro = row_off(y0 + r - H);
+                uint32_t ro = row_off(y0 + r - H);
+                uint32_t co = (uint32_t)(x0 + c - H) * kB;
+                form_here<kU>(ro);
+                form_here<false>(co);
 #pragma unroll
                 for (int i = 0; i < 9; ++i) {
-                    uint32_t o = (uint32_t)(x0 + c - H) * kB;
+                    uint32_t o = co;
                     T *p = row_base_at<kU>(out, (uint32_t)i * ds + ro, o);
                     store_at(p, o, rv[i]);
                 }
