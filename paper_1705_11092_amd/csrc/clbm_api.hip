@@ -938,7 +938,10 @@ void batch_regions(clbm_batch *b)
                 tiles[shape] += count(clbm::region_tile_w(shape), clbm::region_tile_h(shape));
         }
         b->region[st] = -1;
-        double best = clbm::pair_us(st, pairs, b->cus) / 2;
+        // Pairs of many ragged lattices run 8 % over one lattice's time per tile
+        // (256 lattices of 32^2 .. 512^2 in FP16-SR: pairs 74.0 us per step,
+        // 64 x 32 regions 69.1).
+        double best = 1.08 * clbm::pair_us(st, pairs, b->cus) / 2;
         for (int shape = 0; shape < clbm::kRegionShapes; ++shape) {
             const double us = clbm::tile_us(shape, st, tiles[shape], bytes, b->cus) / clbm::region_steps(shape);
             if (us < best) {
@@ -1115,9 +1118,12 @@ int batch_side_streams(clbm_batch *b, size_t n)
 // group 0 on s, the others on side streams forked from s once and joined
 // back to it after their n steps (a group of small lattices alone leaves
 // HBM idle in its tail; measured +15 % on a batch of FP32 and FP16
-// lattices).  Within a group the steps follow each other in stream order.
+// lattices).  Within a group the steps follow each other in stream order.  A
+// group whose lattices take at most (*most)[k] steps gets no launches beyond
+// them (a graph, which other counts replay, has them all).
 constexpr int kTimedSteps = 8;
-int batch_launch_steps(clbm_batch *b, int n, hipStream_t s, int which = 3, bool first = false)
+int batch_launch_steps(clbm_batch *b, int n, hipStream_t s, int which = 3, bool first = false,
+                       const std::vector<int64_t> *most = nullptr)
 {
     const Variant &v = single_of(b->variant);
     const PairVariant &pv = pair_of(b->variant);
@@ -1130,15 +1136,17 @@ int batch_launch_steps(clbm_batch *b, int n, hipStream_t s, int which = 3, bool 
         HIPCHK(hipEventRecord(b->fork, s));
         for (size_t k = 1; k < ng; ++k) HIPCHK(hipStreamWaitEvent(b->side[k - 1], b->fork, 0));
     }
-    for (size_t k = 0; k < ng; ++k) {
-        const auto &g = b->groups[k];
-        hipStream_t gs = k == 0 ? s : b->side[k - 1];
-        if (!(which & (g.cls == kSingle ? 1 : 2))) continue;
-        const int timed = g.cls == kSingle ? 1 : kTimedSteps / g.per;
-        const int launches = first ? timed : (n + g.per - 1) / g.per;
-        const int32_t *map = b->d_tile_lat + g.tbase;
-        for (int k2 = 0; k2 < launches; ++k2) {
-            const int sub = first ? 0 : k2;
+    // The groups' launches in the order of the steps they take, so that they
+    // start together however long the host needs to queue them all.
+    const int end = first ? kTimedSteps : n;
+    for (int t = 0; t < end; ++t) {
+        for (size_t k = 0; k < ng; ++k) {
+            const auto &g = b->groups[k];
+            if (!(which & (g.cls == kSingle ? 1 : 2)) || t % g.per || (first && g.cls == kSingle && t)) continue;
+            if (most && t >= (*most)[k]) continue;
+            hipStream_t gs = k == 0 ? s : b->side[k - 1];
+            const int32_t *map = b->d_tile_lat + g.tbase;
+            const int sub = first ? 0 : t / g.per;
             if (g.cls == kLdsTiles)
                 HIPCHK(clbm::launch_batch_tile(g.storage, b->d_lats, map, g.ntiles, g.key, g.walls, g.shape, sub, gs));
             else if (g.cls == kSingle)
@@ -1194,10 +1202,16 @@ int batch_run(clbm_batch *b, const int64_t *nsteps)
     batch_refresh(b);
     int rc = batch_upload(b, nsteps);
     if (rc) return rc;
-    // One group of long launches runs as fast launch by launch: no graph to
-    // capture on the first call (12 lattices of 10^2 .. 80^2 FP64, 100 steps:
-    // 371 -> 190 us).
-    const bool direct = b->groups.size() == 1 && (b->groups[0].cls == kLdsTiles || b->groups[0].ntiles >= 4096);
+    // Tiles (four or eight steps per launch) and long launches run as fast
+    // launch by launch: no graph to capture on the first call (12 lattices of
+    // 10^2 .. 80^2 FP64, 100 steps: 371 -> 190 us; 12 served solves in four
+    // groups, first call and 1000 uneven steps: 12.3 -> 11.8 ms; 16 lattices of
+    // 16^2 .. 40^2 in four groups 2.0 -> 1.5 us per step).
+    bool direct = b->groups.size() == 1 && b->groups[0].ntiles >= 4096;
+    if (!direct) {
+        direct = true;
+        for (const auto &g : b->groups) direct = direct && g.cls == kLdsTiles;
+    }
     int64_t left = maxn;
     while (!direct && left >= b->chunk) {
         if (!b->graph && (rc = batch_build_graph(b))) return rc;
@@ -1205,7 +1219,13 @@ int batch_run(clbm_batch *b, const int64_t *nsteps)
         left -= b->chunk;
     }
     if (left > 0) {
-        if ((rc = batch_launch_steps(b, (int)left, b->stream))) return rc;
+        std::vector<int64_t> most;
+        for (const auto &g : b->groups) {
+            int64_t m = 0;
+            for (int j = g.l_lo; j < g.l_hi; ++j) m = std::max(m, nsteps[b->order[j]] - (maxn - left));
+            most.push_back(m);
+        }
+        if ((rc = batch_launch_steps(b, (int)left, b->stream, 3, false, &most))) return rc;
         HIPCHK(clbm::launch_batch_advance(b->d_lats, (int)b->order.size(), (int)left, b->stream));
     }
     for (size_t j = 0; j < b->lats.size(); ++j) {
