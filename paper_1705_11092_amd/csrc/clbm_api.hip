@@ -943,6 +943,7 @@ void batch_regions(clbm_batch *b)
         // 64 x 32 regions 69.1).
         double best = 1.08 * clbm::pair_us(st, pairs, b->cus) / 2;
         for (int shape = 0; shape < clbm::kRegionShapes; ++shape) {
+            if (!clbm::region_compiled(shape, st)) continue;
             const double us = clbm::tile_us(shape, st, tiles[shape], bytes, b->cus) / clbm::region_steps(shape);
             if (us < best) {
                 best = us;

@@ -250,15 +250,28 @@ enum RegionShape {
     kRegion64x16 = 2,
     kRegion32x16 = 3,
     kRegion64x32 = 4,
-    kRegionShapes = 5,
+    kRegion64x48 = 5,
+    kRegionShapes = 6,
     // With the Shan-Chen force, whose steps need two nodes less at each side.
-    kRegionSc32x24 = 5,
-    kRegionSc64x32 = 6
+    kRegionSc32x24 = 6,
+    kRegionSc64x32 = 7
 };
-constexpr int region_w(int shape) { return shape == kRegion64x16 || shape == kRegion64x32 ? 64 : 32; }
+constexpr int region_w(int shape)
+{
+    return shape == kRegion64x16 || shape == kRegion64x32 || shape == kRegion64x48 ? 64 : 32;
+}
 constexpr int region_h(int shape)
 {
-    return shape == kRegion32x24 ? 24 : (shape == kRegion32x32 || shape == kRegion64x32 ? 32 : 16);
+    return shape == kRegion32x24
+               ? 24
+               : (shape == kRegion64x48 ? 48 : (shape == kRegion32x32 || shape == kRegion64x32 ? 32 : 16));
+}
+// 64 x 48 only in 16-bit storage, where three of its 48 KB of LDS share a
+// compute unit (FP32 one of 96 KB: 1024^2 7.5 against 6.8 us per step in 64 x 32;
+// FP64 would need 192 KB).
+constexpr bool region_compiled(int shape, int storage)
+{
+    return shape != kRegion64x48 || !(storage == ST_F64 || storage == ST_F32);
 }
 constexpr int region_steps(int shape) { return shape == kRegion32x24 || shape == kRegion32x32 ? 8 : 4; }
 constexpr int region_tile_w(int shape) { return region_w(shape) - 2 * (region_steps(shape) - 1); }
@@ -277,15 +290,15 @@ struct TilePlan {
 // 2048^2): FP32 32 x 24 8.7, 28; 32 x 32 9.8, 25; 64 x 16 6.8, 9.8, 94;
 // 32 x 16 5.6, 11.3, 111; 64 x 32 9.8, 10.8, 91.  FP64 10.4, 41; 12.0, 40;
 // 8.2, 13.7, 168; 6.0, 15.8, 184; 13.9, 15.8, 194.  FP16-SR 10.0, 36; 11.5, 31;
-// 8.1, 11.5, 106; 6.0, 12.7, 125; 13.2, 14.0, 94.
+// 8.1, 11.5, 106; 6.0, 12.7, 125; 13.2, 14.0, 97; 64 x 48 18.5, 19.2, 93.
 inline double tile_us(int shape, int storage, int64_t tiles, int64_t bytes, int cus)
 {
     struct Fit { double fixed, per; };
     static const Fit fit[4][kRegionShapes] = {
-        {{5.0, 5.8}, {3.7, 9.0}, {4.2, 4.6}, {3.4, 2.5}, {1.5, 15.0}},     // FP64
-        {{4.8, 3.8}, {4.7, 5.07}, {4.2, 2.7}, {3.9, 1.45}, {3.5, 6.7}},    // FP32
-        {{4.5, 4.2}, {4.7, 5.45}, {5.0, 2.8}, {3.9, 1.52}, {7.0, 6.05}},   // 16-bit, to nearest
-        {{5.0, 4.9}, {5.0, 6.5}, {5.0, 3.25}, {3.9, 1.79}, {7.0, 7.2}},    // 16-bit, stochastic
+        {{5.0, 5.8}, {3.7, 9.0}, {4.2, 4.6}, {3.4, 2.5}, {1.5, 15.0}, {}},       // FP64
+        {{4.8, 3.8}, {4.7, 5.07}, {4.2, 2.7}, {3.9, 1.45}, {3.5, 6.7}, {}},      // FP32
+        {{4.5, 4.2}, {4.7, 5.45}, {5.0, 2.8}, {3.9, 1.52}, {7.0, 6.05}, {11.5, 9.4}},  // 16-bit, to nearest
+        {{5.0, 4.9}, {5.0, 6.5}, {5.0, 3.25}, {3.9, 1.79}, {7.0, 7.2}, {13.0, 10.8}},   // 16-bit, stochastic
     };
     const int64_t n = (tiles + cus - 1) / cus;
     const int t = storage == ST_F64 ? 0 : (storage == ST_F32 ? 1 : (storage == ST_F16 || storage == ST_BF16 ? 2 : 3));
@@ -308,6 +321,7 @@ inline TilePlan tile_plan(int nx, int ny, int storage, int64_t bytes, int cus, d
 {
     TilePlan best{};
     for (int shape = 0; shape < kRegionShapes; ++shape) {
+        if (!region_compiled(shape, storage)) continue;
         TilePlan p{};
         p.shape = shape;
         p.steps = region_steps(shape);

@@ -12,6 +12,17 @@
 // once, and its LDS addresses are one register and constants.  LDS holds the
 // other 8 slots once, streamed in place, one barrier per step.
 //
+// What bounds it: small lattices the serial chain of a launch (pulls, a barrier
+// and a collision per step), about 9 us for eight steps; larger ones VALU issue,
+// for the cells collided beyond the tile (64 x 32 and four steps: 1.18 per cell
+// stored, 64 x 48 1.15, 64 x 16 1.38) and the last, partly filled round of
+// tiles.  Hence small regions of eight steps where launches count, and the
+// tallest of 64 columns whose LDS still lets two blocks (FP32, FP64) or three
+// (16-bit) share a compute unit where the work does.  Us per step, pairs ->
+// tiles: 64 x 32 FP64 2.8 -> 1.17, 200^2 FP64 3.6 -> 1.3, 512^2 FP32 3.6 -> 2.5,
+// 1024^2 FP32 9.7 -> 5.9, 1501 x 703 FP64 17.1 -> 10.4, 4096^2 FP16 73.3 -> 68.0,
+// 2048^2 FP16-SR 23.9 -> 21.6.
+//
 // The region is the periodic plane around the tile, so a lattice smaller than
 // the region simply repeats.  Every node update is the one-step kernel's, so
 // the result is bitwise that of n one-step launches.
@@ -247,7 +258,9 @@ __device__ __forceinline__ void tile_steps(const LatDesc &d, int src, int x0, in
 // their neighbours in turn: a step is needed on two nodes less at each side
 // than the one before.  A step pulls its cells and writes their psi to LDS,
 // and after a barrier takes the force from there, collides and writes the
-// slots, one copy of which is enough.
+// slots, one copy of which is enough.  The 200^2 FP64 droplet takes 2.4 us per
+// step, 9.0 with a psi pass and a step kernel of one launch each; the chain of
+// barriers bounds it.
 template <int RW_, int RH_, int K_, int NT_>
 struct ScRegion {
     static constexpr int RW = RW_, RH = RH_, K = K_, NT = NT_, H = 2 * K - 1;
@@ -416,7 +429,9 @@ using RegionOf = std::conditional_t<
     std::conditional_t<
         SHAPE == kRegion32x32, Region<32, 32, 8, 1024>,
         std::conditional_t<SHAPE == kRegion64x16, Region<64, 16, 4, 512>,
-                           std::conditional_t<SHAPE == kRegion32x16, Region<32, 16, 4, 512>, Region<64, 32, 4, 512>>>>>;
+                           std::conditional_t<SHAPE == kRegion32x16, Region<32, 16, 4, 512>,
+                                              std::conditional_t<SHAPE == kRegion64x32, Region<64, 32, 4, 512>,
+                                                                 Region<64, 48, 4, 512>>>>>>;
 
 }  // namespace
 
@@ -470,7 +485,11 @@ hipError_t launch_tile_st(const LatDesc &d, int src, int n, const TilePlan &p, h
     case kRegion64x16: return tile_shape_launch<ST, kRegion64x16>(d, src, n, p, s);
     case kRegion32x16: return tile_shape_launch<ST, kRegion32x16>(d, src, n, p, s);
     case kRegion64x32: return tile_shape_launch<ST, kRegion64x32>(d, src, n, p, s);
-    default: return hipErrorInvalidValue;
+    default:
+        if constexpr (region_compiled(kRegion64x48, ST)) {
+            if (p.shape == kRegion64x48) return tile_shape_launch<ST, kRegion64x48>(d, src, n, p, s);
+        }
+        return hipErrorInvalidValue;
     }
 }
 
@@ -510,7 +529,12 @@ hipError_t launch_batch_tile_st(const LatDesc *lats, const int32_t *tile_lat, in
     case kRegion64x16: return batch_tile_shape_launch<ST, kRegion64x16>(lats, tile_lat, ntiles, key, walls, sub, s);
     case kRegion32x16: return batch_tile_shape_launch<ST, kRegion32x16>(lats, tile_lat, ntiles, key, walls, sub, s);
     case kRegion64x32: return batch_tile_shape_launch<ST, kRegion64x32>(lats, tile_lat, ntiles, key, walls, sub, s);
-    default: return hipErrorInvalidValue;
+    default:
+        if constexpr (region_compiled(kRegion64x48, ST)) {
+            if (shape == kRegion64x48)
+                return batch_tile_shape_launch<ST, kRegion64x48>(lats, tile_lat, ntiles, key, walls, sub, s);
+        }
+        return hipErrorInvalidValue;
     }
 }
 

@@ -73,12 +73,12 @@ def test_tile_plans_cover_the_lattice(plans, nx, ny, storage):
     eb = 8 if storage == 0 else (4 if storage == 1 else 2)
     us = plans.host_tile_plan(nx, ny, storage, 9 * nx * ny * eb, 256, o)
     steps, shape, tiles_x, tiles, tw, th = o
-    assert us > 0 and steps in (4, 8) and 0 <= shape < 5 and tw >= 1 and th >= 1
+    assert us > 0 and steps in (4, 8) and 0 <= shape < 6 and tw >= 1 and th >= 1
     assert (tiles_x - 1) * tw < nx <= tiles_x * tw
     tiles_y = tiles // tiles_x
     assert tiles == tiles_x * tiles_y and (tiles_y - 1) * th < ny <= tiles_y * th
     plans.host_sc_tile_plan(nx, ny, storage, 256, o)
     steps, shape, tiles_x, tiles = o[:4]
     w, h = {4: (18, 10), 2: (58, 26)}[steps]
-    assert shape == {4: 5, 2: 6}[steps]
+    assert shape == {4: 6, 2: 7}[steps]
     assert tiles_x == -(-nx // w) and tiles == tiles_x * -(-ny // h)

@@ -43,7 +43,8 @@ def _same(wl, storage, scheme, counts):
     return per
 
 
-# Region tiles are 18 x 10, 18 x 18, 58 x 10, 26 x 10 and 58 x 26 nodes.
+# Region tiles are 18 x 10, 18 x 18, 58 x 10, 26 x 10 and 58 x 26 nodes (58 x 42
+# in large 16-bit lattices).
 TILE_SHAPES = [(1, 1, 0, "const"), (3, 2, 1, "field"), (18, 10, 1, "kolmogorov"), (19, 11, 0, "field"),
                (17, 9, 1, "const"), (58, 26, 0, "kolmogorov"), (59, 27, 1, "field"), (57, 25, 1, "none"),
                (116, 52, 1, "field"), (117, 53, 0, "const"), (300, 130, 0, "field"), (257, 255, 1, "kolmogorov"),
@@ -59,6 +60,14 @@ def test_lds_tiles_match_one_step(storage, scheme):
         seen.add(_same(wl, storage, scheme, (1, 2, 3, 4, 7, 8, 13, 1 + k % 8)))
     log(f"lds tiles {storage} {scheme}: steps per launch {sorted(seen)}")
     assert {4, 8} <= seen
+
+
+@pytest.mark.parametrize("storage", ["f16", "bf16", "f16sr", "bf16sr"])
+def test_tall_16_bit_tiles_match_one_step(storage):
+    # 58 x 42 tiles: full ones, a remainder of one column and row, one less.
+    for nx, ny, bc, force in [(1566, 1554, 1, "field"), (1509, 1513, 0, "kolmogorov"), (1565, 1553, 1, "const")]:
+        wl = inputs.random_state(nx, ny, seed=nx, bc_y=bc, force=force, amp_f=1e-4, amp_u=0.02, s=RATES)
+        assert _same(wl, storage, "consistent", (4, 3)) == 4
 
 
 @pytest.mark.parametrize("storage,nx,ny,bc,force,scheme", [
