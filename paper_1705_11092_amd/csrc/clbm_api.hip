@@ -1114,14 +1114,13 @@ int batch_side_streams(clbm_batch *b, size_t n)
 // the groups that step singly (1) or in fused steps (2); with `first`, only
 // the first launch of every group, as often as makes kTimedSteps fused steps
 // (the autotuner's timed launches, which must not read what they wrote).  The
-// groups
-// touch disjoint lattices, so with more than one they run concurrently:
-// group 0 on s, the others on side streams forked from s once and joined
-// back to it after their n steps (a group of small lattices alone leaves
-// HBM idle in its tail; measured +15 % on a batch of FP32 and FP16
-// lattices).  Within a group the steps follow each other in stream order.  A
-// group whose lattices take at most (*most)[k] steps gets no launches beyond
-// them (a graph, which other counts replay, has them all).
+// groups touch disjoint lattices, so with more than one they run concurrently:
+// group 0 on s, the others on side streams forked from s once and joined back
+// to it after their n steps (a group of small lattices alone leaves HBM idle
+// in its tail; measured +15 % on a batch of FP32 and FP16 lattices).  Within a
+// group the steps follow each other in stream order.  A group whose lattices
+// take at most (*most)[k] steps gets no launches beyond them (a graph, which
+// other counts replay, has them all).
 constexpr int kTimedSteps = 8;
 int batch_launch_steps(clbm_batch *b, int n, hipStream_t s, int which = 3, bool first = false,
                        const std::vector<int64_t> *most = nullptr)

@@ -197,8 +197,9 @@ constexpr int sweep_max_vec(int storage, int force_mode, int bc_y)
 // average, 0.230 us per level and column of a lane in FP32, 0.262 in FP64; one
 // wave per SIMD hides its latencies to 72 % of the issue rate, two to 92 %), or
 // memory at 4.8 TB/s (3.3 with one wave per SIMD; each chunk reads 2 K rows and
-// each strip 2 halo lanes beyond its own), plus 3 us of launch.  Within 10 % of what 1024^2, 2048^2 and
-// 4096^2 lattices take (FP64 48, 154, 532 us; FP32 31, 95, 300).
+// each strip 2 halo lanes beyond its own), plus 3 us of launch.  Within 10 % of
+// what 1024^2, 2048^2 and 4096^2 lattices take (FP64 48, 154, 500 us; FP32 31, 95,
+// 295).
 inline double sweep_us(int64_t nodes, int eb, int simds, int vec, int halo, int rows, int64_t units)
 {
     const int64_t n = (units + simds - 1) / simds;  // waves on the busiest SIMD
