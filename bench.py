@@ -102,6 +102,15 @@ def measured_valu(storage: str, n_nodes: int):
     return t
 
 
+def kernel_label(launch):
+    """The kernel of a launch as Lattice.next_launch names it."""
+    kind, steps, w, h = launch
+    return {"step": "k_step", "pair": "k_step2 (two fused steps per launch)",
+            "tiles": f"k_tile ({steps} fused steps per launch in {w} x {h} regions)",
+            "sweep": f"k_sweep ({steps} fused steps per launch, {w} columns per lane)",
+            "resident": f"k_resident ({steps} steps per launch)"}[kind]
+
+
 def run_gpu(n: int, storage: str, steps: int, warmup: int, inplace: bool = False,
             pairs: bool = True, reps: int = 1):
     """Time `reps` repetitions of exactly `steps` steps each (HIP events on
@@ -119,6 +128,7 @@ def run_gpu(n: int, storage: str, steps: int, warmup: int, inplace: bool = False
     lat.step_pairs = None if pairs else False  # the default fused steps, or singly
     run_gpu.pairs = lat.step_pairs
     run_gpu.per_launch = lat.steps_per_launch
+    run_gpu.launch = lat.next_launch(steps)
     stream = lat.stream
     lat.step(warmup)
     torch.cuda.synchronize()
@@ -477,8 +487,7 @@ def main():
                          "clock_ghz_under_counters": valu.get("clock_ghz")}
     bound = max(limits, key=lambda k: limits[k]["frac"])
     roof = {"bound": bound, **{k: v for k, v in limits[bound].items()},
-            "kernel": {4: "k_sweep (four fused steps per launch)", 2: "k_step2 (two fused steps per launch)",
-                       1: "k_step"}.get(steps_per_launch, f"{steps_per_launch} fused steps per launch"),
+            "kernel": kernel_label(run_gpu.launch),
             "ms_per_launch": round(ms_launch, 5), "limits": limits}
     if pairs:
         # The per-update byte model (every node update reads and writes the

@@ -279,6 +279,24 @@ int clbm_set_occupancy(clbm_handle *h, int32_t blocks_per_cu);
 int clbm_set_step_pairs(clbm_handle *h, int32_t enable);
 int32_t clbm_get_step_pairs(const clbm_handle *h);
 int32_t clbm_steps_per_launch(const clbm_handle *h);
+
+/* The kernel a launch runs: one step (STEP), two fused steps in LDS (PAIR), up
+ * to four or eight in LDS tiles (TILES), four in registers (SWEEP) or many in
+ * one resident block (RESIDENT). */
+typedef enum {
+    CLBM_LAUNCH_STEP = 0,
+    CLBM_LAUNCH_PAIR = 1,
+    CLBM_LAUNCH_TILES = 2,
+    CLBM_LAUNCH_SWEEP = 3,
+    CLBM_LAUNCH_RESIDENT = 4
+} clbm_launch_kind;
+
+/* The launch that clbm_step(h, nsteps) would begin with: launch[0] its kernel
+ * (clbm_launch_kind), launch[1] its steps, launch[2] and launch[3] the width
+ * and height of its tiles' regions (TILES) or its columns per lane and rows
+ * per wave (SWEEP), otherwise 0.  Reads the handle only.
+ * Errors: CLBM_EINVAL (NULL, nsteps < 1). */
+int clbm_next_launch(const clbm_handle *h, int64_t nsteps, int32_t *launch);
 int32_t clbm_get_occupancy(const clbm_handle *h); /* -1 for NULL */
 
 /* Small lattices step in a resident kernel: one block of 1024 threads that

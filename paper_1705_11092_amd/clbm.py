@@ -22,6 +22,7 @@ BC = {"periodic": 0, "bounceback": 1}
 STREAM_TWO_BUFFERS, STREAM_IN_PLACE = 0, 1
 FORCE = {"none": 0, "const": 1, "kolmogorov": 2, "field": 3, "shan_chen": 4}
 SCHEME = {"consistent": 0, "guo_lbl": 1, "premnath": 2}
+LAUNCHES = ("step", "pair", "tiles", "sweep", "resident")
 
 CLBM_OK, CLBM_EINVAL, CLBM_EHIP, CLBM_ESTATE, CLBM_ENONFINITE = 0, -1, -2, -3, -4
 
@@ -64,6 +65,7 @@ def _load():
         "clbm_set_step_pairs": (ctypes.c_int, [vp, i32]),
         "clbm_get_step_pairs": (i32, [vp]),
         "clbm_steps_per_launch": (i32, [vp]),
+        "clbm_next_launch": (ctypes.c_int, [vp, i64, ctypes.POINTER(i32)]),
         "clbm_get_occupancy": (i32, [vp]),
         "clbm_step_count": (i64, [vp]),
         "clbm_moments": (ctypes.c_int, [vp, vp, vp, vp, dp]),
@@ -99,7 +101,7 @@ EXPORTED = (
     "clbm_step", "clbm_step_count", "clbm_moments", "clbm_moments_noalloc", "clbm_error_norms",
     "clbm_get_populations", "clbm_set_populations", "clbm_set_graph_steps",
     "clbm_set_occupancy", "clbm_get_occupancy", "clbm_set_resident_limit",
-    "clbm_set_step_pairs", "clbm_get_step_pairs", "clbm_steps_per_launch",
+    "clbm_set_step_pairs", "clbm_get_step_pairs", "clbm_steps_per_launch", "clbm_next_launch",
     "clbm_last_error", "clbm_nonslip_s3", "clbm_s_from_nu", "clbm_batch_create",
     "clbm_batch_step", "clbm_batch_step_each", "clbm_batch_autotune",
     "clbm_batch_variant_count", "clbm_batch_set_variant", "clbm_batch_get_variant",
@@ -246,6 +248,15 @@ class Lattice:
     def steps_per_launch(self) -> int:
         """Most steps of one launch (1, 2, 4 or 8)."""
         return int(lib.clbm_steps_per_launch(self._h))
+
+    def next_launch(self, n: int):
+        """The launch step(n) would begin with: its kernel ("step", "pair",
+        "tiles", "sweep" or "resident"), its steps, and two sizes (the regions'
+        width and height for "tiles", columns per lane and rows per wave for
+        "sweep", otherwise 0)."""
+        out = (ctypes.c_int32 * 4)()
+        _check(lib.clbm_next_launch(self._h, int(n), out))
+        return (LAUNCHES[out[0]], out[1], out[2], out[3])
 
     @property
     def occupancy(self) -> int:

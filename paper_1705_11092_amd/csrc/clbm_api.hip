@@ -364,25 +364,40 @@ int graph_steps_of(const clbm_handle *h)
     return use_tiles(h) || use_sweeps(h) || (int64_t)h->d.nx * h->d.ny > kGraphMaxNodes ? 0 : kGraphSteps;
 }
 
-// The next launch of a run with `left` steps to go, from state `parity`: as
-// many fused steps as the lattice takes.  Each launch flips the buffer or
-// phase.
+// Whether a run of n steps goes to the resident kernel.
+bool use_resident(const clbm_handle *h, int64_t n)
+{
+    const int rvec = h->d.storage == CLBM_F64 ? 2 : 4;
+    const int64_t groups = (int64_t)h->d.ny * (h->d.pitch / rvec);
+    return n >= 2 && h->d.force_mode != clbm::FM_SC && groups <= h->resident_max;
+}
+constexpr int kResidentSteps = 4096;  // most steps of one resident launch
+
+// The next launch of a run with `left` steps to go: its kernel, and as many
+// steps as that takes.
+struct Launch {
+    clbm_launch_kind kind;
+    int steps;
+};
+Launch next_launch(const clbm_handle *h, int64_t left)
+{
+    if (use_tiles(h)) return {CLBM_LAUNCH_TILES, (int)std::min<int64_t>(left, h->tile.steps)};
+    if (left >= clbm::kSweepSteps && use_sweeps(h)) return {CLBM_LAUNCH_SWEEP, clbm::kSweepSteps};
+    if (left >= 2 && use_pairs(h)) return {CLBM_LAUNCH_PAIR, 2};
+    return {CLBM_LAUNCH_STEP, 1};
+}
+
+// That launch from state `parity`.  Each launch flips the buffer or phase.
 hipError_t launch_next(const clbm_handle *h, int parity, int64_t left, hipStream_t s, int *taken)
 {
-    if (use_tiles(h)) {
-        *taken = (int)std::min<int64_t>(left, h->tile.steps);
-        return clbm::launch_tile(h->d, parity, *taken, h->tile, s);
+    const Launch l = next_launch(h, left);
+    *taken = l.steps;
+    switch (l.kind) {
+    case CLBM_LAUNCH_TILES: return clbm::launch_tile(h->d, parity, l.steps, h->tile, s);
+    case CLBM_LAUNCH_SWEEP: return clbm::launch_sweep(h->d, parity, h->sweep, s);
+    case CLBM_LAUNCH_PAIR: return clbm::launch_step2(h->d, parity, s);
+    default: return clbm::launch_step(h->d, parity, h->vec, step_lds(h, parity), s);
     }
-    if (left >= clbm::kSweepSteps && use_sweeps(h)) {
-        *taken = clbm::kSweepSteps;
-        return clbm::launch_sweep(h->d, parity, h->sweep, s);
-    }
-    if (left >= 2 && use_pairs(h)) {
-        *taken = 2;
-        return clbm::launch_step2(h->d, parity, s);
-    }
-    *taken = 1;
-    return clbm::launch_step(h->d, parity, h->vec, step_lds(h, parity), s);
 }
 
 int build_graph(clbm_handle *h, int parity)
@@ -611,12 +626,10 @@ int clbm_step(clbm_handle *h, int64_t nsteps)
     int rc = need_ready(h);
     if (rc) return rc;
     if (nsteps < 0) return fail(CLBM_EINVAL, "nsteps must be >= 0");
-    const int rvec = h->d.storage == CLBM_F64 ? 2 : 4;
-    const int64_t groups = (int64_t)h->d.ny * (h->d.pitch / rvec);
-    if (nsteps >= 2 && h->d.force_mode != clbm::FM_SC && groups <= h->resident_max) {
+    if (use_resident(h, nsteps)) {
         // A small lattice: many steps per launch in one resident block.
         for (int64_t left = nsteps; left > 0;) {
-            const int n = (int)std::min<int64_t>(left, 4096);
+            const int n = (int)std::min<int64_t>(left, kResidentSteps);
             HIPCHK(clbm::launch_resident(h->d, h->parity, n, h->stream));
             h->parity = (h->parity + n) & 1;
             left -= n;
@@ -770,6 +783,27 @@ int32_t clbm_steps_per_launch(const clbm_handle *h)
     if (use_tiles(h)) return h->tile.steps;
     if (use_sweeps(h)) return clbm::kSweepSteps;
     return use_pairs(h) ? 2 : 1;
+}
+
+int clbm_next_launch(const clbm_handle *h, int64_t nsteps, int32_t *launch)
+{
+    g_err.clear();
+    if (!h || !launch) return fail(CLBM_EINVAL, "handle and launch must not be NULL");
+    if (nsteps < 1) return fail(CLBM_EINVAL, "nsteps must be >= 1");
+    const Launch l = use_resident(h, nsteps)
+                         ? Launch{CLBM_LAUNCH_RESIDENT, (int)std::min<int64_t>(nsteps, kResidentSteps)}
+                         : next_launch(h, nsteps);
+    launch[0] = l.kind;
+    launch[1] = l.steps;
+    launch[2] = launch[3] = 0;
+    if (l.kind == CLBM_LAUNCH_TILES) {
+        launch[2] = clbm::region_w(h->tile.shape);
+        launch[3] = clbm::region_h(h->tile.shape);
+    } else if (l.kind == CLBM_LAUNCH_SWEEP) {
+        launch[2] = h->sweep.vec;
+        launch[3] = h->sweep.rows;
+    }
+    return CLBM_OK;
 }
 
 int clbm_set_occupancy(clbm_handle *h, int32_t blocks_per_cu)

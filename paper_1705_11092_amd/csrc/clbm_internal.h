@@ -259,13 +259,19 @@ enum RegionShape {
 };
 constexpr int region_w(int shape)
 {
-    return shape == kRegion64x16 || shape == kRegion64x32 || shape == kRegion64x48 ? 64 : 32;
+    return shape == kRegion64x16 || shape == kRegion64x32 || shape == kRegion64x48 || shape == kRegionSc64x32 ? 64 : 32;
 }
 constexpr int region_h(int shape)
 {
-    return shape == kRegion32x24
-               ? 24
-               : (shape == kRegion64x48 ? 48 : (shape == kRegion32x32 || shape == kRegion64x32 ? 32 : 16));
+    switch (shape) {
+    case kRegion32x24:
+    case kRegionSc32x24: return 24;
+    case kRegion32x32:
+    case kRegion64x32:
+    case kRegionSc64x32: return 32;
+    case kRegion64x48: return 48;
+    default: return 16;
+    }
 }
 // 64 x 48 only in 16-bit storage, where three of its 48 KB of LDS share a
 // compute unit (FP32 one of 96 KB: 1024^2 7.5 against 6.8 us per step in 64 x 32;
