@@ -305,11 +305,12 @@ int32_t clbm_get_occupancy(const clbm_handle *h); /* -1 for NULL */
  * otherwise bound by launch overhead).  It applies when the lattice has at
  * most max_groups groups of nodes (ny x padded nx / nodes per thread, 2
  * nodes per thread for FP64 and 4 otherwise), nsteps >= 2 and the force is
- * not Shan-Chen.  The default is 512 for in-place lattices, the measured
- * break-even on MI355X (one compute unit does all the work, so larger
- * lattices step faster as graphed launches), and 0 for two-buffer ones, which
- * step faster in LDS tiles.  0 disables it; the limit is at most 2^20.  Results are
- * bitwise the same either way.  Errors: CLBM_EINVAL. */
+ * not Shan-Chen.  The default is 512 where the lattice steps singly or in pairs
+ * (in place, or set so with clbm_set_step_pairs), the measured break-even on
+ * MI355X (one compute unit does all the work, so larger lattices step faster as
+ * graphed launches), and 0 where it steps in LDS tiles, which are faster.  0
+ * disables it; the limit is at most 2^20.  Results are bitwise the same either
+ * way.  Errors: CLBM_EINVAL. */
 int clbm_set_resident_limit(clbm_handle *h, int64_t max_groups);
 
 /* Message for the last failing call on this thread ("" if none). */

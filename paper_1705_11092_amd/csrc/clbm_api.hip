@@ -267,7 +267,7 @@ struct clbm_handle {
     double *partials = nullptr;  // per-block FP64 partial sums (stream-ordered)
     int vec = 4;
     int occ = 0;                 // blocks per compute unit of the step kernel (0: no cap)
-    int64_t resident_max = 0;    // resident kernel up to this many groups
+    int64_t resident_max = -1;   // resident kernel up to this many groups, -1 the default (use_resident)
     size_t lds = 0;              // dynamic LDS per block that enforces occ
     size_t lds0 = 0;             // the same for in-place phase-0 steps
     int pairs = -1;              // two fused steps per launch: 1 where supported,
@@ -364,12 +364,16 @@ int graph_steps_of(const clbm_handle *h)
     return use_tiles(h) || use_sweeps(h) || (int64_t)h->d.nx * h->d.ny > kGraphMaxNodes ? 0 : kGraphSteps;
 }
 
-// Whether a run of n steps goes to the resident kernel.
+// Whether a run of n steps goes to the resident kernel.  By default tiny
+// lattices that would otherwise step singly or in pairs do (16 x 16 FP32, us per
+// step: resident 1.5, pairs 3.0, single steps 2.8); the tile kernel is faster
+// (1.0).
 bool use_resident(const clbm_handle *h, int64_t n)
 {
     const int rvec = h->d.storage == CLBM_F64 ? 2 : 4;
     const int64_t groups = (int64_t)h->d.ny * (h->d.pitch / rvec);
-    return n >= 2 && h->d.force_mode != clbm::FM_SC && groups <= h->resident_max;
+    const int64_t most = h->resident_max >= 0 ? h->resident_max : (use_tiles(h) ? 0 : clbm::kResidentMaxGroups);
+    return n >= 2 && h->d.force_mode != clbm::FM_SC && groups <= most;
 }
 constexpr int kResidentSteps = 4096;  // most steps of one resident launch
 
@@ -496,9 +500,6 @@ int clbm_create(const clbm_config *cfg, clbm_handle **out)
     h->lds = lds_for_occupancy(h->occ);
     h->cus = compute_units();
     plan_fused(h);
-    // The tile kernel steps small lattices faster than the resident one
-    // (16 x 16 FP32 1.0 against 1.7 us per step); it needs two buffers.
-    h->resident_max = h->tile.steps ? 0 : clbm::kResidentMaxGroups;
     h->lds0 = inplace ? lds_for_occupancy(default_occupancy(cfg->storage, 2 * need, true, 0)) : h->lds;
 
     reap_retired();

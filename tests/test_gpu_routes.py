@@ -22,3 +22,30 @@ def test_bench_names_the_kernel_that_runs():
         assert bench.kernel_label(bench.run_gpu.launch).startswith(kernel + " (")
     bench.run_gpu(512, "f16", 8, 0, pairs=False)
     assert bench.kernel_label(bench.run_gpu.launch) == "k_step"
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16"])
+def test_resident_kernel_follows_what_the_lattice_steps_with(storage):
+    # Tiny lattices that step singly or in pairs run in the resident block;
+    # those that step in LDS tiles do not, unless a limit asks for it.
+    for pairs in (False, True):
+        lat = _lattice(16, 16, storage)
+        assert lat.next_launch(10)[:2] == ("tiles", 8)
+        lat.step_pairs = pairs
+        assert lat.next_launch(10)[:2] == ("resident", 10)
+        assert lat.next_launch(1)[:2] == ("step", 1)
+        lat.step_pairs = None
+        assert lat.next_launch(10)[:2] == ("tiles", 8)
+        lat.set_resident_limit(1 << 20)
+        assert lat.next_launch(10)[:2] == ("resident", 10)
+        lat.step_pairs = pairs
+        lat.set_resident_limit(0)
+        assert lat.next_launch(10)[0] == ("pair" if pairs else "step")
+        lat.close()
+    lat = _lattice(16, 16, storage, inplace=True)
+    assert lat.next_launch(10)[:2] == ("resident", 10)
+    lat.close()
+    big = _lattice(100, 100, storage)
+    big.step_pairs = False
+    assert big.next_launch(10)[0] == "step"
+    big.close()
