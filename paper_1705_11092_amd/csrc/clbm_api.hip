@@ -275,6 +275,7 @@ struct clbm_handle {
     int cus = 256;               // compute units of the device
     clbm::SweepPlan sweep{};     // four fused steps per launch by default (vec 0: never)
     clbm::TilePlan tile{};       // up to tile.steps fused steps per launch by default (0: never)
+    clbm::ShortRun brief{};      // what the last one or two steps take under that plan (tiles_take)
     int graph_steps = -1;        // steps per graph, 0 none, -1 the default (graph_steps_of)
     int graph_launches = 0;      // launches of one graph: each flips the parity
     hipGraphExec_t graph[2] = {nullptr, nullptr};
@@ -313,6 +314,12 @@ bool tile_offsets_fit(const LatDesc &d)
     return clbm_buffer_bytes(d.nx, d.ny, d.storage) < (size_t)1 << 32;
 }
 
+// Tiles of w x h nodes that cover the lattice.
+int64_t tile_count(const LatDesc &d, int w, int h)
+{
+    return (int64_t)((d.nx + w - 1) / w) * ((d.ny + h - 1) / h);
+}
+
 // The plan of the fused kernels for the lattice and its force (at creation
 // and when the force changes): the tile kernel, the sweep kernel or pairs,
 // whichever model gives the least time per step.  Tiles and sweeps cross near
@@ -340,9 +347,12 @@ void plan_fused(clbm_handle *h)
             return;
         }
     }
-    const int64_t pair_tiles = (int64_t)((d.nx + 63) / 64) * ((d.ny + clbm::tile_h(0, d.storage) - 1) /
-                                                              clbm::tile_h(0, d.storage));
-    if (tile_offsets_fit(d) && us < clbm::pair_us(d.storage, pair_tiles, cus) / 2) h->tile = t;
+    const int64_t pair_tiles = tile_count(d, clbm::tile_w(clbm::kTile64x16), clbm::tile_h(clbm::kTile64x16, d.storage));
+    if (tile_offsets_fit(d) && us < clbm::pair_us(d.storage, pair_tiles, cus) / 2) {
+        h->tile = t;
+        h->brief = clbm::ShortRun{t.shape, d.storage, d.bc_y != 0, t.tiles, pair_tiles, nodes,
+                                  (int64_t)clbm_buffer_bytes(d.nx, d.ny, d.storage)};
+    }
 }
 
 // Whether steps go several per launch (the tile or the sweep kernel): by
@@ -385,7 +395,8 @@ struct Launch {
 };
 Launch next_launch(const clbm_handle *h, int64_t left)
 {
-    if (use_tiles(h)) return {CLBM_LAUNCH_TILES, (int)std::min<int64_t>(left, h->tile.steps)};
+    if (use_tiles(h) && (h->d.force_mode == clbm::FM_SC || clbm::tiles_take(left, h->brief, h->cus)))
+        return {CLBM_LAUNCH_TILES, (int)std::min<int64_t>(left, h->tile.steps)};
     if (left >= clbm::kSweepSteps && use_sweeps(h)) return {CLBM_LAUNCH_SWEEP, clbm::kSweepSteps};
     if (left >= 2 && use_pairs(h)) return {CLBM_LAUNCH_PAIR, 2};
     return {CLBM_LAUNCH_STEP, 1};
@@ -938,10 +949,7 @@ namespace {
 int pair_shape(int variant_shape, const clbm::LatDesc &d)
 {
     if (variant_shape != kShapePerLattice) return variant_shape;
-    auto tiles = [&](int shape) {
-        const int w = clbm::tile_w(shape), h = clbm::tile_h(shape, d.storage);
-        return (int64_t)((d.nx + w - 1) / w) * ((d.ny + h - 1) / h);
-    };
+    auto tiles = [&](int shape) { return tile_count(d, clbm::tile_w(shape), clbm::tile_h(shape, d.storage)); };
     return tiles(clbm::kTile32x32) < tiles(clbm::kTile64x16) ? clbm::kTile32x32 : clbm::kTile64x16;
 }
 
@@ -966,11 +974,10 @@ void batch_regions(clbm_batch *b)
         for (const auto *h : b->lats) {
             const LatDesc &d = h->d;
             if (d.storage != st || h->pairs >= 0 || !use_pairs(h)) continue;
-            auto count = [&](int w, int hh) { return (int64_t)((d.nx + w - 1) / w) * ((d.ny + hh - 1) / hh); };
-            pairs += count(64, clbm::tile_h(clbm::kTile64x16, st));
+            pairs += tile_count(d, clbm::tile_w(clbm::kTile64x16), clbm::tile_h(clbm::kTile64x16, st));
             bytes += (int64_t)clbm_buffer_bytes(d.nx, d.ny, st);
             for (int shape = 0; shape < clbm::kRegionShapes; ++shape)
-                tiles[shape] += count(clbm::region_tile_w(shape), clbm::region_tile_h(shape));
+                tiles[shape] += tile_count(d, clbm::region_tile_w(shape), clbm::region_tile_h(shape));
         }
         b->region[st] = -1;
         // Pairs of many ragged lattices run 8 % over one lattice's time per tile

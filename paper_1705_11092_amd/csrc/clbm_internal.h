@@ -346,6 +346,40 @@ inline TilePlan tile_plan(int nx, int ny, int storage, int64_t bytes, int cus, d
     return best;
 }
 
+// Whether the last one or two steps of a run go to the tile kernel like the
+// launches before them, or to the one-step kernel and the pair kernel.  A tile
+// launch of n steps takes about n / K of a full one, but stores pieces of lines
+// (58 columns and fewer), which costs memory a read of each: beyond the Infinity
+// Cache it never pays (us, tile launch against the other: FP64 1500^2 one step 66
+// / 57, two 73 / 67; FP16 4096^2 140 / 110, 170 / 153).  Within it the tile
+// kernel wins where it has work enough to cover its fixed part (FP64 1024^2 24 /
+// 30, 28 / 33; FP32 1500^2 25 / 31, 30 / 39; FP16 1500^2 17 / 19; but 512^2 FP64
+// 8.1 / 7.3, FP16 768^2 8.4 / 7.2), unless its tiles cover much more than the
+// lattice, or than the pairs' tiles do (16 x 20000 FP32 9.0 / 6.0 for one step,
+// 11.7 / 13.4 for two; 64 x 20003 17.7 / 17.9, 24.0 / 22.4); between walls 16-bit
+// tiles run at a lower occupancy (FP16 2048^2 36 / 35, 52 / 47).  Tiles of one
+// round are launch-bound: equal.  Three steps take one launch instead of two
+// (0.4 to 1.0 of their time).
+struct ShortRun {
+    int32_t shape, storage;
+    bool walls;
+    int64_t tiles, pair_tiles, nodes, bytes;  // bytes: one buffer of all the lattices
+};
+inline bool tiles_take(int64_t left, const ShortRun &r, int cus)
+{
+    if (left >= 3 || r.tiles <= cus) return true;
+    const int64_t mb = (int64_t)1 << 20, both = 2 * r.bytes;
+    if (both > 256 * mb) return false;
+    const double cells = (double)r.tiles * region_tile_w(r.shape) * region_tile_h(r.shape);
+    const double pair_cells = (double)r.pair_tiles * tile_w(kTile64x16) * tile_h(kTile64x16, r.storage);
+    double most = r.shape == kRegion32x16 ? 1.2 : 1.3;
+    if (r.storage == ST_F64) most = both >= 40 * mb ? 1.5 : 1.0;
+    const bool narrow = !(r.storage == ST_F64 || r.storage == ST_F32);  // 16-bit
+    if (left == 1) return (narrow ? !r.walls && both >= 64 * mb : both >= 40 * mb) && cells <= most * (double)r.nodes;
+    if (narrow && r.walls && both >= 32 * mb) most = 0.9;
+    return cells <= most * pair_cells;
+}
+
 // The plan of a Shan-Chen lattice: regions of 32 x 24 cells and four steps
 // (tiles of 18 x 10) or of 64 x 32 and two (58 x 26), whichever takes less
 // time per step.

@@ -49,3 +49,34 @@ def test_resident_kernel_follows_what_the_lattice_steps_with(storage):
     big.step_pairs = False
     assert big.next_launch(10)[0] == "step"
     big.close()
+
+
+@pytest.mark.parametrize("storage,nx,ny,bc,one,two", [
+    ("f64", 40, 30, 1, "tiles", "tiles"),       # one round of tiles
+    ("f64", 384, 380, 0, "step", "pair"),       # little work
+    ("f64", 1024, 1000, 1, "tiles", "tiles"),   # in the Infinity Cache
+    ("f64", 1450, 1460, 0, "step", "pair"),     # beyond it
+    ("f32", 512, 500, 1, "step", "tiles"),
+    ("f32", 1500, 1400, 0, "tiles", "tiles"),
+    ("f32", 16, 20000, 0, "step", "tiles"),     # tiles cover more than the lattice
+    ("f32", 64, 20003, 0, "step", "pair"),      # and more than the pairs' tiles
+    ("f16", 768, 760, 0, "step", "tiles"),
+    ("f16", 1500, 1490, 0, "tiles", "tiles"),
+    ("f16sr", 1500, 1490, 1, "step", "pair"),   # 16-bit between walls
+    ("bf16", 2800, 2750, 0, "step", "pair"),    # beyond the Infinity Cache
+])
+def test_last_steps_of_a_run_take_the_cheaper_kernel(storage, nx, ny, bc, one, two):
+    import torch
+    lat, ref = (_lattice(nx, ny, storage, bc) for _ in range(2))
+    assert lat.next_launch(3)[0] == lat.next_launch(9)[0] == "tiles"
+    assert lat.next_launch(1)[:2] == (one, 1)
+    assert lat.next_launch(2)[:2] == (two, 2)
+    ref.step_pairs = False
+    ref.set_resident_limit(0)
+    most = lat.next_launch(9)[1]
+    for n in (1, 2, most + 1, most + 2):
+        lat.step(n)
+        ref.step(n)
+    assert torch.equal(lat.get_populations(), ref.get_populations())
+    lat.close()
+    ref.close()
