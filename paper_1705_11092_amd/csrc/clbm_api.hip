@@ -320,6 +320,8 @@ int64_t tile_count(const LatDesc &d, int w, int h)
     return (int64_t)((d.nx + w - 1) / w) * ((d.ny + h - 1) / h);
 }
 
+clbm::Form form_of(const LatDesc &d) { return clbm::Form{d.force_mode == clbm::FM_FIELD, d.bc_y != 0}; }
+
 // The plan of the fused kernels for the lattice and its force (at creation
 // and when the force changes): the tile kernel, the sweep kernel or pairs,
 // whichever model gives the least time per step.  Tiles and sweeps cross near
@@ -338,7 +340,9 @@ void plan_fused(clbm_handle *h)
         h->tile = clbm::sc_tile_plan(d.nx, d.ny, d.storage, cus);
     if (!clbm::step2_supported(d)) return;
     double us = 0.0;
-    const clbm::TilePlan t = clbm::tile_plan(d.nx, d.ny, d.storage, (int64_t)clbm_buffer_bytes(d.nx, d.ny, d.storage), cus, &us);
+    const clbm::Form form = form_of(d);
+    const int64_t bytes = (int64_t)clbm_buffer_bytes(d.nx, d.ny, d.storage);
+    const clbm::TilePlan t = clbm::tile_plan(d.nx, d.ny, d.storage, bytes, cus, &us, form);
     if (eb != 2 && d.nx >= 64 && d.ny >= 64) {
         const clbm::SweepPlan p =
             clbm::sweep_plan(d.nx, d.ny, eb, 4 * cus, clbm::sweep_max_vec(d.storage, d.force_mode, d.bc_y));
@@ -348,10 +352,9 @@ void plan_fused(clbm_handle *h)
         }
     }
     const int64_t pair_tiles = tile_count(d, clbm::tile_w(clbm::kTile64x16), clbm::tile_h(clbm::kTile64x16, d.storage));
-    if (tile_offsets_fit(d) && us < clbm::pair_us(d.storage, pair_tiles, cus) / 2) {
+    if (tile_offsets_fit(d) && us < clbm::pair_us(d.storage, pair_tiles, cus, clbm::pair_form(d.storage, form)) / 2) {
         h->tile = t;
-        h->brief = clbm::ShortRun{t.shape, d.storage, d.bc_y != 0, t.tiles, pair_tiles, nodes,
-                                  (int64_t)clbm_buffer_bytes(d.nx, d.ny, d.storage)};
+        h->brief = clbm::ShortRun{t.shape, d.storage, form.walls, t.tiles, pair_tiles, nodes, bytes};
     }
 }
 
@@ -970,23 +973,43 @@ int step_class(const clbm_batch *b, const clbm_handle *h)
 void batch_regions(clbm_batch *b)
 {
     for (int st = 0; st < kStorageKinds; ++st) {
+        // Tiles of all the lattices, and in units of tiles what they cost with
+        // each lattice's form (a group with walls in it runs the kernel for
+        // walls throughout).
         int64_t pairs = 0, bytes = 0, tiles[clbm::kRegionShapes] = {};
+        double pair_cost = 0.0, cost[clbm::kRegionShapes] = {};
+        auto candidate = [&](const clbm_handle *h) { return h->d.storage == st && h->pairs < 0 && use_pairs(h); };
+        bool walls[clbm::kKernelKeys] = {};
+        for (const auto *h : b->lats)
+            if (candidate(h)) walls[clbm::kernel_key(h->d)] |= h->d.bc_y != 0;
         for (const auto *h : b->lats) {
             const LatDesc &d = h->d;
-            if (d.storage != st || h->pairs >= 0 || !use_pairs(h)) continue;
-            pairs += tile_count(d, clbm::tile_w(clbm::kTile64x16), clbm::tile_h(clbm::kTile64x16, st));
+            if (!candidate(h)) continue;
+            const clbm::Form form{form_of(d).field, walls[clbm::kernel_key(d)]};
+            const int64_t np = tile_count(d, clbm::tile_w(clbm::kTile64x16), clbm::tile_h(clbm::kTile64x16, st));
+            pairs += np;
+            pair_cost += np * clbm::pair_form(st, form);
             bytes += (int64_t)clbm_buffer_bytes(d.nx, d.ny, st);
-            for (int shape = 0; shape < clbm::kRegionShapes; ++shape)
-                tiles[shape] += tile_count(d, clbm::region_tile_w(shape), clbm::region_tile_h(shape));
+            for (int shape = 0; shape < clbm::kRegionShapes; ++shape) {
+                const int64_t n = tile_count(d, clbm::region_tile_w(shape), clbm::region_tile_h(shape));
+                tiles[shape] += n;
+                cost[shape] += n * clbm::tile_form(shape, st, form);
+            }
         }
         b->region[st] = -1;
-        // Pairs of many ragged lattices run 8 % over one lattice's time per tile
-        // (256 lattices of 32^2 .. 512^2 in FP16-SR: pairs 74.0 us per step,
-        // 64 x 32 regions 69.1).
-        double best = 1.08 * clbm::pair_us(st, pairs, b->cus) / 2;
+        if (!pairs) continue;
+        // Against one lattice's time per tile, tiles of many ragged lattices gain
+        // 2 % on pairs, in 16-bit storage rounded to nearest 6 % (256 lattices of
+        // 32^2 .. 512^2, us per step, tiles and pairs by model, then measured:
+        // FP16-SR periodic 46.5 / 48.2, 45.7 / 46.8; walls and force fields 53.5 /
+        // 51.8, 55.5 / 51.5; FP16 walls, fields and rows mixed 46.9 / 45.1, 42.6 /
+        // 46.8).
+        const double gain = st == CLBM_F16 || st == CLBM_BF16 ? 1.06 : 1.02;
+        double best = gain * clbm::pair_us(st, pairs, b->cus, pair_cost / pairs) / 2;
         for (int shape = 0; shape < clbm::kRegionShapes; ++shape) {
             if (!clbm::region_compiled(shape, st)) continue;
-            const double us = clbm::tile_us(shape, st, tiles[shape], bytes, b->cus) / clbm::region_steps(shape);
+            const double us = clbm::tile_us(shape, st, tiles[shape], bytes, b->cus, cost[shape] / tiles[shape]) /
+                              clbm::region_steps(shape);
             if (us < best) {
                 best = us;
                 b->region[st] = shape;

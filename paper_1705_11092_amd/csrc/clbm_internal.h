@@ -273,9 +273,10 @@ constexpr int region_h(int shape)
     default: return 16;
     }
 }
-// 64 x 48 only in 16-bit storage, where three of its 48 KB of LDS share a
-// compute unit (FP32 one of 96 KB: 1024^2 7.5 against 6.8 us per step in 64 x 32;
-// FP64 would need 192 KB).
+// 64 x 48 only in 16-bit storage, where three blocks of its 48 KB of LDS share a
+// compute unit (two between walls or with a force field, whose kernels take 82 to
+// 124 VGPRs against 65 to 79: tile_form) (FP32 one of 96 KB: 1024^2 7.5 against
+// 6.8 us per step in 64 x 32; FP64 would need 192 KB).
 constexpr bool region_compiled(int shape, int storage)
 {
     return shape != kRegion64x48 || !(storage == ST_F64 || storage == ST_F32);
@@ -298,7 +299,9 @@ struct TilePlan {
 // 32 x 16 5.6, 11.3, 111; 64 x 32 9.8, 10.8, 91.  FP64 10.4, 41; 12.0, 40;
 // 8.2, 13.7, 168; 6.0, 15.8, 184; 13.9, 15.8, 194.  FP16-SR 10.0, 36; 11.5, 31;
 // 8.1, 11.5, 106; 6.0, 12.7, 125; 13.2, 14.0, 97; 64 x 48 18.5, 19.2, 93.
-inline double tile_us(int shape, int storage, int64_t tiles, int64_t bytes, int cus)
+// Those flows were periodic with a constant or row force; form is tile_form's
+// factor of the lattices.
+inline double tile_us(int shape, int storage, int64_t tiles, int64_t bytes, int cus, double form = 1.0)
 {
     struct Fit { double fixed, per; };
     static const Fit fit[4][kRegionShapes] = {
@@ -312,19 +315,51 @@ inline double tile_us(int shape, int storage, int64_t tiles, int64_t bytes, int 
     // Tiles of FP32 and FP64 take longer where the two buffers no longer fit the
     // 256 MB Infinity Cache.
     const double miss = 2 * bytes > (int64_t)256 << 20 ? (t == 0 ? 1.17 : (t == 1 ? 1.08 : 1.0)) : 1.0;
-    return fit[t][shape].fixed + fit[t][shape].per * miss * n;
+    return fit[t][shape].fixed + fit[t][shape].per * miss * form * n;
+}
+
+// What a lattice's steps carry beside the collision.
+struct Form {
+    bool field, walls;  // a force per node; walls in y
+};
+
+// Time of a tile's steps against a periodic lattice without a force field, in
+// 16-bit storage: between walls the 64-wide regions take 22 to 34 registers more
+// and one block less shares a compute unit; a field takes them 6 to 10 and its
+// loads (us per launch at 4096^2 FP16, periodic, field, walls: 64 x 48 280, 314,
+// 325; 64 x 32 277, 294, 335; 64 x 16 321, 334, 353; FP16-SR 64 x 48 318, 358,
+// 372; 64 x 32 328, 333, 382).  In FP32 and FP64 all regions take 3 to 9 % more,
+// and the choice is the same.
+inline double tile_form(int shape, int storage, Form f)
+{
+    if (storage == ST_F64 || storage == ST_F32) return 1.0;
+    const bool nearest = storage == ST_F16 || storage == ST_BF16;
+    switch (shape) {
+    case kRegion64x48: return f.walls ? 1.17 : (f.field ? 1.12 : 1.0);
+    case kRegion64x32: return f.walls ? (nearest ? 1.21 : 1.15) : (f.field ? (nearest ? 1.06 : 1.02) : 1.0);
+    case kRegion64x16: return f.walls ? 1.09 : (f.field ? 1.03 : 1.0);
+    case kRegion32x16: return f.walls ? 1.03 : 1.0;
+    default: return 1.0;
+    }
+}
+// The same of a fused pair, whose field loads are not hidden by more steps
+// (4096^2 FP16 153 -> 175, FP16-SR 170 -> 186; walls cost nothing).
+inline double pair_form(int storage, Form f)
+{
+    if (storage == ST_F64 || storage == ST_F32 || !f.field) return 1.0;
+    return storage == ST_F16 || storage == ST_BF16 ? 1.13 : 1.08;
 }
 
 // Microseconds of one launch of a fused pair on `tiles` tiles of 64 x 16
 // nodes (64 x 8 in FP64), four and more of which share a compute unit.
-inline double pair_us(int storage, int64_t tiles, int cus)
+inline double pair_us(int storage, int64_t tiles, int cus, double form = 1.0)
 {
-    const double per = storage == ST_F64 ? 3.2 : (storage == ST_F32 ? 3.35 : (storage == ST_F16 || storage == ST_BF16 ? 2.27 : 2.5));
-    return 6.0 + per * tiles / cus;
+    const double per = storage == ST_F64 ? 3.2 : (storage == ST_F32 ? 3.35 : (storage == ST_F16 || storage == ST_BF16 ? 2.27 : 2.55));
+    return 6.0 + per * form * tiles / cus;
 }
 
 // The plan with the least time per step, which goes to *us_per_step.
-inline TilePlan tile_plan(int nx, int ny, int storage, int64_t bytes, int cus, double *us_per_step)
+inline TilePlan tile_plan(int nx, int ny, int storage, int64_t bytes, int cus, double *us_per_step, Form form = Form{})
 {
     TilePlan best{};
     for (int shape = 0; shape < kRegionShapes; ++shape) {
@@ -337,7 +372,7 @@ inline TilePlan tile_plan(int nx, int ny, int storage, int64_t bytes, int cus, d
         const int64_t tiles = (int64_t)p.tiles_x * ((ny + th - 1) / th);
         if (tiles > INT32_MAX) continue;
         p.tiles = (int32_t)tiles;
-        const double us = tile_us(shape, storage, tiles, bytes, cus) / p.steps;
+        const double us = tile_us(shape, storage, tiles, bytes, cus, tile_form(shape, storage, form)) / p.steps;
         if (best.steps == 0 || us < *us_per_step) {
             best = p;
             *us_per_step = us;

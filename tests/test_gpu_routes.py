@@ -80,3 +80,23 @@ def test_last_steps_of_a_run_take_the_cheaper_kernel(storage, nx, ny, bc, one, t
     assert torch.equal(lat.get_populations(), ref.get_populations())
     lat.close()
     ref.close()
+
+
+def test_16_bit_plans_weigh_walls_and_force_fields():
+    # The tall regions lose a block per compute unit to walls and fields.
+    import torch
+    for storage, nx, ny, bc, force, want in [
+            ("f16sr", 2900, 2890, 0, "const", ("tiles", 4, 64, 48)),
+            ("f16sr", 2900, 2890, 0, "kolmogorov", ("tiles", 4, 64, 48)),
+            ("f16sr", 2900, 2890, 0, "field", ("tiles", 4, 64, 32)),
+            ("f16sr", 2900, 2890, 1, "const", ("pair", 2, 0, 0)),
+            ("bf16", 2900, 2890, 1, "const", ("pair", 2, 0, 0)),
+            ("f32", 1200, 1210, 1, "field", ("tiles", 4, 64, 32))]:
+        lat, ref = (_lattice(nx, ny, storage, bc, force) for _ in range(2))
+        assert lat.next_launch(8) == want, (storage, bc, force)
+        ref.step_pairs = False
+        lat.step(5)
+        ref.step(5)
+        assert torch.equal(lat.get_populations(), ref.get_populations()), (storage, bc, force)
+        lat.close()
+        ref.close()
