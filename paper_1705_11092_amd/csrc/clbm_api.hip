@@ -352,7 +352,13 @@ void plan_fused(clbm_handle *h)
         }
     }
     const int64_t pair_tiles = tile_count(d, clbm::tile_w(clbm::kTile64x16), clbm::tile_h(clbm::kTile64x16, d.storage));
-    if (tile_offsets_fit(d) && us < clbm::pair_us(d.storage, pair_tiles, cus, clbm::pair_form(d.storage, form)) / 2) {
+    // Pairs only beyond what the models miss in 16-bit storage (FP16-SR with
+    // walls, us per step, tiles and pairs: 1500^2 14.2 / 14.6 where the models
+    // say 14.2 / 14.2, 2048^2 24.3 / 23.0 for 25.4 / 23.4; FP16 2048^2 21.1 / 20.9
+    // for 22.1 / 21.2, 3000^2 44.5 / 42.7 for 44.1 / 42.1).
+    const double gain = d.storage == CLBM_F16_SR || d.storage == CLBM_BF16_SR ? 1.05 : (eb == 2 ? 1.03 : 1.0);
+    const double pairs = clbm::pair_us(d.storage, pair_tiles, cus, clbm::pair_form(d.storage, form)) / 2;
+    if (tile_offsets_fit(d) && us < gain * pairs) {
         h->tile = t;
         h->brief = clbm::ShortRun{t.shape, d.storage, form.walls, t.tiles, pair_tiles, nodes, bytes};
     }
