@@ -914,19 +914,16 @@ int vec_for(int storage, int vec_bytes)
 
 }  // namespace
 
-struct clbm_batch {
-    std::vector<clbm_handle *> lats;  // caller's order
+namespace {
+
+// How the lattices of a batch are laid out for a call: their groups and tiles
+// under a region shape per storage type.
+struct BatchPlan {
+    int region[kStorageKinds] = {};   // LDS-tile region shape per storage type, or -1: pairs
+    bool made = false;                // the members below are up to date
     std::vector<int> order;           // table position -> caller index (grouped by kind)
     std::vector<int> keys;            // group key of each lattice when ordered
     std::vector<int> per;             // steps per launch of each lattice (caller's order)
-    hipStream_t stream = nullptr;
-    hipStream_t cap = nullptr;        // capture-only stream, created on first graph
-    // Groups beyond the first run on side streams, forked from and joined
-    // back to the launching stream around every step (also inside graphs).
-    std::vector<hipStream_t> side;
-    hipEvent_t fork = nullptr;
-    std::vector<hipEvent_t> join;
-    LatDesc *d_lats = nullptr;        // device lattice table (stream-ordered)
     struct Group {
         int storage, key, vec, l_lo, l_hi;  // key = clbm::kernel_key
         int64_t ntiles;
@@ -937,17 +934,35 @@ struct clbm_batch {
         bool small;                   // pairs: every buffer below 4 GB
         bool walls;                   // a lattice of the group has walls
         int per;                      // steps per launch
+        int64_t most;                 // most steps a lattice of the group takes in this call
     };
     std::vector<Group> groups;
     std::vector<LatDesc> tab;         // host copy of the table's geometry
     int32_t *d_tile_lat = nullptr;    // tile -> lattice map of every group (stream-ordered)
     int64_t tile_lat_cap = 0;         // entries allocated
     bool map_dirty = true;            // geometry changed since the map was built
+    hipGraphExec_t graph = nullptr;
+};
+
+}  // namespace
+
+struct clbm_batch {
+    std::vector<clbm_handle *> lats;  // caller's order
+    hipStream_t stream = nullptr;
+    hipStream_t cap = nullptr;        // capture-only stream, created on first graph
+    // Groups beyond the first run on side streams, forked from and joined
+    // back to the launching stream around every step (also inside graphs).
+    std::vector<hipStream_t> side;
+    hipEvent_t fork = nullptr;
+    std::vector<hipEvent_t> join;
+    LatDesc *d_lats = nullptr;        // device lattice table (stream-ordered), uploaded by each call
+    // Plan 0, and those of calls of one and two steps where their regions
+    // differ (tiles_take), each made on its first call.
+    static constexpr int kPlans = 3;
+    BatchPlan plan[kPlans];
     int variant = 0;
     int cus = 256;
-    int region[kStorageKinds] = {};   // LDS-tile region shape per storage type, or -1
     int chunk = 64;                   // steps per captured graph (a multiple of every group's steps per launch)
-    hipGraphExec_t graph = nullptr;
 };
 
 namespace {
@@ -965,27 +980,28 @@ int pair_shape(int variant_shape, const clbm::LatDesc &d)
 // How a lattice of a batch steps: singly, in pairs of one of two tile shapes
 // or in LDS tiles (whose region shape the whole group shares).
 enum StepClass { kSingle = 0, kPair0 = 1, kPair1 = 2, kLdsTiles = 3, kStepClasses = 4 };
-int step_class(const clbm_batch *b, const clbm_handle *h)
+int step_class(const clbm_batch *b, const BatchPlan &p, const clbm_handle *h)
 {
     const PairVariant &pv = pair_of(b->variant);
     if (!use_pairs(h)) return kSingle;
-    if (pv.tiles && h->pairs < 0 && b->region[h->d.storage] >= 0 && tile_offsets_fit(h->d)) return kLdsTiles;
+    if (pv.tiles && h->pairs < 0 && p.region[h->d.storage] >= 0 && tile_offsets_fit(h->d)) return kLdsTiles;
     return kPair0 + pair_shape(pv.shape, h->d);
 }
 
 // Region shape of the lattices of each storage type that may step in LDS
 // tiles: the one with the least modelled time per step for all their tiles,
-// or -1 where pairs take less.
+// or -1 where pairs take less; in calls of one or two steps also where a tile
+// launch of those would take more than the pair kernel's (tiles_take).
 void batch_regions(clbm_batch *b)
 {
     for (int st = 0; st < kStorageKinds; ++st) {
         // Tiles of all the lattices, and in units of tiles what they cost with
         // each lattice's form (a group with walls in it runs the kernel for
         // walls throughout).
-        int64_t pairs = 0, bytes = 0, tiles[clbm::kRegionShapes] = {};
+        int64_t pairs = 0, bytes = 0, nodes = 0, tiles[clbm::kRegionShapes] = {};
         double pair_cost = 0.0, cost[clbm::kRegionShapes] = {};
         auto candidate = [&](const clbm_handle *h) { return h->d.storage == st && h->pairs < 0 && use_pairs(h); };
-        bool walls[clbm::kKernelKeys] = {};
+        bool walls[clbm::kKernelKeys] = {}, any_walls = false;
         for (const auto *h : b->lats)
             if (candidate(h)) walls[clbm::kernel_key(h->d)] |= h->d.bc_y != 0;
         for (const auto *h : b->lats) {
@@ -996,14 +1012,16 @@ void batch_regions(clbm_batch *b)
             pairs += np;
             pair_cost += np * clbm::pair_form(st, form);
             bytes += (int64_t)clbm_buffer_bytes(d.nx, d.ny, st);
+            nodes += (int64_t)d.nx * d.ny;
+            any_walls |= form.walls;
             for (int shape = 0; shape < clbm::kRegionShapes; ++shape) {
                 const int64_t n = tile_count(d, clbm::region_tile_w(shape), clbm::region_tile_h(shape));
                 tiles[shape] += n;
                 cost[shape] += n * clbm::tile_form(shape, st, form);
             }
         }
-        b->region[st] = -1;
-        if (!pairs) continue;
+        int &region = b->plan[0].region[st];
+        region = -1;
         // Against one lattice's time per tile, tiles of many ragged lattices gain
         // 2 % on pairs, in 16-bit storage rounded to nearest 6 % (256 lattices of
         // 32^2 .. 512^2, us per step, tiles and pairs by model, then measured:
@@ -1011,15 +1029,19 @@ void batch_regions(clbm_batch *b)
         // 51.8, 55.5 / 51.5; FP16 walls, fields and rows mixed 46.9 / 45.1, 42.6 /
         // 46.8).
         const double gain = st == CLBM_F16 || st == CLBM_BF16 ? 1.06 : 1.02;
-        double best = gain * clbm::pair_us(st, pairs, b->cus, pair_cost / pairs) / 2;
+        double best = pairs ? gain * clbm::pair_us(st, pairs, b->cus, pair_cost / pairs) / 2 : 0.0;
         for (int shape = 0; shape < clbm::kRegionShapes; ++shape) {
-            if (!clbm::region_compiled(shape, st)) continue;
+            if (!pairs || !clbm::region_compiled(shape, st)) continue;
             const double us = clbm::tile_us(shape, st, tiles[shape], bytes, b->cus, cost[shape] / tiles[shape]) /
                               clbm::region_steps(shape);
             if (us < best) {
                 best = us;
-                b->region[st] = shape;
+                region = shape;
             }
+        }
+        for (int left = 1; left < clbm_batch::kPlans; ++left) {
+            const clbm::ShortRun run{region, st, any_walls, region < 0 ? 0 : tiles[region], pairs, nodes, bytes};
+            b->plan[left].region[st] = region >= 0 && clbm::tiles_take(left, run, b->cus) ? region : -1;
         }
     }
 }
@@ -1027,44 +1049,43 @@ void batch_regions(clbm_batch *b)
 // Launch group of a lattice: how it steps, storage type and kernel (storage
 // scheme, force mode, forcing scheme).
 constexpr int kGroupKeys = kStepClasses * kStorageKinds * clbm::kKernelKeys;
-int group_key(const clbm_batch *b, const clbm_handle *h)
+int group_key(const clbm_batch *b, const BatchPlan &p, const clbm_handle *h)
 {
-    return (step_class(b, h) * kStorageKinds + h->d.storage) * clbm::kKernelKeys + clbm::kernel_key(h->d);
+    return (step_class(b, p, h) * kStorageKinds + h->d.storage) * clbm::kKernelKeys + clbm::kernel_key(h->d);
 }
 
 // Table order: grouped by tile shape, storage and kernel (one launch per
 // group), caller order inside a group.
-void batch_order(clbm_batch *b)
+void batch_order(const clbm_batch *b, BatchPlan &p)
 {
-    b->order.clear();
-    b->keys.clear();
-    batch_regions(b);
-    for (auto *h : b->lats) b->keys.push_back(group_key(b, h));
+    p.order.clear();
+    p.keys.clear();
+    for (auto *h : b->lats) p.keys.push_back(group_key(b, p, h));
     for (int key = 0; key < kGroupKeys; ++key)
         for (size_t j = 0; j < b->lats.size(); ++j)
-            if (b->keys[j] == key) b->order.push_back((int)j);
+            if (p.keys[j] == key) p.order.push_back((int)j);
 }
 
 // Geometry of the current variant: per lattice nodes per thread, tile
 // shape and first tile; per group its lattice range and tile count.
-void batch_geometry(clbm_batch *b)
+void batch_geometry(const clbm_batch *b, BatchPlan &p)
 {
-    b->groups.clear();
+    p.groups.clear();
     int64_t tbase = 0;
-    b->tab.assign(b->order.size(), LatDesc());
-    b->per.assign(b->order.size(), 1);
+    p.tab.assign(p.order.size(), LatDesc());
+    p.per.assign(p.order.size(), 1);
     size_t pos = 0;
-    while (pos < b->order.size()) {
-        const clbm_handle *h0 = b->lats[b->order[pos]];
+    while (pos < p.order.size()) {
+        const clbm_handle *h0 = b->lats[p.order[pos]];
         const LatDesc &d0 = h0->d;
-        const int key = group_key(b, h0);
-        const int cls = step_class(b, h0), st = d0.storage;
+        const int key = group_key(b, p, h0);
+        const int cls = step_class(b, p, h0), st = d0.storage;
         const int vec = cls == kSingle ? vec_for(st, single_of(b->variant).vec_bytes) : 4;
         const int lo = (int)pos;
         size_t end = pos;
-        while (end < b->order.size() && group_key(b, b->lats[b->order[end]]) == key) ++end;
+        while (end < p.order.size() && group_key(b, p, b->lats[p.order[end]]) == key) ++end;
         // Tile size of the fused steps in the group's shape.
-        const int shape = cls == kLdsTiles ? b->region[st] : (cls == kPair1 ? 1 : 0);
+        const int shape = cls == kLdsTiles ? p.region[st] : (cls == kPair1 ? 1 : 0);
         const int tw = cls == kLdsTiles ? clbm::region_tile_w(shape) : clbm::tile_w(shape);
         const int th = cls == kLdsTiles ? clbm::region_tile_h(shape) : clbm::tile_h(shape, st);
         const int per = cls == kLdsTiles ? clbm::region_steps(shape) : (cls == kSingle ? 1 : 2);
@@ -1072,7 +1093,7 @@ void batch_geometry(clbm_batch *b)
         size_t bytes = 0, largest = 0;
         bool walls = false;
         for (; pos < end; ++pos) {
-            LatDesc d = b->lats[b->order[pos]]->d;
+            LatDesc d = b->lats[p.order[pos]]->d;
             clbm::tile_geometry(d.pitch, d.ny, vec, &d.tpr, &d.inv_tpr, &d.ntiles);
             if (cls != kSingle) {  // the fused kernel's tiles, and their walk
                 const int tx = (d.nx + tw - 1) / tw, ty = (d.ny + th - 1) / th;
@@ -1082,42 +1103,43 @@ void batch_geometry(clbm_batch *b)
             }
             d.vec = vec;
             d.per = per;
-            b->per[b->order[pos]] = per;
+            p.per[p.order[pos]] = per;
             d.tile0 = tiles;
             tiles += d.ntiles;
             const size_t one = clbm_buffer_bytes(d.nx, d.ny, d.storage);
             bytes += 2 * one;
             largest = std::max(largest, one);
             walls = walls || d.bc_y;
-            b->tab[pos] = d;
+            p.tab[pos] = d;
         }
         const int cap = single_of(b->variant).cap;
         const size_t lds = lds_for_occupancy(cap < 0 ? default_occupancy(st, bytes) : cap);
         const bool small = largest + 4096 < ((size_t)1 << 32);
-        b->groups.push_back({st, clbm::kernel_key(d0), vec, lo, (int)pos, tiles, tbase, lds, cls, shape, small, walls,
-                             per});
+        p.groups.push_back({st, clbm::kernel_key(d0), vec, lo, (int)pos, tiles, tbase, lds, cls, shape, small, walls,
+                            per, 0});
         tbase += tiles;
     }
-    b->map_dirty = true;
-    retire_graph(b->graph, b->stream);
-    b->graph = nullptr;
+    p.map_dirty = true;
+    retire_graph(p.graph, b->stream);
+    p.graph = nullptr;
+    p.made = true;
 }
 
 // Refresh the table from the lattices (force, parity) with the steps each
 // takes in this call, and send it to the device through kernel arguments.
 // With `spare`, in-place lattices write there instead of into their state
 // (the autotuner's timed launches).
-int batch_upload(clbm_batch *b, const int64_t *nsteps, void *spare = nullptr)
+int batch_upload(clbm_batch *b, BatchPlan &p, const int64_t *nsteps, void *spare = nullptr)
 {
-    clbm::UploadPayload p;
-    const int count = (int)b->order.size();
+    clbm::UploadPayload load;
+    const int count = (int)p.order.size();
     for (int first = 0; first < count; first += clbm::kUploadMax) {
         const int n = std::min(clbm::kUploadMax, count - first);
         for (int k = 0; k < n; ++k) {
             const int pos = first + k;
-            const clbm_handle *h = b->lats[b->order[pos]];
+            const clbm_handle *h = b->lats[p.order[pos]];
             LatDesc d = h->d;
-            const LatDesc &g = b->tab[pos];
+            const LatDesc &g = p.tab[pos];
             d.tpr = g.tpr;
             d.inv_tpr = g.inv_tpr;
             d.vec = g.vec;
@@ -1126,44 +1148,72 @@ int batch_upload(clbm_batch *b, const int64_t *nsteps, void *spare = nullptr)
             d.walk = g.walk;
             d.per = g.per;
             d.parity = h->parity;
-            d.steps = (int32_t)nsteps[b->order[pos]];
+            d.steps = (int32_t)nsteps[p.order[pos]];
             if (spare && d.inplace) d.buf[1] = spare;
-            p.d[k] = d;
+            load.d[k] = d;
         }
-        HIPCHK(clbm::launch_upload(b->d_lats, first, n, p, b->stream));
+        HIPCHK(clbm::launch_upload(b->d_lats, first, n, load, b->stream));
     }
-    if (b->map_dirty) {
+    if (p.map_dirty) {
         // Tile -> lattice map of the new geometry.  Graphs that read the old
         // map were retired with the old geometry; the old map is freed in
         // stream order behind their launches.
-        const int64_t total = b->groups.empty() ? 0 : b->groups.back().tbase + b->groups.back().ntiles;
-        if (total > b->tile_lat_cap) {
-            if (b->d_tile_lat) HIPCHK(hipFreeAsync(b->d_tile_lat, b->stream));
-            b->d_tile_lat = nullptr;
-            b->tile_lat_cap = 0;
-            HIPCHK(hipMallocAsync(reinterpret_cast<void **>(&b->d_tile_lat),
+        const int64_t total = p.groups.empty() ? 0 : p.groups.back().tbase + p.groups.back().ntiles;
+        if (total > p.tile_lat_cap) {
+            if (p.d_tile_lat) HIPCHK(hipFreeAsync(p.d_tile_lat, b->stream));
+            p.d_tile_lat = nullptr;
+            p.tile_lat_cap = 0;
+            HIPCHK(hipMallocAsync(reinterpret_cast<void **>(&p.d_tile_lat),
                                   sizeof(int32_t) * (size_t)total, b->stream));
-            b->tile_lat_cap = total;
+            p.tile_lat_cap = total;
         }
-        for (const auto &g : b->groups)
-            HIPCHK(clbm::launch_tile_map(b->d_lats, g.l_lo, g.l_hi, g.ntiles, b->d_tile_lat + g.tbase,
+        for (const auto &g : p.groups)
+            HIPCHK(clbm::launch_tile_map(b->d_lats, g.l_lo, g.l_hi, g.ntiles, p.d_tile_lat + g.tbase,
                                          b->stream));
-        b->map_dirty = false;
+        p.map_dirty = false;
     }
     return CLBM_OK;
 }
 
-// A force change since the last call can move a lattice to another kernel
-// (force mode): regroup before launching.
-void batch_refresh(clbm_batch *b)
+// Regions anew, and with them every plan, each when a call next takes it.
+void batch_replan(clbm_batch *b)
 {
-    for (size_t j = 0; j < b->lats.size(); ++j) {
-        if (group_key(b, b->lats[j]) != b->keys[j]) {
-            batch_order(b);
-            batch_geometry(b);
-            return;
-        }
+    batch_regions(b);
+    for (auto &p : b->plan) p.made = false;
+}
+
+bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(s, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
+}
+
+// The plan of a call whose lattices take at most n steps.  A plan's first call
+// allocates and fills its tile map, which a captured call would leave to the
+// replays: there plan 0 serves until the other is there.
+BatchPlan &batch_pick(clbm_batch *b, int64_t n)
+{
+    BatchPlan &p = b->plan[n < clbm_batch::kPlans ? n : 0];
+    if (std::equal(p.region, p.region + kStorageKinds, b->plan[0].region)) return b->plan[0];
+    return (!p.made || p.map_dirty) && capturing(b->stream) ? b->plan[0] : p;
+}
+
+// The same, made.  A force change since the last call can move a lattice to
+// another kernel (force mode): regroup before launching.
+BatchPlan &batch_plan(clbm_batch *b, int64_t n)
+{
+    BatchPlan *p = &batch_pick(b, n);
+    bool same = p->made;
+    for (size_t j = 0; same && j < b->lats.size(); ++j) same = group_key(b, *p, b->lats[j]) == p->keys[j];
+    if (p->made && !same) {
+        batch_replan(b);
+        p = &batch_pick(b, n);
     }
+    if (!p->made) {
+        batch_order(b, *p);
+        batch_geometry(b, *p);
+    }
+    return *p;
 }
 
 // Side streams and events for groups 1 .. n-1 (default priority).
@@ -1189,18 +1239,18 @@ int batch_side_streams(clbm_batch *b, size_t n)
 // group 0 on s, the others on side streams forked from s once and joined back
 // to it after their n steps (a group of small lattices alone leaves HBM idle
 // in its tail; measured +15 % on a batch of FP32 and FP16 lattices).  Within a
-// group the steps follow each other in stream order.  A group whose lattices
-// take at most (*most)[k] steps gets no launches beyond them (a graph, which
-// other counts replay, has them all).
+// group the steps follow each other in stream order.  With
+// `cut`, a group gets no launches beyond its `most` steps (a graph, which other
+// counts replay, has them all).
 constexpr int kTimedSteps = 8;
-int batch_launch_steps(clbm_batch *b, int n, hipStream_t s, int which = 3, bool first = false,
-                       const std::vector<int64_t> *most = nullptr)
+int batch_launch_steps(clbm_batch *b, const BatchPlan &p, int n, hipStream_t s, int which = 3, bool first = false,
+                       bool cut = false)
 {
     const Variant &v = single_of(b->variant);
     const PairVariant &pv = pair_of(b->variant);
     const int64_t grid = v.blocks_per_cu ? (int64_t)b->cus * v.blocks_per_cu : INT32_MAX;
     const int64_t pgrid = pv.blocks_per_cu ? (int64_t)b->cus * pv.blocks_per_cu : 0;
-    const size_t ng = b->groups.size();
+    const size_t ng = p.groups.size();
     if (ng > 1) {
         int rc = batch_side_streams(b, ng - 1);
         if (rc) return rc;
@@ -1212,11 +1262,11 @@ int batch_launch_steps(clbm_batch *b, int n, hipStream_t s, int which = 3, bool 
     const int end = first ? kTimedSteps : n;
     for (int t = 0; t < end; ++t) {
         for (size_t k = 0; k < ng; ++k) {
-            const auto &g = b->groups[k];
+            const auto &g = p.groups[k];
             if (!(which & (g.cls == kSingle ? 1 : 2)) || t % g.per || (first && g.cls == kSingle && t)) continue;
-            if (most && t >= (*most)[k]) continue;
+            if (cut && t >= g.most) continue;
             hipStream_t gs = k == 0 ? s : b->side[k - 1];
-            const int32_t *map = b->d_tile_lat + g.tbase;
+            const int32_t *map = p.d_tile_lat + g.tbase;
             const int sub = first ? 0 : t / g.per;
             if (g.cls == kLdsTiles)
                 HIPCHK(clbm::launch_batch_tile(g.storage, b->d_lats, map, g.ntiles, g.key, g.walls, g.shape, sub, gs));
@@ -1235,14 +1285,14 @@ int batch_launch_steps(clbm_batch *b, int n, hipStream_t s, int which = 3, bool 
     return CLBM_OK;
 }
 
-int batch_build_graph(clbm_batch *b)
+int batch_build_graph(clbm_batch *b, BatchPlan &p)
 {
     hipGraph_t g = nullptr;
     if (!b->cap) HIPCHK(hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking));
     HIPCHK(hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal));
-    const int rc = batch_launch_steps(b, b->chunk, b->cap);
+    const int rc = batch_launch_steps(b, p, b->chunk, b->cap);
     hipError_t le = rc == CLBM_OK
-                        ? clbm::launch_batch_advance(b->d_lats, (int)b->order.size(), b->chunk, b->cap)
+                        ? clbm::launch_batch_advance(b->d_lats, (int)p.order.size(), b->chunk, b->cap)
                         : hipSuccess;
     hipError_t ce = hipStreamEndCapture(b->cap, &g);
     if (rc != CLBM_OK || le != hipSuccess) {
@@ -1250,7 +1300,7 @@ int batch_build_graph(clbm_batch *b)
         return rc != CLBM_OK ? rc : hip_fail(le, "launch_batch_advance (capture)");
     }
     if (ce != hipSuccess) return hip_fail(ce, "hipStreamEndCapture");
-    hipError_t ie = hipGraphInstantiate(&b->graph, g, nullptr, nullptr, 0);
+    hipError_t ie = hipGraphInstantiate(&p.graph, g, nullptr, nullptr, 0);
     (void)hipGraphDestroy(g);
     if (ie != hipSuccess) return hip_fail(ie, "hipGraphInstantiate");
     return CLBM_OK;
@@ -1270,39 +1320,37 @@ int batch_run(clbm_batch *b, const int64_t *nsteps)
             return fail(CLBM_EINVAL, "a Shan-Chen lattice steps alone, not in a batch");
     }
     if (maxn == 0) return CLBM_OK;
-    batch_refresh(b);
-    int rc = batch_upload(b, nsteps);
+    BatchPlan &p = batch_plan(b, maxn);
+    int rc = batch_upload(b, p, nsteps);
     if (rc) return rc;
     // Tiles (four or eight steps per launch) and long launches run as fast
     // launch by launch: no graph to capture on the first call (12 lattices of
     // 10^2 .. 80^2 FP64, 100 steps: 371 -> 190 us; 12 served solves in four
     // groups, first call and 1000 uneven steps: 12.3 -> 11.8 ms; 16 lattices of
     // 16^2 .. 40^2 in four groups 2.0 -> 1.5 us per step).
-    bool direct = b->groups.size() == 1 && b->groups[0].ntiles >= 4096;
+    bool direct = p.groups.size() == 1 && p.groups[0].ntiles >= 4096;
     if (!direct) {
         direct = true;
-        for (const auto &g : b->groups) direct = direct && g.cls == kLdsTiles;
+        for (const auto &g : p.groups) direct = direct && g.cls == kLdsTiles;
     }
     int64_t left = maxn;
     while (!direct && left >= b->chunk) {
-        if (!b->graph && (rc = batch_build_graph(b))) return rc;
-        HIPCHK(hipGraphLaunch(b->graph, b->stream));
+        if (!p.graph && (rc = batch_build_graph(b, p))) return rc;
+        HIPCHK(hipGraphLaunch(p.graph, b->stream));
         left -= b->chunk;
     }
     if (left > 0) {
-        std::vector<int64_t> most;
-        for (const auto &g : b->groups) {
-            int64_t m = 0;
-            for (int j = g.l_lo; j < g.l_hi; ++j) m = std::max(m, nsteps[b->order[j]] - (maxn - left));
-            most.push_back(m);
+        for (auto &gr : p.groups) {
+            gr.most = 0;
+            for (int j = gr.l_lo; j < gr.l_hi; ++j) gr.most = std::max(gr.most, nsteps[p.order[j]] - (maxn - left));
         }
-        if ((rc = batch_launch_steps(b, (int)left, b->stream, 3, false, &most))) return rc;
-        HIPCHK(clbm::launch_batch_advance(b->d_lats, (int)b->order.size(), (int)left, b->stream));
+        if ((rc = batch_launch_steps(b, p, (int)left, b->stream, 3, false, true))) return rc;
+        HIPCHK(clbm::launch_batch_advance(b->d_lats, (int)p.order.size(), (int)left, b->stream));
     }
     for (size_t j = 0; j < b->lats.size(); ++j) {
         // Buffers flip once per launch; every chunk but a lattice's last
         // holds whole launches.
-        const int64_t launches = (nsteps[j] + b->per[j] - 1) / b->per[j];
+        const int64_t launches = (nsteps[j] + p.per[j] - 1) / p.per[j];
         b->lats[j]->parity = (int)((b->lats[j]->parity + launches) & 1);
         b->lats[j]->steps += nsteps[j];
     }
@@ -1354,14 +1402,13 @@ int clbm_batch_create(clbm_handle *const *lattices, int32_t count, void *stream,
     b->lats = v;
     b->stream = static_cast<hipStream_t>(stream);
     b->cus = compute_units();
-    batch_order(b);
+    batch_replan(b);
     hipError_t e = hipMallocAsync(reinterpret_cast<void **>(&b->d_lats), sizeof(LatDesc) * count,
                                   b->stream);
     if (e != hipSuccess) {
         delete b;
         return hip_fail(e, "clbm_batch_create allocation");
     }
-    batch_geometry(b);
     *out = b;
     return CLBM_OK;
 }
@@ -1390,8 +1437,7 @@ int clbm_batch_set_variant(clbm_batch *b, int32_t variant)
     if (variant < 0 || variant >= kNumVariants) return fail(CLBM_EINVAL, "variant out of range");
     if (variant == b->variant) return CLBM_OK;
     b->variant = variant;
-    batch_order(b);  // the groups of a per-lattice tile shape differ
-    batch_geometry(b);
+    batch_replan(b);  // the groups of a per-lattice tile shape differ
     return CLBM_OK;
 }
 
@@ -1406,7 +1452,6 @@ int clbm_batch_autotune(clbm_batch *b, const char *cache_path, int32_t *chosen)
         if (h->d.force_mode == clbm::FM_SC)
             return fail(CLBM_EINVAL, "a Shan-Chen lattice steps alone, not in a batch");
     }
-    batch_refresh(b);
     const std::string sig = batch_signature(b);
     if (cache_path) {
         std::ifstream in(cache_path);
@@ -1446,15 +1491,16 @@ int clbm_batch_autotune(clbm_batch *b, const char *cache_path, int32_t *chosen)
     // step singly, kTimedSteps of those that step fused.
     auto time_variant = [&](int v, int which, float *ms) -> int {
         int r = clbm_batch_set_variant(b, v);
-        std::vector<int64_t> counts(b->lats.size());
-        for (size_t j = 0; j < counts.size(); ++j) counts[j] = b->per[j];
-        if (!r) r = batch_upload(b, counts.data(), spare);
+        if (r) return r;
+        BatchPlan &p = batch_plan(b, clbm_batch::kPlans);
+        std::vector<int64_t> counts(p.per.begin(), p.per.end());
+        r = batch_upload(b, p, counts.data(), spare);
         const int reps = 5;
-        for (int w = 0; w < 2 && r == CLBM_OK; ++w) r = batch_launch_steps(b, 1, b->stream, which, true);
+        for (int w = 0; w < 2 && r == CLBM_OK; ++w) r = batch_launch_steps(b, p, 1, b->stream, which, true);
         if (r) return r;
         hipError_t e = hipEventRecord(t0, b->stream);
         for (int k = 0; k < reps && r == CLBM_OK && e == hipSuccess; ++k)
-            r = batch_launch_steps(b, 1, b->stream, which, true);
+            r = batch_launch_steps(b, p, 1, b->stream, which, true);
         if (r) return r;
         if (e == hipSuccess) e = hipEventRecord(t1, b->stream);
         if (e == hipSuccess) e = hipEventSynchronize(t1);
@@ -1502,9 +1548,11 @@ int clbm_batch_autotune(clbm_batch *b, const char *cache_path, int32_t *chosen)
 int clbm_batch_destroy(clbm_batch *b)
 {
     if (!b) return CLBM_OK;
-    retire_graph(b->graph, b->stream);
+    for (auto &p : b->plan) {
+        retire_graph(p.graph, b->stream);
+        if (p.d_tile_lat) (void)hipFreeAsync(p.d_tile_lat, b->stream);
+    }
     if (b->d_lats) (void)hipFreeAsync(b->d_lats, b->stream);
-    if (b->d_tile_lat) (void)hipFreeAsync(b->d_tile_lat, b->stream);
     if (b->cap) (void)hipStreamDestroy(b->cap);
     for (auto st : b->side) (void)hipStreamDestroy(st);
     for (auto ev : b->join) (void)hipEventDestroy(ev);

@@ -100,3 +100,32 @@ def test_16_bit_plans_weigh_walls_and_force_fields():
         assert torch.equal(lat.get_populations(), ref.get_populations()), (storage, bc, force)
         lat.close()
         ref.close()
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16sr"])
+def test_short_batch_calls_between_long_ones(storage):
+    # Calls of one and two steps may step in pairs where longer ones step in
+    # tiles; force changes in between regroup both.
+    import torch
+
+    from paper_1705_11092_amd import clbm
+    sizes = [(700, 650), (640, 700), (333, 1000), (900, 400), (16, 16), (500, 777)]
+    lats, refs = ([_lattice(nx, ny, storage, k % 2, ["const", "field", "kolmogorov"][k % 3])
+                   for k, (nx, ny) in enumerate(sizes)] for _ in range(2))
+    for lat in refs:
+        lat.step_pairs = False
+        lat.set_resident_limit(0)
+    batch = clbm.Batch(lats)
+    for call, n in enumerate((1, 9, 2, 1, 2, 5, 1, 70, 2, 3, 1)):
+        counts = [n if (k + call) % 3 else n - 1 for k in range(len(lats))]
+        batch.step_each(counts)
+        for lat, c in zip(refs, counts):
+            lat.step(c)
+        if call in (3, 7):
+            for lat in (lats[call % 6], refs[call % 6]):
+                lat.set_force("kolmogorov", params=(2e-4, 2))
+        for lat, ref, size in zip(lats, refs, sizes):
+            assert torch.equal(lat.get_populations(), ref.get_populations()), (storage, call, size)
+    batch.close()
+    for lat in lats + refs:
+        lat.close()
