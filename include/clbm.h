@@ -244,8 +244,12 @@ int clbm_get_populations(clbm_handle *h, double *f);
 int clbm_set_populations(clbm_handle *h, const double *f);
 
 /* Steps per captured hipGraph replay in clbm_step; 0 launches every step
- * directly.  By default 64 where launches are short (lattices of up to 600,000
- * nodes that step singly or in pairs) and 0 elsewhere. */
+ * directly.  By default 64 where launches are short (lattices that step singly
+ * or in pairs with up to 256 MB of traffic per step) and 0 elsewhere: the
+ * launches of LDS tiles and of the four-step kernel run as fast directly, but
+ * the calling thread then queues each (about 4 us per launch of four or eight
+ * steps).  A lattice stepping with those replays graphs of at least eight
+ * launches (16, 32 or 64 steps); fewer steps asked for launch directly. */
 int clbm_set_graph_steps(clbm_handle *h, int32_t steps);
 
 /* Cap on the step kernel's resident blocks per compute unit (0 = none, or

@@ -370,17 +370,11 @@ void plan_fused(clbm_handle *h)
 bool use_tiles(const clbm_handle *h) { return h->pairs < 0 && h->tile.steps != 0; }
 bool use_sweeps(const clbm_handle *h) { return h->pairs < 0 && h->sweep.vec != 0; }
 
-// Steps per graph replay.  By default graphs only serve launches shorter than
-// what the host needs to queue them, about 6 us (in place 256^2: 4.7 us per step
-// through graphs, 5.7 without): the tile and sweep kernels and large lattices
-// take longer, run as fast launch by launch, and a first run saves the
-// capture (64 x 32 FP64, 200 steps: 320 -> 248 us, 246 on a repeat).
-constexpr int kGraphSteps = 64;
-constexpr int64_t kGraphMaxNodes = 600000;
+// Steps per graph replay (clbm::graph_steps).
 int graph_steps_of(const clbm_handle *h)
 {
-    if (h->graph_steps >= 0) return h->graph_steps;
-    return use_tiles(h) || use_sweeps(h) || (int64_t)h->d.nx * h->d.ny > kGraphMaxNodes ? 0 : kGraphSteps;
+    const int fused = use_tiles(h) ? h->tile.steps : (use_sweeps(h) ? clbm::kSweepSteps : 0);
+    return clbm::graph_steps(h->graph_steps, fused, (int64_t)clbm_buffer_bytes(h->d.nx, h->d.ny, h->d.storage));
 }
 
 // Whether a run of n steps goes to the resident kernel.  By default tiny

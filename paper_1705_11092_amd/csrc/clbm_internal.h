@@ -435,6 +435,26 @@ inline TilePlan sc_tile_plan(int nx, int ny, int storage, int cus)
     return us[1] < us[0] ? p[1] : p[0];
 }
 
+// Steps per graph replay of a lattice (0: launch by launch), from those asked
+// for (-1: the default), the fused steps of a launch of the tile or sweep kernel
+// (0: single steps or pairs) and the bytes of a buffer.  Launch by launch each
+// single step or pair takes 0.3 to 0.7 us more than in a replay (in place FP32
+// 512^2 6.1 / 5.4 us, 900^2 12.6 / 12.3, 2000 x 1200 31.5 / 31.1; 3000^2 equal),
+// so they replay 64 steps by default up to 256 MB of traffic per step.  Launches
+// of the tile and sweep kernels take longer than the host needs to queue them and
+// run as fast without a capture (64 x 32 FP64, 512 steps: 0.60 ms either way); a
+// replay of a few of them is slower (of two steps 4.3 ms), so one asked for
+// serves from eight launches on.
+constexpr int kGraphSteps = 64;
+constexpr int64_t kGraphMaxTraffic = (int64_t)256 << 20;
+constexpr int kGraphMinFused = 8;
+inline int graph_steps(int asked, int fused, int64_t bytes)
+{
+    if (fused) return asked >= kGraphMinFused * fused ? asked : 0;
+    if (asked >= 0) return asked;
+    return 2 * bytes <= kGraphMaxTraffic ? kGraphSteps : 0;
+}
+
 // Lattice descriptors carried in one upload kernel's arguments.
 constexpr int kUploadMax = 12;
 struct UploadPayload {
