@@ -4,6 +4,8 @@
 // the launchers.  The step kernels themselves live in clbm_step.h and are
 // instantiated one storage type per translation unit (clbm_step_*.hip),
 // so the library builds in parallel.
+#include <algorithm>
+
 #include "clbm_device.h"
 #include "clbm_internal.h"
 #include "clbm_force.h"
@@ -296,7 +298,8 @@ __global__ void k_force_field(R *field, int64_t n, const double *fx, const doubl
 
 // One node per thread: blocks then pass over the planes in order.  (4096^2
 // FP32, us with a grid of 4096 blocks striding over the nodes and with this
-// one: start state 237 and 187, populations out 379 and 322.)
+// one: start state 241 and 186, populations out 388 and 328, in 402 and 332; at
+// 2000 x 1500 27 and 28, 66 and 59, 61 and 58; at 1200 x 1100 and below equal.)
 int helper_blocks(int64_t n)
 {
     return (int)((n + kBlock - 1) / kBlock);
@@ -481,10 +484,7 @@ hipError_t launch_psi(const LatDesc &d, int src, const double *rho, hipStream_t 
 
 hipError_t launch_set_populations(const LatDesc &d, int dst, const double *f, hipStream_t s)
 {
-    // One node per thread on large lattices (4096^2 FP32 397 -> 329 us), 3072
-    // blocks on smaller ones (2048 x 1025 39.6 -> 35.8).
-    int g = helper_blocks((int64_t)d.nx * d.ny);
-    if (g > 3072 && g <= 16384) g = 3072;
+    const int g = helper_blocks((int64_t)d.nx * d.ny);
     CLBM_BY_STORAGE(k_set_pop, g, d, dst, f);
     return hipGetLastError();
 }
@@ -533,7 +533,10 @@ hipError_t launch_force_field(const LatDesc &d, void *field, const double *fx, c
                               hipStream_t s)
 {
     const int64_t n = (int64_t)d.nx * d.ny;
-    const int g = helper_blocks(n);
+    // At most 16384 blocks: larger fields stride (us, one node per thread, 16384
+    // and 4096 blocks: FP64 3000^2 60, 52, 54; FP32 3600 x 3500 55, 48, 50;
+    // 4096^2 74, 78, 83).
+    const int g = std::min(helper_blocks(n), 16384);
     if (d.storage == ST_F64)
         k_force_field<double><<<g, kBlock, 0, s>>>(static_cast<double *>(field), n, fx, fy);
     else

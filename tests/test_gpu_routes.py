@@ -129,3 +129,25 @@ def test_short_batch_calls_between_long_ones(storage):
     batch.close()
     for lat in lats + refs:
         lat.close()
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32"])
+def test_large_force_fields_and_populations_reach_every_node(storage):
+    # More nodes than the force field's grid has threads.  Without momentum the
+    # velocity is F / 2 rho; these forces (24 bits or fewer) are stored exactly.
+    import torch
+
+    from paper_1705_11092_amd import clbm
+    nx, ny = 3100, 2803
+    lat = clbm.Lattice(nx, ny, RATES, storage=storage)
+    k = torch.arange(nx * ny, device="cuda", dtype=torch.float64).reshape(ny, nx)
+    fx, fy = k * 2.0**-40, (nx * ny - k) * 2.0**-40
+    lat.set_force("field", fx=fx, fy=fy)
+    lat.set_populations(torch.ones((9, ny, nx), device="cuda", dtype=torch.float64))
+    rho, ux, uy, _ = lat.moments(totals=False)
+    assert torch.equal(ux, 0.5 * fx / rho) and torch.equal(uy, 0.5 * fy / rho)
+    f = torch.rand((9, ny, nx), device="cuda", dtype=torch.float32).to(torch.float64)
+    lat.set_populations(f)
+    # The deviations from the rest weights are stored: one rounding each way.
+    assert float((lat.get_populations() - f).abs().max()) <= (2.0**-52 if storage == "f64" else 2.0**-24)
+    lat.close()
