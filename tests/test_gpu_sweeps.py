@@ -1,0 +1,70 @@
+"""The sweep kernel (four fused steps in registers) where each lane takes two
+columns, and beyond 4 GB, against the one-step kernel, bitwise.
+
+The plan chooses between one column per lane and two by the lattice's size, so
+each case asserts what it runs: even widths, and odd ones, whose last group is
+ragged (the seam), periodic and between walls, under every force mode.
+"""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+RATES = (1.0, 1.2, 1.25, 1.25, 1.1, 1.1)
+
+
+def _lattice(nx, ny, storage, bc, force, scheme):
+    # A seeded noisy state made on the device (these lattices are large).
+    import torch
+
+    from paper_1705_11092_amd import clbm
+    lat = clbm.Lattice(nx, ny, RATES, storage=storage, bc_y="bounceback" if bc else "periodic", scheme=scheme)
+    g = torch.Generator(device="cuda").manual_seed(nx + 7 * ny)
+
+    def noise(amp):
+        return amp * (2.0 * torch.rand((ny, nx), generator=g, device="cuda", dtype=torch.float64) - 1.0)
+    if force == "field":
+        lat.set_force("field", fx=noise(1e-4), fy=noise(1e-4))
+    elif force == "kolmogorov":
+        lat.set_force("kolmogorov", params=(1e-4, 3))
+    else:
+        lat.set_force("const", params=(1e-4, -5e-5))
+    lat.init(1.0 + noise(0.01), noise(0.02), noise(0.02))
+    return lat
+
+
+def _compare(nx, ny, storage, bc, force, scheme, columns, counts):
+    import torch
+    out = []
+    for fused in (True, False):
+        lat = _lattice(nx, ny, storage, bc, force, scheme)
+        if fused:
+            assert lat.next_launch(8)[:3] == ("sweep", 4, columns)
+        else:
+            lat.step_pairs = False
+        for n in counts:
+            lat.step(n)
+        out.append(lat.moments(totals=False)[:3] if nx * ny > 30_000_000 else (lat.get_populations(),))
+        lat.close()
+        del lat
+    assert all(bool(torch.isfinite(a).all()) for a in out[0])
+    assert all(torch.equal(a, b) for a, b in zip(*out)), f"{nx}x{ny} {storage} bc={bc} {force} {scheme}"
+    del out
+    torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("storage,nx,ny,bc,force,scheme", [
+    ("f32", 3000, 3000, 0, "const", "consistent"),      # whole groups
+    ("f32", 3000, 3000, 1, "field", "guo_lbl"),
+    ("f32", 4096, 4096, 1, "kolmogorov", "consistent"),
+    ("f32", 1849, 4096, 0, "const", "premnath"),        # the seam of an odd row
+    ("f32", 1849, 4096, 1, "field", "consistent"),
+    ("f32", 1737, 8000, 0, "field", "guo_lbl"),
+    ("f32", 1737, 8000, 1, "const", "guo_lbl"),
+    ("f32", 1851, 8000, 0, "kolmogorov", "consistent"),
+    ("f32", 3001, 8000, 1, "kolmogorov", "consistent"),
+    ("f64", 4096, 4096, 0, "kolmogorov", "consistent"),
+    ("f64", 3133, 8000, 0, "const", "guo_lbl"),
+    ("f64", 3251, 8000, 0, "kolmogorov", "consistent"),
+])
+def test_two_columns_per_lane_match_one_step(storage, nx, ny, bc, force, scheme):
+    _compare(nx, ny, storage, bc, force, scheme, 2, (4, 11))
