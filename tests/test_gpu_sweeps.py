@@ -68,3 +68,15 @@ def _compare(nx, ny, storage, bc, force, scheme, columns, counts):
 ])
 def test_two_columns_per_lane_match_one_step(storage, nx, ny, bc, force, scheme):
     _compare(nx, ny, storage, bc, force, scheme, 2, (4, 11))
+
+
+@pytest.mark.parametrize("storage,n,bc,force,columns", [
+    ("f32", 11000, 1, "kolmogorov", 2), ("f32", 11000, 0, "field", 2),
+    ("f64", 7800, 0, "const", 2), ("f64", 7800, 1, "kolmogorov", 1),
+])
+def test_sweeps_above_4gb_match_one_step(storage, n, bc, force, columns):
+    # Buffers of more than 4 GB, the default kernel: velocities and densities of
+    # two sweeps, and of two sweeps, a pair and a step.
+    from paper_1705_11092_amd import clbm
+    assert clbm.buffer_bytes(n, n, storage) > 2**32
+    _compare(n, n, storage, bc, force, "consistent", columns, (8, 11))
