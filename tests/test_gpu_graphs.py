@@ -106,3 +106,34 @@ def test_batches_of_tiles_and_in_place_lattices_through_several_chunks(storage):
     batch.close()
     for lat in lats + refs:
         lat.close()
+
+
+def test_captured_short_batch_calls():
+    # Calls of one step have a plan of their own, whose tile map a captured call
+    # must not leave to the replays: eager calls before a replay would read it.
+    import torch
+
+    from paper_1705_11092_amd import clbm
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        lats, refs = ([_lattice(nx, ny, "f16") for nx, ny in ((768, 760), (500, 700))] for _ in range(2))
+        batch = clbm.Batch(lats, stream=stream)
+        batch.step(9)
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            batch.step(1)
+            batch.step(1)  # two launches: the replay leaves each state in the buffer it took it from
+        batch.step(1)      # eager, before any replay
+        batch.step(1)
+        for _ in range(3):
+            graph.replay()
+        batch.step(1)
+        for ref in refs:
+            ref.step_pairs = False
+            ref.step(9 + 2 + 3 * 2 + 1)
+        for lat, ref in zip(lats, refs):
+            assert torch.equal(lat.get_populations(), ref.get_populations())
+        batch.close()
+        for lat in lats + refs:
+            lat.close()
