@@ -951,7 +951,7 @@ struct clbm_batch {
     std::vector<hipEvent_t> join;
     LatDesc *d_lats = nullptr;        // device lattice table (stream-ordered), uploaded by each call
     // Plan 0, and those of calls of one and two steps where their regions
-    // differ (tiles_take), each made on its first call.
+    // differ (tiles_take), those made on their first call.
     static constexpr int kPlans = 3;
     BatchPlan plan[kPlans];
     int variant = 0;
@@ -1403,6 +1403,7 @@ int clbm_batch_create(clbm_handle *const *lattices, int32_t count, void *stream,
         delete b;
         return hip_fail(e, "clbm_batch_create allocation");
     }
+    (void)batch_plan(b, clbm_batch::kPlans);
     *out = b;
     return CLBM_OK;
 }
@@ -1432,6 +1433,7 @@ int clbm_batch_set_variant(clbm_batch *b, int32_t variant)
     if (variant == b->variant) return CLBM_OK;
     b->variant = variant;
     batch_replan(b);  // the groups of a per-lattice tile shape differ
+    (void)batch_plan(b, clbm_batch::kPlans);
     return CLBM_OK;
 }
 

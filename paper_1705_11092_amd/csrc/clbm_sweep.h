@@ -146,7 +146,7 @@ struct Held {
 };
 
 template <int ST, int FM, int SCH, int K, int V, bool WALL, bool SEAM>
-__device__ __forceinline__ void sweep_strip(const LatDesc &d, int src, int q, int base, bool store, int ya, int yb,
+__device__ __forceinline__ void sweep_strip(const LatDesc &d, int src, int base, bool store, int ya, int yb,
                                             const Seam &seam)
 {
     using S = Storage<ST>;
@@ -404,9 +404,9 @@ k_sweep(LatDesc d, int src, SweepPlan p)
     const int r = d.nx - (p.groups - 1) * V;
     const Seam seam{qw == p.groups - 1 && r != V ? r : 0};
     if (__any(seam.r))
-        sweep_strip<ST, FM, SCH, K, V, WALL, true>(d, src, q, qw * V, store, ya, yb, seam);
+        sweep_strip<ST, FM, SCH, K, V, WALL, true>(d, src, qw * V, store, ya, yb, seam);
     else
-        sweep_strip<ST, FM, SCH, K, V, WALL, false>(d, src, q, qw * V, store, ya, yb, seam);
+        sweep_strip<ST, FM, SCH, K, V, WALL, false>(d, src, qw * V, store, ya, yb, seam);
 }
 
 }  // namespace
