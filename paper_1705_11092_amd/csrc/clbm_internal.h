@@ -391,10 +391,11 @@ inline TilePlan tile_plan(int nx, int ny, int storage, int64_t bytes, int cus, d
 // 30, 28 / 33; FP32 1500^2 25 / 31, 30 / 39; FP16 1500^2 17 / 19; but 512^2 FP64
 // 8.1 / 7.3, FP16 768^2 8.4 / 7.2), unless its tiles cover much more than the
 // lattice, or than the pairs' tiles do (16 x 20000 FP32 9.0 / 6.0 for one step,
-// 11.7 / 13.4 for two; 64 x 20003 17.7 / 17.9, 24.0 / 22.4); between walls 16-bit
-// tiles run at a lower occupancy (FP16 2048^2 36 / 35, 52 / 47).  Tiles of one
-// round are launch-bound: equal.  Three steps take one launch instead of two
-// (0.4 to 1.0 of their time).
+// 11.7 / 13.4 for two; 64 x 20003 17.7 / 17.9, 24.0 / 22.4; 16-bit in many rounds
+// of 32 x 16 regions, FP16 64 x 20003 24.9 / 17.2 for two, 768^2 12.2 / 12.2);
+// between walls 16-bit tiles run at a lower occupancy (FP16 2048^2 36 / 35, 52 /
+// 47).  Tiles of one round are launch-bound: equal.  Three steps take one launch
+// instead of two (0.4 to 1.0 of their time).
 struct ShortRun {
     int32_t shape, storage;
     bool walls;
@@ -407,11 +408,15 @@ inline bool tiles_take(int64_t left, const ShortRun &r, int cus)
     if (both > 256 * mb) return false;
     const double cells = (double)r.tiles * region_tile_w(r.shape) * region_tile_h(r.shape);
     const double pair_cells = (double)r.pair_tiles * tile_w(kTile64x16) * tile_h(kTile64x16, r.storage);
-    double most = r.shape == kRegion32x16 ? 1.2 : 1.3;
-    if (r.storage == ST_F64) most = both >= 40 * mb ? 1.5 : 1.0;
-    const bool narrow = !(r.storage == ST_F64 || r.storage == ST_F32);  // 16-bit
-    if (left == 1) return (narrow ? !r.walls && both >= 64 * mb : both >= 40 * mb) && cells <= most * (double)r.nodes;
-    if (narrow && r.walls && both >= 32 * mb) most = 0.9;
+    const bool f64 = r.storage == ST_F64, narrow = !(f64 || r.storage == ST_F32);  // narrow: 16-bit
+    const bool work = both >= (narrow ? 64 : 40) * mb;
+    if (left == 1) {
+        const double most = f64 ? 1.5 : (r.shape == kRegion32x16 ? 1.2 : 1.3);
+        return work && !(narrow && r.walls) && cells <= most * (double)r.nodes;
+    }
+    double most = f64 ? (work ? 1.5 : 1.0) : 1.3;
+    if (!f64 && r.shape == kRegion32x16) most = !narrow ? 1.2 : (r.tiles > 9 * cus ? 0.6 : 1.3);
+    if (narrow && r.walls && both >= 32 * mb && most > 0.9) most = 0.9;
     return cells <= most * pair_cells;
 }
 
