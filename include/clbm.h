@@ -269,10 +269,12 @@ int clbm_set_occupancy(clbm_handle *h, int32_t blocks_per_cu);
  * step n + 1 on a tile (64 x 16 nodes, 64 x 8 for FP64) and a one-node halo
  * from HBM, keeps it in LDS, and computes step n + 2 from there, so the state
  * crosses HBM once per two steps.  The default takes up to four or eight steps
- * per launch in LDS tiles (lattices of up to about a million nodes, and any
- * Shan-Chen lattice), four in a kernel that marches down the rows with four
- * time levels in registers (larger FP32 and FP64 lattices), and otherwise
- * pairs.  Every node update is the one-step kernel's, so results are bitwise
+ * per launch in LDS tiles (FP32 lattices of up to some 2000^2 nodes, FP64 up to
+ * some 1500^2, most 16-bit and all Shan-Chen lattices), four in a kernel that
+ * marches down the rows with four time levels in registers (larger FP32 and FP64
+ * lattices), and otherwise pairs (large 16-bit lattices between walls); the last
+ * one or two steps of a run take a single step or a pair where that is faster.
+ * Every node update is the one-step kernel's, so results are bitwise
  * equal (stochastic rounding included: a node's operand depends on its index
  * and values only).  In-place lattices always step singly, and Shan-Chen ones
  * under 0 or 1.  clbm_get_step_pairs returns 1 when this lattice takes two or
@@ -334,7 +336,10 @@ double clbm_s_from_nu(double nu);
  * kernel launch per time step (or per two, four or eight fused steps) and
  * kernel kind.
  * Each node is updated by exactly the arithmetic of clbm_step, so a
- * lattice's result is bitwise the same alone and in any batch. */
+ * lattice's result is bitwise the same alone and in any batch.
+ * Calls of many steps replay a captured hipGraph of 64 steps, unless all lattices
+ * step in LDS tiles or the batch is one large group: then the calling thread
+ * queues every launch (about 4 us per group and four or eight steps). */
 typedef struct clbm_batch clbm_batch;
 
 /* Build a batch over count >= 1 existing handles (not owned; they must

@@ -325,10 +325,11 @@ clbm::Form form_of(const LatDesc &d) { return clbm::Form{d.force_mode == clbm::F
 // The plan of the fused kernels for the lattice and its force (at creation
 // and when the force changes): the tile kernel, the sweep kernel or pairs,
 // whichever model gives the least time per step.  Tiles and sweeps cross near
-// a million nodes.  The 16-bit types have no sweeps (their pair kernel is as
-// fast: FP16-SR 4096^2 202 against 181 GLUPS) and go from tiles to pairs
-// (FP16-SR, us per step in tiles and pairs: 512^2 3.1 / 3.9, 768^2 6.2 / 6.4,
-// 1024^2 8.4 / 8.4).
+// 2000^2 nodes in FP32 and 1500^2 in FP64.  The 16-bit types have no sweeps
+// (slower than pairs: FP16-SR 4096^2 181 against 202 GLUPS) and step in tiles at
+// every size, or in pairs between walls where they are large (FP16-SR, us per
+// step in tiles and pairs: 512^2 3.0 / 4.3, 1024^2 7.1 / 8.4, 4096^2 79.6 / 85.3;
+// between walls 1024^2 8.0 / 8.3, 4096^2 93.0 / 84.9).
 void plan_fused(clbm_handle *h)
 {
     const LatDesc &d = h->d;

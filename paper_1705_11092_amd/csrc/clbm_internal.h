@@ -515,7 +515,7 @@ hipError_t launch_sweep(const LatDesc &d, int src, const SweepPlan &p, hipStream
 template <int ST>
 hipError_t launch_sweep_st(const LatDesc &d, int src, const SweepPlan &p, hipStream_t s);
 // n <= p.steps fused steps from buffer src into src ^ 1 under a plan of
-// tile_plan: as step2_supported, buffers below 4 G elements.
+// tile_plan: as step2_supported, buffers below 4 GB (32-bit byte offsets).
 hipError_t launch_tile(const LatDesc &d, int src, int n, const TilePlan &p, hipStream_t s);
 template <int ST>
 hipError_t launch_tile_st(const LatDesc &d, int src, int n, const TilePlan &p, hipStream_t s);

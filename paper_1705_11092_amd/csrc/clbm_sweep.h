@@ -22,10 +22,11 @@
 // result is bitwise that of K one-step launches.
 //
 // What bounds it: VALU issue in FP32 (4096^2: 148 instructions per update with
-// the halo, 95 % of issue at the 2.19 GHz the chip holds, 73 us per step against
-// 106 in pairs); in FP64 its longer instructions and the latency of two waves
-// per SIMD (122 against 197 us).  Four levels: a fifth or sixth lost more to halo
-// and registers than the state's traffic gives back.
+// the halo, 92 to 95 % of issue at the clock the chip holds, 2.16 to 2.19 GHz from
+// box to box, 73 to 77 us per step against 106 in pairs); in FP64 its longer
+// instructions and the latency of two waves per SIMD (122 to 133 against 197 us).
+// Four levels: a fifth or sixth lost more to halo and registers than the state's
+// traffic gives back.
 #pragma once
 
 #include <type_traits>
@@ -367,9 +368,9 @@ __device__ __forceinline__ void sweep_strip(const LatDesc &d, int src, int base,
     if constexpr (sizeof(R) == 4) {
         // The steady part: after every level has started, and with walls
         // while level 1 stays below the upper one and level K above the lower
-        // one.  116 VALU instructions per update against 135 (66 of them
-        // moves) with the conditions, 201 VGPRs against 171.  In FP64 it would
-        // spill 450 registers.
+        // one.  129 VALU instructions per update collided (1030 for the 8 of an
+        // iteration with two columns) against 135 (66 of the 1080 moves) with the
+        // conditions, 201 VGPRs against 171.  In FP64 it would spill 450 registers.
         int t1 = 2 * (K - 1), t2 = iters - 1;
         if (WALL) {
             t1 = t1 > K - first ? t1 : K - first;
@@ -382,8 +383,8 @@ __device__ __forceinline__ void sweep_strip(const LatDesc &d, int src, int base,
 }
 
 // Waves per SIMD the compiler must leave room for: 2 with two columns per
-// lane (FP32 162-179 VGPRs; FP64 256), 3 with one (FP32 90-107, FP64 162-168),
-// but 2 in FP64 with a per-node force, which would spill.
+// lane (FP32 182-210 VGPRs; FP64 256), 3 with one (FP32 94-128, FP64 141-166),
+// but 2 in FP64 with a per-node force (157-176), which would spill.
 template <int ST, int FM, int V>
 constexpr int sweep_waves() { return V == 1 && !(ST == ST_F64 && FM == FM_FIELD) ? 3 : 2; }
 

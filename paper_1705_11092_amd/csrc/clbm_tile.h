@@ -18,7 +18,8 @@
 // stored, 64 x 48 1.15, 64 x 16 1.38) and the last, partly filled round of
 // tiles.  Hence small regions of eight steps where launches count, and the
 // tallest of 64 columns whose LDS still lets two blocks (FP32, FP64) or three
-// (16-bit) share a compute unit where the work does.  Us per step, pairs ->
+// (16-bit; two between walls, by their registers) share a compute unit where the
+// work does.  Us per step, pairs ->
 // tiles: 64 x 32 FP64 2.8 -> 1.17, 200^2 FP64 3.6 -> 1.3, 512^2 FP32 3.6 -> 2.5,
 // 1024^2 FP32 9.7 -> 5.9, 1501 x 703 FP64 17.1 -> 10.4, 4096^2 FP16 73.3 -> 68.0,
 // 2048^2 FP16-SR 23.9 -> 21.6.
