@@ -23,7 +23,7 @@
 //
 // What bounds it: VALU issue in FP32 (4096^2: 148 instructions per update with
 // the halo, 92 to 95 % of issue at the clock the chip holds, 2.16 to 2.19 GHz from
-// box to box, 73 to 77 us per step against 106 in pairs); in FP64 its longer
+// card to card, 73 to 77 us per step against 106 in pairs); in FP64 its longer
 // instructions and the latency of two waves per SIMD (122 to 133 against 197 us).
 // Four levels: a fifth or sixth lost more to halo and registers than the state's
 // traffic gives back.
